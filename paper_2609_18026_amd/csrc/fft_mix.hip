@@ -1,0 +1,582 @@
+// Mixed-radix FFTs for the lengths n = R1 R2 (R1, R2 of 2, 3, 4, 5, 6, 8, 9, 10, 12, 15, 16) other than
+// 256: a line is transformed in two passes held in registers, a radix-R1 pass, one exchange through
+// LDS and a radix-R2 pass,
+//   X[k1 + R1 k2] = sum_{n2} w_n^(k1 n2) w_R2^(k2 n2) sum_{n1} w_R1^(k1 n1) x[R2 n1 + n2],
+// where the Stockham passes of radices 2 to 5 in kernels.hip move every sample through LDS four to
+// seven times (they stay for the lengths with no such pair: 125, 162, 200, 216, 243 and 250 below
+// 256, and most lengths above).
+//
+// Kernels: the z transforms over contiguous lines, up to six fields in one launch, and the azimuthal
+// stages on groups of lines (the scalar transforms and nonlinear terms, and the vector stage of the
+// toroidal-poloidal RHS).
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+#include <cstdint>
+
+#include "dev_common.h"
+#include "mlg_internal.h"
+
+namespace mlg {
+namespace {
+
+using namespace ::mlg::dev;
+
+// cos and sin of 2 pi j / R
+template <int R>
+struct Root;
+template <>
+struct Root<6> {
+  static constexpr double c[6] = {1.0, 0.5, -0.5, -1.0, -0.5, 0.5};
+  static constexpr double s[6] = {0.0, 0.8660254037844386, 0.8660254037844386, 0.0, -0.8660254037844386,
+                                  -0.8660254037844386};
+};
+template <>
+struct Root<8> {
+  static constexpr double c[8] = {1.0, 0.7071067811865476, 0.0, -0.7071067811865476, -1.0, -0.7071067811865476, 0.0,
+                                  0.7071067811865476};
+  static constexpr double s[8] = {0.0, 0.7071067811865476, 1.0, 0.7071067811865476, 0.0, -0.7071067811865476, -1.0,
+                                  -0.7071067811865476};
+};
+template <>
+struct Root<9> {
+  static constexpr double c[9] = {1.0, 0.766044443118978, 0.17364817766693036, -0.5, -0.9396926207859084,
+                                  -0.9396926207859084, -0.5, 0.17364817766693036, 0.766044443118978};
+  static constexpr double s[9] = {0.0, 0.6427876096865394, 0.984807753012208, 0.8660254037844386,
+                                  0.3420201433256687, -0.3420201433256687, -0.8660254037844386, -0.984807753012208,
+                                  -0.6427876096865394};
+};
+template <>
+struct Root<10> {
+  static constexpr double c[10] = {1.0, 0.8090169943749475, 0.30901699437494745, -0.30901699437494745,
+                                   -0.8090169943749475, -1.0, -0.8090169943749475, -0.30901699437494745,
+                                   0.30901699437494745, 0.8090169943749475};
+  static constexpr double s[10] = {0.0, 0.5877852522924731, 0.9510565162951535, 0.9510565162951535,
+                                   0.5877852522924731, 0.0, -0.5877852522924731, -0.9510565162951535,
+                                   -0.9510565162951535, -0.5877852522924731};
+};
+template <>
+struct Root<12> {
+  static constexpr double c[12] = {1.0, 0.8660254037844386, 0.5, 0.0, -0.5, -0.8660254037844386, -1.0,
+                                   -0.8660254037844386, -0.5, 0.0, 0.5, 0.8660254037844386};
+  static constexpr double s[12] = {0.0, 0.5, 0.8660254037844386, 1.0, 0.8660254037844386, 0.5, 0.0, -0.5,
+                                   -0.8660254037844386, -1.0, -0.8660254037844386, -0.5};
+};
+template <>
+struct Root<15> {
+  static constexpr double c[15] = {1.0, 0.9135454576426009, 0.6691306063588582, 0.30901699437494745,
+                                   -0.10452846326765347, -0.5, -0.8090169943749475, -0.9781476007338057,
+                                   -0.9781476007338057, -0.8090169943749475, -0.5, -0.10452846326765347,
+                                   0.30901699437494745, 0.6691306063588582, 0.9135454576426009};
+  static constexpr double s[15] = {0.0, 0.4067366430758002, 0.7431448254773942, 0.9510565162951535,
+                                   0.9945218953682733, 0.8660254037844386, 0.5877852522924731, 0.20791169081775934,
+                                   -0.20791169081775934, -0.5877852522924731, -0.8660254037844386,
+                                   -0.9945218953682733, -0.9510565162951535, -0.7431448254773942,
+                                   -0.4067366430758002};
+};
+template <>
+struct Root<16> {
+  static constexpr double c[16] = {1.0, 0.9238795325112867, 0.7071067811865476, 0.3826834323650898, 0.0,
+                                   -0.3826834323650898, -0.7071067811865476, -0.9238795325112867, -1.0,
+                                   -0.9238795325112867, -0.7071067811865476, -0.3826834323650898, 0.0,
+                                   0.3826834323650898, 0.7071067811865476, 0.9238795325112867};
+  static constexpr double s[16] = {0.0, 0.3826834323650898, 0.7071067811865476, 0.9238795325112867, 1.0,
+                                   0.9238795325112867, 0.7071067811865476, 0.3826834323650898, 0.0,
+                                   -0.3826834323650898, -0.7071067811865476, -0.9238795325112867, -1.0,
+                                   -0.9238795325112867, -0.7071067811865476, -0.3826834323650898};
+};
+
+// multiply by exp(-+ 2 pi i J / R) (forward: minus); J and R are compile-time constants after unrolling
+template <int R, bool INV>
+__device__ __forceinline__ double2 rot(double2 a, int J) {
+  if (J == 0) return a;
+  if (4 * J == R) return cmul_mi(a, INV);
+  if (2 * J == R) return make_double2(-a.x, -a.y);
+  if (4 * J == 3 * R) return cmul_mi(a, !INV);
+  return cmul(a, make_double2(Root<R>::c[J], INV ? Root<R>::s[J] : -Root<R>::s[J]));
+}
+
+// In-register DFT of length R: v[n] -> V[k] = sum_n v[n] exp(-+ 2 pi i n k / R)
+template <int R, bool INV>
+struct Dft;
+template <bool INV>
+struct Dft<2, INV> {
+  static __device__ __forceinline__ void run(double2 (&v)[2]) {
+    const double2 a = v[0], b = v[1];
+    v[0] = cadd(a, b);
+    v[1] = csub(a, b);
+  }
+};
+template <bool INV>
+struct Dft<3, INV> {
+  static __device__ __forceinline__ void run(double2 (&v)[3]) {
+    constexpr double h = 0.86602540378443864676;  // sqrt(3) / 2
+    const double2 t1 = cadd(v[1], v[2]), t3 = cmul_mi(cscale(csub(v[1], v[2]), h), INV);
+    const double2 t2 = make_double2(v[0].x - 0.5 * t1.x, v[0].y - 0.5 * t1.y);
+    v[0] = cadd(v[0], t1);
+    v[1] = cadd(t2, t3);
+    v[2] = csub(t2, t3);
+  }
+};
+template <bool INV>
+struct Dft<4, INV> {
+  static __device__ __forceinline__ void run(double2 (&v)[4]) {
+    const double2 t0 = cadd(v[0], v[2]), t1 = csub(v[0], v[2]);
+    const double2 t2 = cadd(v[1], v[3]), t3 = cmul_mi(csub(v[1], v[3]), INV);
+    v[0] = cadd(t0, t2);
+    v[1] = cadd(t1, t3);
+    v[2] = csub(t0, t2);
+    v[3] = csub(t1, t3);
+  }
+};
+template <bool INV>
+struct Dft<5, INV> {
+  static __device__ __forceinline__ void run(double2 (&v)[5]) {
+    constexpr double c1 = 0.30901699437494742410, c2 = -0.80901699437494742410;  // cos 2 pi / 5, cos 4 pi / 5
+    constexpr double s1 = 0.95105651629515357212, s2 = 0.58778525229247312917;   // sin 2 pi / 5, sin 4 pi / 5
+    const double2 t1 = cadd(v[1], v[4]), t2 = cadd(v[2], v[3]), t3 = csub(v[1], v[4]), t4 = csub(v[2], v[3]);
+    const double2 r1 = make_double2(v[0].x + c1 * t1.x + c2 * t2.x, v[0].y + c1 * t1.y + c2 * t2.y);
+    const double2 r2 = make_double2(v[0].x + c2 * t1.x + c1 * t2.x, v[0].y + c2 * t1.y + c1 * t2.y);
+    const double2 i1 = cmul_mi(make_double2(s1 * t3.x + s2 * t4.x, s1 * t3.y + s2 * t4.y), INV);
+    const double2 i2 = cmul_mi(make_double2(s2 * t3.x - s1 * t4.x, s2 * t3.y - s1 * t4.y), INV);
+    v[0] = cadd(v[0], cadd(t1, t2));
+    v[1] = cadd(r1, i1);
+    v[4] = csub(r1, i1);
+    v[2] = cadd(r2, i2);
+    v[3] = csub(r2, i2);
+  }
+};
+// R = A B: n = B n1 + n2, k = k1 + A k2
+template <int A, int B, bool INV>
+struct DftAB {
+  static __device__ __forceinline__ void run(double2 (&v)[A * B]) {
+    double2 y[A][B];
+#pragma unroll
+    for (int n2 = 0; n2 < B; ++n2) {
+      double2 t[A];
+#pragma unroll
+      for (int n1 = 0; n1 < A; ++n1) t[n1] = v[B * n1 + n2];
+      Dft<A, INV>::run(t);
+#pragma unroll
+      for (int k1 = 0; k1 < A; ++k1) y[k1][n2] = rot<A * B, INV>(t[k1], n2 * k1);
+    }
+#pragma unroll
+    for (int k1 = 0; k1 < A; ++k1) {
+      Dft<B, INV>::run(y[k1]);
+#pragma unroll
+      for (int k2 = 0; k2 < B; ++k2) v[k1 + A * k2] = y[k1][k2];
+    }
+  }
+};
+template <bool INV> struct Dft<6, INV> : DftAB<2, 3, INV> {};
+template <bool INV> struct Dft<8, INV> : DftAB<2, 4, INV> {};
+template <bool INV> struct Dft<9, INV> : DftAB<3, 3, INV> {};
+template <bool INV> struct Dft<10, INV> : DftAB<2, 5, INV> {};
+template <bool INV> struct Dft<12, INV> : DftAB<3, 4, INV> {};
+template <bool INV> struct Dft<15, INV> : DftAB<3, 5, INV> {};
+template <bool INV> struct Dft<16, INV> : DftAB<4, 4, INV> {};
+
+// v[c] *= w_n^(e c), c = 1 .. R - 1, w_n = exp(-2 pi i / n) (conjugated for the inverse), e R <= n: the
+// powers 1, 2, 4, 8 come from the table, every other factor is a product of at most four of them
+template <int R, bool INV>
+__device__ __forceinline__ void twiddle(double2 (&v)[R], const double2* __restrict__ tw, int e) {
+  double2 w[R];
+#pragma unroll
+  for (int c = 1; c < R; ++c) {
+    const int top = c >= 8 ? 8 : (c >= 4 ? 4 : (c >= 2 ? 2 : 1));
+    if (c == top) {
+      w[c] = tw[c * e];
+      if (INV) w[c] = cconj(w[c]);
+    } else {
+      w[c] = cmul(w[top], w[c - top]);
+    }
+    v[c] = cmul(v[c], w[c]);
+  }
+}
+
+// the same with every factor from the table (c e < n): for stages whose lanes run over the lines first, where
+// a table read is a broadcast and the products' registers cost more
+template <int R, bool INV>
+__device__ __forceinline__ void twiddle_tab(double2 (&v)[R], const double2* __restrict__ tw, int e) {
+#pragma unroll
+  for (int c = 1; c < R; ++c) {
+    const double2 w = tw[c * e];
+    v[c] = cmul(v[c], INV ? cconj(w) : w);
+  }
+}
+
+// The lengths served, as R1 >= R2 with R1 as small as possible: one kernel instance per length, so that each
+// takes the registers of its own radices.  MIX_PAIRS: R2 <= 10, all stages; MIX_WIDE: the rest, which the
+// vector stage (three pairs of R2 values per lane) leaves to the kernel in kernels.hip.
+#define MIX_PAIRS(X) \
+  X(2, 2) X(3, 2) X(4, 2) X(3, 3) X(5, 2) X(4, 3) X(5, 3) X(4, 4) X(6, 3) X(5, 4) X(6, 4) X(5, 5) X(9, 3) \
+  X(6, 5) X(8, 4) X(6, 6) X(8, 5) X(9, 5) X(8, 6) X(10, 5) X(9, 6) X(10, 6) X(8, 8) X(9, 8) X(15, 5) X(10, \
+  8) X(9, 9) X(10, 9) X(12, 8) X(10, 10) X(12, 9) X(12, 10) X(16, 8) X(15, 9) X(16, 9) X(15, 10) X(16, 10)
+#define MIX_WIDE(X) \
+  X(15, 12) X(16, 12) X(15, 15) X(16, 15)
+
+__device__ __forceinline__ int kval(int kk, int nz) { return (2 * kk < nz) ? kk : kk - nz; }
+
+// ---------------------------------------------------------------- z transforms
+// Contiguous lines, lb lines per block.  Lane (line, n2) of the first pass loads x[n2 + R2 n1] straight
+// into registers; lane (line, k1) of the second stores X[k1 + R1 k2].  In LDS a line is R1 rows of RS
+// (R2 rounded up to odd) entries, so that the rows read by neighbouring lanes start in different
+// banks.  In place when in == out: every line belongs to one block, which has read it before the
+// barrier and writes it after.  Bound by memory: at 128^3 the six inverse transforms of the vector term take
+// 24 us (113 MB, 4.7 TB/s, the rate of a plain copy) against 72 us in six launches of zfft_kernel.
+struct ZMix {
+  int lb, mask_m, mask_k, kept_only;  // kept slots: |k| <= mask_k
+  int64_t rows, per_field;
+  const int32_t* row_m;
+  const double2* in[6];
+  double2* out[6];
+};
+
+template <int R1, int R2, bool INV>
+__global__ __launch_bounds__(256) void zmix_kernel(ZMix a, const double2* __restrict__ twg) {
+  extern __shared__ double2 smem[];
+  constexpr int n = R1 * R2, RS = R2 | 1;
+  const int lb = a.lb;
+  double2* T = smem;
+  double2* tw = smem + lb * R1 * RS;
+  const int64_t nf = gridDim.x / a.per_field;
+  const int64_t f = blockIdx.x % nf;
+  const int64_t r0 = (int64_t)(blockIdx.x / nf) * lb;
+  const double2* __restrict__ in = a.in[f];
+  double2* __restrict__ out = a.out[f];
+  const int kp = a.mask_k;
+  for (int t = threadIdx.x; t < n; t += 256) tw[t] = twg[t];
+  __syncthreads();
+  for (int e = threadIdx.x; e < lb * R2; e += 256) {
+    const int line = e / R2, n2 = e % R2;
+    const int64_t row = r0 + line;
+    const bool ok = row < a.rows && !(INV && a.row_m && a.row_m[row < a.rows ? row : 0] > a.mask_m);
+    const double2* x = in + row * n;
+    double2 v[R1];
+#pragma unroll
+    for (int c = 0; c < R1; ++c) {
+      const int kk = n2 + c * R2;
+      v[c] = make_double2(0.0, 0.0);
+      if (ok && (!INV || kk <= kp || kk >= n - kp)) v[c] = x[kk];
+    }
+    Dft<R1, INV>::run(v);
+    twiddle<R1, INV>(v, tw, n2);
+    double2* d = T + line * (R1 * RS) + n2;
+#pragma unroll
+    for (int c = 0; c < R1; ++c) d[c * RS] = v[c];
+  }
+  __syncthreads();
+  for (int e = threadIdx.x; e < lb * R1; e += 256) {
+    const int line = e / R1, k1 = e % R1;
+    const int64_t row = r0 + line;
+    if (row >= a.rows) continue;
+    const double2* d = T + line * (R1 * RS) + k1 * RS;
+    double2 v[R2];
+#pragma unroll
+    for (int c = 0; c < R2; ++c) v[c] = d[c];
+    Dft<R2, INV>::run(v);
+    const bool dead = !INV && a.row_m && a.row_m[row] > a.mask_m;
+    double2* y = out + row * n;
+#pragma unroll
+    for (int c = 0; c < R2; ++c) {
+      const int kk = k1 + c * R1;
+      if (INV) {
+        y[kk] = v[c];
+      } else if (!dead && (kk <= kp || kk >= n - kp)) {
+        y[kk] = cscale(v[c], 1.0 / n);
+      } else if (!a.kept_only) {
+        y[kk] = make_double2(0.0, 0.0);
+      }
+    }
+  }
+}
+
+// ---------------------------------------------------------------- azimuthal stages
+// Line q = i N_z + l; physical samples at (l N_r + i) N_phi + j; harmonic m at m * nlines + q.  A block
+// takes 2^lbs lines (or pairs of lines); in LDS entry (k, line) sits at k * row + line, so the lanes of
+// every access run over the lines first: 16-byte entries side by side, whatever the order k.
+struct PhiMix {
+  int n, R1, R2, lbs, nr, nz;
+  int min_, mout;       // orders read (the others enter as zero) and orders written
+  int64_t nlines;
+};
+
+__device__ __forceinline__ int64_t phys_off(const PhiMix& g, int64_t q) {
+  const int64_t i = q / g.nz, l = q - i * g.nz;
+  return (l * g.nr + i) * g.n;
+}
+
+// First pass (radix R of n = R S): lane (n2, line) reads x[n2 + S n1] from X and writes row k1, entry n2
+// of Y; second pass in second_pass: lane (k1, line) reads row k1 of length R2 and leaves X[k1 + R1 k2].
+template <int R, bool INV>
+__device__ __forceinline__ void mix_first(const double2* X, double2* Y, int S, int n2, int line, int row,
+                                          const double2* tw) {
+  double2 v[R];
+#pragma unroll
+  for (int c = 0; c < R; ++c) v[c] = X[(n2 + c * S) * row + line];
+  Dft<R, INV>::run(v);
+  twiddle_tab<R, INV>(v, tw, n2);
+#pragma unroll
+  for (int c = 0; c < R; ++c) Y[(c * S + n2) * row + line] = v[c];
+}
+
+struct Six {
+  double2* f[6];
+};
+
+// Vector stage: six harmonic fields -> nodal u, w -> N = (U + u) x w -> harmonics of N_r / r, N_phi / r,
+// N_z over fields 0, 1, 2 (see phi_vec256_kernel, of which this is the form for the other lengths).  A
+// block holds 2^lbs lines, R1 lanes per line; pairs of fields travel as one complex line.  The
+// inverse transforms end with their radix-R2 pass and leave X[k1 + R1 k2] in lane k1: the input of
+// the forward transforms' first pass taken with the radices in the other order, so the nodal values
+// stay in registers from the inverse to the forward transform.  The next pair's harmonics are
+// loaded into registers while the current pair is transformed.  R2 <= R1 keeps the three pairs' values
+// (12 R2 registers) small.
+// Bound by memory: 6 fields read and 3 written on the kept orders, in pieces of 16 2^lbs bytes: at 128^3
+// 101 MB in 35 us (2.9 TB/s) against 142 us with phi_vec_kernel, at 200 x 128 x 128 50 against 216 us.
+template <int R1, int R2, bool TAPS>
+__global__ __launch_bounds__(128) void phi_vec_mix_kernel(PhiMix g, const double2* __restrict__ twg, Six fs,
+                                                          const double* __restrict__ rinv, double Ux, double Uy,
+                                                          double Uz, double* __restrict__ taps) {
+  extern __shared__ double2 smem[];
+  constexpr int n = R1 * R2;
+  const int lb = 1 << g.lbs;
+  double2* Z = smem;                 // [n][lb]
+  double2* T = smem + (n << g.lbs);  // [n][lb]
+  double2* tw = T + (n << g.lbs);
+  const int tid = threadIdx.x, ll = tid & (lb - 1), k1 = tid >> g.lbs;  // blockDim = lb R1
+  const int64_t q0 = (int64_t)blockIdx.x << g.lbs, q = q0 + ll;
+  const bool valid = q < g.nlines;
+  constexpr int NP = (R2 + 1) / 2;  // orders below n / 2 per lane and field
+  double2 pa[NP], pb[NP];
+  auto load = [&](const double2* __restrict__ fa, const double2* __restrict__ fb) {
+#pragma unroll
+    for (int it = 0; it < NP; ++it) {
+      const int m = k1 + it * R1;
+      const bool ok = valid && m < g.min_;
+      const int64_t o = ok ? (int64_t)m * g.nlines + q : 0;
+      pa[it] = ok ? fa[o] : make_double2(0.0, 0.0);
+      pb[it] = ok ? fb[o] : make_double2(0.0, 0.0);
+    }
+  };
+  // the pair's Hermitian spectrum A + i B at the orders read; the other entries stay zero
+  auto store = [&]() {
+#pragma unroll
+    for (int it = 0; it < NP; ++it) {
+      const int m = k1 + it * R1;
+      if (m >= g.min_) continue;
+      const double2 a = pa[it], b = pb[it];
+      if (m == 0) {
+        Z[ll] = make_double2(a.x, b.x);
+      } else {
+        Z[(m << g.lbs) + ll] = make_double2(a.x - b.y, a.y + b.x);
+        Z[((n - m) << g.lbs) + ll] = make_double2(a.x + b.y, -a.y + b.x);
+      }
+    }
+  };
+  load(fs.f[0], fs.f[1]);
+  for (int e = tid; e < n; e += blockDim.x) tw[e] = twg[e];
+  for (int k = g.min_ + k1; k <= n - g.min_; k += R1) Z[(k << g.lbs) + ll] = make_double2(0.0, 0.0);
+  double2 x[3][R2];
+#pragma unroll
+  for (int pr = 0; pr < 3; ++pr) {
+    store();
+    if (pr < 2) load(fs.f[2 * pr + 2], fs.f[2 * pr + 3]);
+    __syncthreads();
+    if (k1 < R2) mix_first<R1, true>(Z, T, R2, k1, ll, lb, tw);
+    __syncthreads();
+#pragma unroll
+    for (int c = 0; c < R2; ++c) x[pr][c] = T[((k1 * R2 + c) << g.lbs) + ll];
+    Dft<R2, true>::run(x[pr]);
+  }
+  // nodal cross product at phi_j, j = k1 + R1 c: cos(phi_j) = tw[j].x, sin(phi_j) = -tw[j].y
+  const double ri = valid ? rinv[q / g.nz] : 0.0;
+  const int64_t pe = g.nlines * n;
+#pragma unroll
+  for (int c = 0; c < R2; ++c) {
+    const int j = k1 + c * R1;
+    const double2 t = tw[j];
+    const double cphi = t.x, sphi = -t.y;
+    const double ur = x[0][c].x, up = x[0][c].y, uz = x[1][c].x, wr = x[1][c].y, wp = x[2][c].x, wz = x[2][c].y;
+    const double Ur = ur + Ux * cphi + Uy * sphi;
+    const double Up = up - Ux * sphi + Uy * cphi;
+    const double Uzz = uz + Uz;
+    const double Nr = Up * wz - Uzz * wp;
+    const double Np = Uzz * wr - Ur * wz;
+    const double Nz = Ur * wp - Up * wr;
+    if (TAPS && valid) {
+      const int64_t o = phys_off(g, q) + j;
+      taps[0 * pe + o] = ur; taps[1 * pe + o] = up; taps[2 * pe + o] = uz;
+      taps[3 * pe + o] = wr; taps[4 * pe + o] = wp; taps[5 * pe + o] = wz;
+      taps[6 * pe + o] = Nr; taps[7 * pe + o] = Np; taps[8 * pe + o] = Nz;
+    }
+    x[0][c] = make_double2(Nr * ri, Np * ri);
+    x[1][c] = make_double2(Nz, 0.0);
+  }
+  // forward: radix R2, then radix R1 on rows c of length R1; N_r, N_phi through Z, N_z through T
+#pragma unroll
+  for (int f = 0; f < 2; ++f) {
+    Dft<R2, false>::run(x[f]);
+    twiddle_tab<R2, false>(x[f], tw, k1);
+  }
+#pragma unroll
+  for (int c = 0; c < R2; ++c) Z[((c * R1 + k1) << g.lbs) + ll] = x[0][c];
+  __syncthreads();  // every lane has read its last row of T
+#pragma unroll
+  for (int c = 0; c < R2; ++c) T[((c * R1 + k1) << g.lbs) + ll] = x[1][c];
+  __syncthreads();
+  // lanes 0 .. R2 - 1 take Z, the next R2 take T where the line has as many lanes, else a second round
+  constexpr bool split = 2 * R2 <= R1;
+#pragma unroll
+  for (int round = 0; round < (split ? 1 : 2); ++round) {
+    const int f = split ? k1 / R2 : round, k = split ? k1 - f * R2 : k1;
+    const bool act = f < 2 && k < R2;
+    double2* B = f ? T : Z;
+    double2 v[R1];
+    if (act) {
+#pragma unroll
+      for (int c = 0; c < R1; ++c) v[c] = B[((k * R1 + c) << g.lbs) + ll];
+      Dft<R1, false>::run(v);
+    }
+    __syncthreads();
+    if (act) {
+#pragma unroll
+      for (int c = 0; c < R1; ++c) B[((k + c * R2) << g.lbs) + ll] = v[c];
+    }
+  }
+  __syncthreads();
+  if (!valid) return;
+  const double h = 0.5 / n;
+  for (int m = k1; m < g.mout; m += R1) {
+    const int mc = m ? n - m : 0;
+    const double2 zm = Z[(m << g.lbs) + ll], zc = cconj(Z[(mc << g.lbs) + ll]);
+    const double2 cm = T[(m << g.lbs) + ll], cc = cconj(T[(mc << g.lbs) + ll]);
+    const double2 d = csub(zm, zc);
+    const int64_t o = (int64_t)m * g.nlines + q;
+    fs.f[0][o] = cscale(cadd(zm, zc), h);
+    fs.f[1][o] = make_double2(h * d.y, -h * d.x);
+    fs.f[2][o] = cscale(cadd(cm, cc), h);
+  }
+}
+
+mlg_status check(const char* what) {
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return fail(MLG_E_DEVICE, std::string(what) + ": " + hipGetErrorString(e));
+  return MLG_OK;
+}
+
+}  // namespace
+
+// n = R1 R2 of MIX_PAIRS (wide: or of MIX_WIDE); false if n is none of them
+bool mix_pair(int n, bool wide, int* R1, int* R2) {
+#define MIX_FIND(A, B) \
+  if (n == A * B) {    \
+    *R1 = A;           \
+    *R2 = B;           \
+    return true;       \
+  }
+  MIX_PAIRS(MIX_FIND)
+  if (wide) {
+    MIX_WIDE(MIX_FIND)
+  }
+#undef MIX_FIND
+  return false;
+}
+
+bool zmix_ok(const mlg_plan_s* p) {
+  int a, b;
+  return p->prec == MLG_FP64 && mix_pair(p->nz, true, &a, &b);
+}
+
+mlg_status launch_zmix(const mlg_plan_s* p, const double* const* in, double* const* out, int nf, int64_t rows, int dir,
+                       const int32_t* row_m, int mask_m, int mask_k, hipStream_t s, bool kept_only) {
+  if (nf < 1 || nf > 6) return fail(MLG_E_ARG, "z transform: 1 to 6 fields per launch");
+  ZMix a{};
+  int R1, R2;
+  if (!mix_pair(p->nz, true, &R1, &R2)) return fail(MLG_E_UNSUPPORTED, "z transform: length without a radix pair");
+  // the largest kept |k|: the chop, never the Nyquist slot, and the mask
+  int kp = std::min(p->nzc - 1, (p->nz - 1) / 2);
+  if (mask_k >= 0) kp = std::min(kp, mask_k);
+  a.mask_k = kp;
+  a.mask_m = mask_m;
+  a.row_m = row_m;
+  a.kept_only = kept_only;
+  a.rows = rows;
+  // about one line-lane per thread, and at most 64 KB of LDS
+  const int line = R1 * (R2 | 1);
+  a.lb = std::min(std::max(1, 256 / R1), (4096 - p->nz) / line);
+  a.per_field = (rows + a.lb - 1) / a.lb;
+  for (int i = 0; i < nf; ++i) {
+    a.in[i] = reinterpret_cast<const double2*>(in[i]);
+    a.out[i] = reinterpret_cast<double2*>(out[i]);
+  }
+  const size_t shm = ((size_t)a.lb * line + p->nz) * sizeof(double2);
+  const dim3 grid((unsigned)(a.per_field * nf));
+  const double2* tw = reinterpret_cast<const double2*>(p->d_tw_z);
+  p->timing.begin("z_fft", s);
+  switch (p->nz) {
+#define MIX_Z(A, B)                                                      \
+  case A * B:                                                            \
+    if (dir > 0) zmix_kernel<A, B, true><<<grid, 256, shm, s>>>(a, tw);  \
+    else zmix_kernel<A, B, false><<<grid, 256, shm, s>>>(a, tw);         \
+    break;
+    MIX_PAIRS(MIX_Z) MIX_WIDE(MIX_Z)
+#undef MIX_Z
+  }
+  p->timing.end(s);
+  return check("zmix_kernel");
+}
+
+namespace {
+
+PhiMix phi_mix(const mlg_plan_s* p, bool masked) {
+  PhiMix g{};
+  g.n = p->nphi;
+  g.nr = p->nr;
+  g.nz = p->nz;
+  g.nlines = (int64_t)p->nr * p->nz;
+  g.min_ = std::min(p->M, (p->nphi + 1) / 2);  // stored orders below the Nyquist order
+  if (masked) g.min_ = std::min(g.min_, p->dealias_m + 1);
+  g.mout = g.min_;
+  return g;
+}
+
+template <int R1, int R2>
+void vec_go(const PhiMix& g, const double2* tw, const Six& six, const double* node, const double* U, double* taps,
+            size_t shm, hipStream_t s) {
+  const unsigned blocks = (unsigned)((g.nlines + (1 << g.lbs) - 1) >> g.lbs);
+  const unsigned threads = (unsigned)(R1 << g.lbs);
+  if (taps)
+    phi_vec_mix_kernel<R1, R2, true><<<blocks, threads, shm, s>>>(g, tw, six, node, U[0], U[1], U[2], taps);
+  else
+    phi_vec_mix_kernel<R1, R2, false><<<blocks, threads, shm, s>>>(g, tw, six, node, U[0], U[1], U[2], taps);
+}
+
+}  // namespace
+
+bool phi_vec_mix_ok(const mlg_plan_s* p) {
+  int a, b;
+  return p->prec == MLG_FP64 && mix_pair(p->nphi, false, &a, &b);
+}
+
+mlg_status launch_phi_vec_mix(const mlg_plan_s* p, const double* U, double* const* f6, double* taps, hipStream_t s) {
+  PhiMix g = phi_mix(p, p->g.dealias != 0);
+  if (!mix_pair(p->nphi, false, &g.R1, &g.R2)) return fail(MLG_E_UNSUPPORTED, "phi stage: length without a radix pair");
+  g.lbs = 3;
+  while (g.lbs < 5 && (g.R1 << g.lbs) < 64) ++g.lbs;
+  const size_t shm = ((size_t)2 * (g.n << g.lbs) + g.n) * sizeof(double2);
+  Six six;
+  for (int i = 0; i < 6; ++i) six.f[i] = reinterpret_cast<double2*>(f6[i]);
+  const double2* tw = reinterpret_cast<const double2*>(p->d_tw_phi);
+  p->timing.begin("phi_fft", s);
+  switch (g.n) {
+#define MIX_VEC(A, B) \
+  case A * B: vec_go<A, B>(g, tw, six, p->d_node, U, taps, shm, s); break;
+    MIX_PAIRS(MIX_VEC)
+#undef MIX_VEC
+  }
+  p->timing.end(s);
+  return check("phi_vec_mix_kernel");
+}
+
+}  // namespace mlg

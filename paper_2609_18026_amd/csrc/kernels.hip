@@ -1234,6 +1234,7 @@ mlg_status launch_phi_vec_rhs(const mlg_plan_s* p, const double* U, double* cons
   // the 256-point kernel forms per-lane byte offsets of up to 31 lines of orders in 32 bits
   if (p->nphi == 256 && p->use_fast_fft && (int64_t)p->nr * p->nz <= (int64_t(1) << 23))
     return launch_phi256_vec(p, U, f6, taps, s);
+  if (phi_vec_mix_ok(p)) return launch_phi_vec_mix(p, U, f6, taps, s);
   if (p->prec != MLG_FP64) return fail(MLG_E_UNSUPPORTED, "reduced-precision plans need N_phi = 256");
   PhiGeom g = phi_geom(p, p->g.dealias != 0);
   int lb = 1024 / p->nphi;  // 4 buffers of n complex per line: 64 * lb * n bytes <= 64 KB
@@ -1259,6 +1260,7 @@ mlg_status launch_zfft_fields(const mlg_plan_s* p, const double* const* in, doub
     return launch_split_zdft(p, in, out, nf, rows, dir, row_m, mask_m, mask_k, s);
   if (p->nz == 256 && p->use_fast_fft)
     return launch_zfft256(p, in, out, nf, rows, dir, row_m, mask_m, mask_k, s, kept_only);
+  if (zmix_ok(p)) return launch_zmix(p, in, out, nf, rows, dir, row_m, mask_m, mask_k, s, kept_only);
   if (p->prec != MLG_FP64) return fail(MLG_E_UNSUPPORTED, "reduced-precision plans need N_z = 256");
   for (int i = 0; i < nf; ++i)
     if (mlg_status st = launch_zfft(p, in[i], out[i], rows, dir, row_m, mask_m, mask_k, s)) return st;
@@ -1270,6 +1272,7 @@ mlg_status launch_zfft(const mlg_plan_s* p, const double* in, double* out, int64
   if (rows <= 0) return MLG_OK;
   if (p->nz == 256 && p->prec == MLG_SPLIT_BF16) return launch_split_zdft(p, &in, &out, 1, rows, dir, row_m, mask_m, mask_k, s);
   if (p->nz == 256 && p->use_fast_fft) return launch_zfft256(p, &in, &out, 1, rows, dir, row_m, mask_m, mask_k, s);
+  if (zmix_ok(p)) return launch_zmix(p, &in, &out, 1, rows, dir, row_m, mask_m, mask_k, s, false);
   if (p->prec != MLG_FP64) return fail(MLG_E_UNSUPPORTED, "reduced-precision plans need N_z = 256");
   ZGeom g{};
   g.nz = p->nz;

@@ -272,6 +272,12 @@ mlg_status launch_far_field(const mlg_plan_s* p, double* spec, hipStream_t st);
 mlg_status launch_zfft256(const mlg_plan_s* p, const double* const* in, double* const* out, int nf, int64_t rows,
                           int dir, const int32_t* row_m, int mask_m, int mask_k, hipStream_t s,
                           bool kept_only = false);
+// fft_mix.hip: two-pass transforms of the lengths n = R1 R2 other than 256
+bool zmix_ok(const mlg_plan_s* p);
+mlg_status launch_zmix(const mlg_plan_s* p, const double* const* in, double* const* out, int nf, int64_t rows, int dir,
+                       const int32_t* row_m, int mask_m, int mask_k, hipStream_t s, bool kept_only);
+bool phi_vec_mix_ok(const mlg_plan_s* p);
+mlg_status launch_phi_vec_mix(const mlg_plan_s* p, const double* U, double* const* f6, double* taps, hipStream_t s);
 mlg_status launch_phi256_forward(const mlg_plan_s* p, const double* phys, double* mixed, hipStream_t s);
 mlg_status launch_phi256_backward(const mlg_plan_s* p, const double* mixed, double* phys, hipStream_t s);
 mlg_status launch_phi256_scalar(const mlg_plan_s* p, int kind, double gamma, double* mixed, hipStream_t s);
