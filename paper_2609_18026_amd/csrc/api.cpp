@@ -268,14 +268,13 @@ mlg_status mlg_rhs_scalar(mlg_plan p, int kind, double gamma, const void* spec_u
 
 }  // extern "C"
 
-// Whether mlg_rhs_tp skips the orders and axial blocks the two-thirds mask removes: the folded
-// FP64 / FP32 or the split synthesis followed by the 256-point z (or split z DFT) and phi stages
-// (the kernels that leave them unread, or discard what they read there); otherwise the synthesis
-// writes them as zeros.
+// Whether mlg_rhs_tp skips the orders and axial blocks the two-thirds mask removes: wherever the vector
+// phi stage reads the kept orders only (the 256-point and the two-pass stages; every z transform
+// reads the kept slots only).  Under phi_vec_kernel, which reads all stored orders, the synthesis
+// writes the masked ones as zeros.
 static bool rhs_skips_masked(const mlg_plan_s* p) {
-  const bool synth_ok = p->prec == MLG_SPLIT_BF16 || (p->use_fold && p->nr % 2 == 0);
-  return p->g.dealias != 0 && synth_ok && p->nz == 256 && p->nphi == 256 && p->use_fast_fft &&
-         (int64_t)p->nr * p->nz <= (int64_t(1) << 23);
+  const bool fast = p->nphi == 256 && p->use_fast_fft && (int64_t)p->nr * p->nz <= (int64_t(1) << 23);
+  return p->g.dealias != 0 && (fast || phi_vec_mix_ok(p));
 }
 
 // The kernel sequence of mlg_rhs_tp on the workspace 'ws' (caller-provided, or the per-GPU array of
@@ -300,8 +299,8 @@ static mlg_status rhs_tp_run(mlg_plan p, const double* U, const void* psi, const
   mlg_status st;
   // 1. radial synthesis: the six velocity / vorticity harmonics (k spectral), fused.  Under the
   // two-thirds mask the potentials enter through it (Sec. 3.3: the fields of a product hold no mode
-  // in the dealiasing margin); with the 256-point z and phi stages the masked orders and column
-  // blocks are not synthesized at all, and the stages after it do not read them
+  // in the dealiasing margin); the masked orders and column blocks are then not synthesized at all
+  // (rhs_skips_masked), and the stages after it do not read them
   const bool dealias = p->g.dealias != 0;
   SynthMask smask;
   if (dealias) {

@@ -303,7 +303,6 @@ mlg_status check(const char* what) {
 mlg_status launch_synth_gemm(const mlg_plan_s* p, const double* psi, const double* chi, double* const* out6,
                              hipStream_t s, const SynthMask& mask) {
   if (p->use_fold && p->nr % 2 == 0) return launch_synth_fold(p, psi, chi, out6, s, mask);
-  if (mask.skip) return fail(MLG_E_UNSUPPORTED, "synthesis: skipping masked blocks needs the folded products");
   SynthArgs a{};
   a.Pb = p->d_Pb;
   a.Tb = p->d_Tb;
@@ -319,7 +318,9 @@ mlg_status launch_synth_gemm(const mlg_plan_s* p, const double* psi, const doubl
   a.kap0 = 2.0 * M_PI / p->g.lz;
   a.mkeep = mask.mkeep;
   a.kmax = mask.kmax;
-  dim3 grid((unsigned)((p->nz + TC - 1) / TC), (unsigned)((p->nr + TM - 1) / TM), (unsigned)p->M);
+  // under 'skip' the kept orders only, all their columns (the tiles are 16 slots wide)
+  const int orders = mask.skip ? std::min(p->M, mask.mkeep + 1) : p->M;
+  dim3 grid((unsigned)((p->nz + TC - 1) / TC), (unsigned)((p->nr + TM - 1) / TM), (unsigned)orders);
   p->timing.begin("synth_gemm", s);
   synth_gemm_kernel<<<grid, 256, 0, s>>>(a);
   p->timing.end(s);
