@@ -483,6 +483,13 @@ mlg_status mlg_tp_advance(mlg_plan p, const double* U, void* psi, void* chi, voi
     if (mlg_status e = launch_proxy_force(p, ra, rb, s)) return e;   // dissipation of the proxy parts
     return closure ? closure_correct(closure, a, b, ra, rb, s) : MLG_OK;
   };
+  // one step of both potentials
+  auto step = [&](int mode, int which, const double* s0, const double* s1, const double* a0, const double* a1,
+                  const double* b0, const double* b1, double* o0, double* o1) -> mlg_status {
+    const double *sv[2] = {s0, s1}, *av[2] = {a0, a1}, *bv[2] = {b0, b1};
+    double* ov[2] = {o0, o1};
+    return launch_steps(p, 2, mode, which, sv, av, bv, ov, s);
+  };
   // the adaptive modal filter between steps (Sec. 3.3), when enabled
   auto filter = [&]() -> mlg_status {
     if (!p->filter_on) return MLG_OK;
@@ -493,14 +500,10 @@ mlg_status mlg_tp_advance(mlg_plan p, const double* U, void* psi, void* chi, voi
   if (start) {
     // s1 = 2 S_{dt/2}(S_{dt/2}(s0)) - S_dt(s0), S_h(s) = (I - h L)^{-1} (s + h A(s))
     if ((st = rhs(sp, sc, hp, hc))) return st;
-    if ((st = launch_step(p, 0, 1, sp, hp, nullptr, t[2], s)) || (st = launch_step(p, 0, 1, sc, hc, nullptr, t[3], s)))
-      return st;
-    if ((st = launch_step(p, 0, 0, sp, hp, nullptr, t[4], s)) || (st = launch_step(p, 0, 0, sc, hc, nullptr, t[5], s)))
-      return st;
+    if ((st = step(0, 1, sp, sc, hp, hc, nullptr, nullptr, t[2], t[3]))) return st;
+    if ((st = step(0, 0, sp, sc, hp, hc, nullptr, nullptr, t[4], t[5]))) return st;
     if ((st = rhs(t[4], t[5], t[0], t[1]))) return st;
-    if ((st = launch_step(p, 0, 0, t[4], t[0], nullptr, t[4], s)) ||
-        (st = launch_step(p, 0, 0, t[5], t[1], nullptr, t[5], s)))
-      return st;
+    if ((st = step(0, 0, t[4], t[5], t[0], t[1], nullptr, nullptr, t[4], t[5]))) return st;
     if ((st = launch_richardson(p, t[4], t[2], sp, s)) || (st = launch_richardson(p, t[5], t[3], sc, s))) return st;
     if ((st = filter())) return st;
     done = 1;
@@ -510,8 +513,7 @@ mlg_status mlg_tp_advance(mlg_plan p, const double* U, void* psi, void* chi, voi
   for (; done < nsteps; ++done) {
     double* now[2] = {prev[0] == hp ? t[0] : hp, prev[0] == hp ? t[1] : hc};
     if ((st = rhs(sp, sc, now[0], now[1]))) return st;
-    if ((st = launch_step(p, 1, 0, sp, now[0], prev[0], sp, s)) || (st = launch_step(p, 1, 0, sc, now[1], prev[1], sc, s)))
-      return st;
+    if ((st = step(1, 0, sp, sc, now[0], now[1], prev[0], prev[1], sp, sc))) return st;
     if ((st = filter())) return st;
     prev[0] = now[0];
     prev[1] = now[1];

@@ -45,13 +45,19 @@ constexpr int TK = 16;  // k depth per LDS stage
 
 __device__ __forceinline__ int kval(int kk, int nz) { return (2 * kk < nz) ? kk : kk - nz; }
 
-struct StepArgs {
+// one field of a step
+struct StepField {
   const double2* s;
   const double2* a1;
   const double2* a0;   // AB-CN: A^{j-1}; FE-BE: null
   double2* out;
   double2* W;          // packed like the spectra (rows n >= n0 of each m)
   double2* W0;         // m = 0 divided-difference products [j][kk]
+};
+
+struct StepArgs {
+  StepField f[2];      // one launch steps one or both potentials (nf fields)
+  int nf, nrow0;
   const double* fwd;
   const double* bwd;
   const double* lam;
@@ -60,7 +66,7 @@ struct StepArgs {
   const int64_t* loff;
   const int64_t* off;
   int M, nrc, nz, nzc, mode, q;   // mode 0 FE-BE, 1 AB-CN; q = p / 2 (1 without hyperviscosity)
-  int gx, gy, gz;                 // tiles: axial column blocks, row blocks, orders
+  int gx, gy, gz;                 // tiles: axial column blocks, row blocks (of each field), orders
   double h, nu, nuh, kap0;
 };
 
@@ -77,10 +83,16 @@ __device__ __forceinline__ double denom(const StepArgs& a, double mu) {
   return 1.0 + a.h * (a.nu * mu + a.nuh * pw);
 }
 
-// Z = V^{-1} [s | a] per m, then W = Phi Zs + Psi Za (and the m = 0 divided differences)
+// Z = V^{-1} [s | a] per m, then W = Phi Zs + Psi Za (and the m = 0 divided differences).  Both
+// potentials go in one launch, the tiles of an order on one XCD (they share its tables), and a
+// wavefront whose rows lie past the order's last leaves the products out.  Ten steps at 128 (96) x 64 x 32, where
+// one field has 128 blocks for the 256 CUs: 1.40 -> 1.14 ms, the n = 0 row taken along by the second launch.
 __global__ __launch_bounds__(256) void step_fwd_kernel(StepArgs a) {
   Tile3 tl;
-  if (!xcd_tile(a.gx, a.gy, a.gz, tl)) return;
+  if (!xcd_tile(a.gx, a.gy * a.nf, a.gz, tl)) return;
+  const bool second = tl.y >= a.gy;
+  const StepField fd = second ? a.f[1] : a.f[0];
+  if (second) tl.y -= a.gy;
   const int m = tl.z;
   if (m >= a.M || m >= a.nrc) return;
   const int n0 = m == 0 ? 1 : 0;
@@ -90,9 +102,9 @@ __global__ __launch_bounds__(256) void step_fwd_kernel(StepArgs a) {
   const int nz = a.nz;
   const double* __restrict__ A = a.fwd + a.qoff[m];
   const int64_t rb = (a.off[m] + n0) * nz;
-  const double2* __restrict__ s = a.s + rb;
-  const double2* __restrict__ p1 = a.a1 + rb;
-  const double2* __restrict__ p0 = a.a0 ? a.a0 + rb : nullptr;
+  const double2* __restrict__ s = fd.s + rb;
+  const double2* __restrict__ p1 = fd.a1 + rb;
+  const double2* __restrict__ p0 = fd.a0 ? fd.a0 + rb : nullptr;
   __shared__ double As[2][TK][TM];
   __shared__ double Bs[2][2][TK][2 * TC];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -139,6 +151,7 @@ __global__ __launch_bounds__(256) void step_fwd_kernel(StepArgs a) {
     Bs[buf][1][kr][TC + cc] = ok ? v.y : 0.0;
   };
   const int nk = (K + TK - 1) / TK;
+  const bool rows_in = j0 + wave * 16 < K;
   load(0);
   store(0, 0);
   __syncthreads();
@@ -147,6 +160,7 @@ __global__ __launch_bounds__(256) void step_fwd_kernel(StepArgs a) {
     if (kt + 1 < nk) load((kt + 1) * TK);
 #pragma unroll
     for (int ks = 0; ks < TK; ks += 4) {
+      if (!rows_in) break;
       const int kr = ks + (lane >> 4);
       const double av = As[buf][kr][wave * 16 + (lane & 15)];
       acc[0][0] = MFMA(av, Bs[buf][0][kr][lane & 15], acc[0][0]);
@@ -173,7 +187,7 @@ __global__ __launch_bounds__(256) void step_fwd_kernel(StepArgs a) {
     const double psi = a.h / D;
     const double phi = a.mode == 1 ? 2.0 / D - 1.0 : 1.0 / D;
     const double zsr = acc[0][0][v], zsi = acc[0][1][v], zar = acc[1][0][v], zai = acc[1][1][v];
-    a.W[rb + (int64_t)j * nz + kk] = make_double2(phi * zsr + psi * zar, phi * zsi + psi * zai);
+    fd.W[rb + (int64_t)j * nz + kk] = make_double2(phi * zsr + psi * zar, phi * zsi + psi * zai);
     if (m == 0) {
       // (f(mu) - f(alpha)) / lam in closed form: L(mu) - L(alpha) = lam * dl
       double sum = 0.0, mp = 1.0;
@@ -187,15 +201,70 @@ __global__ __launch_bounds__(256) void step_fwd_kernel(StepArgs a) {
       const double inv = a.h * dl / (D * Da);
       const double dphi = (a.mode == 1 ? 2.0 : 1.0) * inv;
       const double dpsi = a.h * inv;
-      a.W0[(int64_t)j * nz + kk] = make_double2(dphi * zsr + dpsi * zar, dphi * zsi + dpsi * zai);
+      fd.W0[(int64_t)j * nz + kk] = make_double2(dphi * zsr + dpsi * zar, dphi * zsi + dpsi * zai);
     }
   }
 }
 
-// out rows n >= n0 = V W per m; inactive axial slots are zeroed
+// m = 0, n = 0: out = Phi(alpha) s0 + Psi(alpha) a0 + sum_j u_j W0[j].  A block takes R0C axial
+// columns; the R0S lanes of a column sum every R0S-th j (their loads all in flight at once) and
+// the partial sums are added in LDS in a fixed order.
+constexpr int R0C = 16;  // columns per block
+constexpr int R0S = 16;  // partial sums per column
+
+__device__ __forceinline__ void step_row0(const StepArgs& a, const StepField& fd, int block, double2 (*part)[R0C]) {
+  const int c = threadIdx.x % R0C, sl = threadIdx.x / R0C;
+  const int kk = block * R0C + c;
+  const int K = a.nrc - 1;
+  double re = 0.0, im = 0.0;
+  if (kk < a.nz) {
+#pragma unroll 8
+    for (int j = sl; j < K; j += R0S) {
+      const double2 w = fd.W0[(int64_t)j * a.nz + kk];
+      re += a.u[j] * w.x;
+      im += a.u[j] * w.y;
+    }
+  }
+  part[sl][c] = make_double2(re, im);
+  __syncthreads();
+  if (sl != 0 || kk >= a.nz) return;
+  if (!active_slot(kk, a.nz, a.nzc)) {
+    fd.out[kk] = make_double2(0.0, 0.0);
+    return;
+  }
+  double sr = 0.0, si = 0.0;
+#pragma unroll
+  for (int q = 0; q < R0S; ++q) {
+    sr += part[q][c].x;
+    si += part[q][c].y;
+  }
+  const double kap = a.kap0 * kval(kk, a.nz);
+  const double alpha = kap * kap;
+  const double D = denom(a, alpha);
+  const double psi = a.h / D;
+  const double phi = a.mode == 1 ? 2.0 / D - 1.0 : 1.0 / D;
+  const double2 s0 = fd.s[kk];
+  double2 v = fd.a1[kk];
+  if (fd.a0) v = make_double2(3.0 * v.x - fd.a0[kk].x, 3.0 * v.y - fd.a0[kk].y);
+  fd.out[kk] = make_double2(phi * s0.x + psi * v.x + sr, phi * s0.y + psi * v.y + si);
+}
+
+// out rows n >= n0 = V W per m; inactive axial slots are zeroed.  The first nrow0 blocks (a multiple of
+// 8, so that the others keep their XCDs) take the n = 0 rows of the fields.
 __global__ __launch_bounds__(256) void step_bwd_kernel(StepArgs a) {
+  __shared__ double As[2][TK][TM];
+  __shared__ double Bs[2][TK][2 * TC];
+  if ((int)blockIdx.x < a.nrow0) {
+    static_assert(sizeof(double2) * R0S * R0C <= sizeof(As), "the partial sums fit in the table stage");
+    const int per = (a.nz + R0C - 1) / R0C, f = (int)blockIdx.x / per;
+    if (f < a.nf) step_row0(a, f ? a.f[1] : a.f[0], (int)blockIdx.x - f * per, reinterpret_cast<double2(*)[R0C]>(&As[0][0][0]));
+    return;
+  }
   Tile3 tl;
-  if (!xcd_tile(a.gx, a.gy, a.gz, tl)) return;
+  if (!xcd_tile(a.gx, a.gy * a.nf, a.gz, tl, blockIdx.x - a.nrow0)) return;
+  const bool second = tl.y >= a.gy;
+  const StepField fd = second ? a.f[1] : a.f[0];
+  if (second) tl.y -= a.gy;
   const int m = tl.z;
   if (m >= a.M || m >= a.nrc) return;
   const int n0 = m == 0 ? 1 : 0;
@@ -205,9 +274,7 @@ __global__ __launch_bounds__(256) void step_bwd_kernel(StepArgs a) {
   const int nz = a.nz;
   const double* __restrict__ A = a.bwd + a.qoff[m];
   const int64_t rb = (a.off[m] + n0) * nz;
-  const double2* __restrict__ Wm = a.W + rb;
-  __shared__ double As[2][TK][TM];
-  __shared__ double Bs[2][TK][2 * TC];
+  const double2* __restrict__ Wm = fd.W + rb;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   double4_t acc[2];
   acc[0] = acc[1] = double4_t{0.0, 0.0, 0.0, 0.0};
@@ -241,6 +308,7 @@ __global__ __launch_bounds__(256) void step_bwd_kernel(StepArgs a) {
     Bs[buf][kr][TC + cc] = ok ? rbv.y : 0.0;
   };
   const int nk = (K + TK - 1) / TK;
+  const bool rows_in = r0 + wave * 16 < K;
   load(0);
   store(0, 0);
   __syncthreads();
@@ -249,6 +317,7 @@ __global__ __launch_bounds__(256) void step_bwd_kernel(StepArgs a) {
     if (kt + 1 < nk) load((kt + 1) * TK);
 #pragma unroll
     for (int ks = 0; ks < TK; ks += 4) {
+      if (!rows_in) break;
       const int kr = ks + (lane >> 4);
       const double av = As[buf][kr][wave * 16 + (lane & 15)];
       acc[0] = MFMA(av, Bs[buf][kr][lane & 15], acc[0]);
@@ -264,54 +333,9 @@ __global__ __launch_bounds__(256) void step_bwd_kernel(StepArgs a) {
   for (int v = 0; v < 4; ++v) {
     const int r = r0 + wave * 16 + (lane >> 4) + 4 * v;
     if (r >= K) continue;
-    a.out[rb + (int64_t)r * nz + kk] = act ? make_double2(acc[0][v], acc[1][v]) : make_double2(0.0, 0.0);
+    fd.out[rb + (int64_t)r * nz + kk] = act ? make_double2(acc[0][v], acc[1][v]) : make_double2(0.0, 0.0);
   }
 }
-
-// m = 0, n = 0: out = Phi(alpha) s0 + Psi(alpha) a0 + sum_j u_j W0[j].  A block takes R0C axial
-// columns; the R0S lanes of a column sum every R0S-th j (their loads all in flight at once) and
-// the partial sums are added in LDS in a fixed order.
-constexpr int R0C = 16;  // columns per block
-constexpr int R0S = 16;  // partial sums per column
-
-__global__ __launch_bounds__(R0C * R0S) void step_row0_kernel(StepArgs a) {
-  __shared__ double2 part[R0S][R0C];
-  const int c = threadIdx.x % R0C, sl = threadIdx.x / R0C;
-  const int kk = blockIdx.x * R0C + c;
-  const int K = a.nrc - 1;
-  double re = 0.0, im = 0.0;
-  if (kk < a.nz) {
-#pragma unroll 8
-    for (int j = sl; j < K; j += R0S) {
-      const double2 w = a.W0[(int64_t)j * a.nz + kk];
-      re += a.u[j] * w.x;
-      im += a.u[j] * w.y;
-    }
-  }
-  part[sl][c] = make_double2(re, im);
-  __syncthreads();
-  if (sl != 0 || kk >= a.nz) return;
-  if (!active_slot(kk, a.nz, a.nzc)) {
-    a.out[kk] = make_double2(0.0, 0.0);
-    return;
-  }
-  double sr = 0.0, si = 0.0;
-#pragma unroll
-  for (int q = 0; q < R0S; ++q) {
-    sr += part[q][c].x;
-    si += part[q][c].y;
-  }
-  const double kap = a.kap0 * kval(kk, a.nz);
-  const double alpha = kap * kap;
-  const double D = denom(a, alpha);
-  const double psi = a.h / D;
-  const double phi = a.mode == 1 ? 2.0 / D - 1.0 : 1.0 / D;
-  const double2 s0 = a.s[kk];
-  double2 v = a.a1[kk];
-  if (a.a0) v = make_double2(3.0 * v.x - a.a0[kk].x, 3.0 * v.y - a.a0[kk].y);
-  a.out[kk] = make_double2(phi * s0.x + psi * v.x + sr, phi * s0.y + psi * v.y + si);
-}
-
 
 // ---------------------------------------------------------------- adaptive modal filter
 // Sec. 3.3: every coefficient whose normalised index zeta = max(n / N_r^c, m / N_phi^c,
@@ -504,7 +528,7 @@ mlg_status step_setup(mlg_plan_s* p, const mlg_dissip* d) {
   if ((st = upl(&p->d_step_fwd, fwd)) || (st = upl(&p->d_step_bwd, bwd)) || (st = upl(&p->d_step_lam, lam)) ||
       (st = upl(&p->d_step_u, u)) || (st = upl(&p->d_step_qoff, qoff)) || (st = upl(&p->d_step_loff, loff)))
     return st;
-  const size_t wel = ((size_t)p->tau + std::max(nrc - 1, 1)) * nz * 2;
+  const size_t wel = 2 * ((size_t)p->tau + std::max(nrc - 1, 1)) * nz * 2;  // two fields
   hipError_t e = hipMalloc(reinterpret_cast<void**>(&p->d_step_w), wel * sizeof(double));
   if (e != hipSuccess) {
     p->d_step_w = nullptr;
@@ -527,13 +551,23 @@ mlg_status step_setup(mlg_plan_s* p, const mlg_dissip* d) {
 
 mlg_status launch_step(const mlg_plan_s* p, int mode, int which, const double* s, const double* a1, const double* a0,
                        double* out, hipStream_t st) {
+  return launch_steps(p, 1, mode, which, &s, &a1, &a0, &out, st);
+}
+
+mlg_status launch_steps(const mlg_plan_s* p, int nf, int mode, int which, const double* const* s,
+                        const double* const* a1, const double* const* a0, double* const* out, hipStream_t st) {
   StepArgs a{};
-  a.s = reinterpret_cast<const double2*>(s);
-  a.a1 = reinterpret_cast<const double2*>(a1);
-  a.a0 = mode == 1 ? reinterpret_cast<const double2*>(a0) : nullptr;
-  a.out = reinterpret_cast<double2*>(out);
-  a.W = reinterpret_cast<double2*>(p->d_step_w);
-  a.W0 = a.W + (size_t)p->tau * p->nz;
+  const size_t w_len = (size_t)p->tau * p->nz, w0_len = (size_t)std::max(p->nrc - 1, 1) * p->nz;
+  a.nf = nf;
+  for (int i = 0; i < nf; ++i) {
+    StepField& f = a.f[i];
+    f.s = reinterpret_cast<const double2*>(s[i]);
+    f.a1 = reinterpret_cast<const double2*>(a1[i]);
+    f.a0 = mode == 1 ? reinterpret_cast<const double2*>(a0[i]) : nullptr;
+    f.out = reinterpret_cast<double2*>(out[i]);
+    f.W = reinterpret_cast<double2*>(p->d_step_w) + i * (w_len + w0_len);
+    f.W0 = f.W + w_len;
+  }
   a.fwd = p->d_step_fwd;
   a.bwd = p->d_step_bwd;
   a.lam = p->d_step_lam;
@@ -551,17 +585,14 @@ mlg_status launch_step(const mlg_plan_s* p, int mode, int which, const double* s
   a.nu = p->step_nu;
   a.nuh = p->step_nuh;
   a.kap0 = 2.0 * M_PI / p->g.lz;
-  const int mz = std::min(p->M, p->nrc);
   p->timing.begin("step", st);
-  if (p->step_maxk > 0) {
-    a.gx = (p->nz + TC - 1) / TC;
-    a.gy = (p->step_maxk + TM - 1) / TM;
-    a.gz = mz;
-    const dim3 grid(xcd_blocks(a.gx, a.gy, a.gz));
-    step_fwd_kernel<<<grid, 256, 0, st>>>(a);
-    step_bwd_kernel<<<grid, 256, 0, st>>>(a);
-  }
-  step_row0_kernel<<<(unsigned)((p->nz + R0C - 1) / R0C), R0C * R0S, 0, st>>>(a);
+  a.gx = (p->nz + TC - 1) / TC;
+  a.gy = std::max(1, (p->step_maxk + TM - 1) / TM);
+  a.gz = std::min(p->M, p->nrc);
+  a.nrow0 = (nf * ((p->nz + R0C - 1) / R0C) + 7) / 8 * 8;
+  const unsigned tiles = p->step_maxk > 0 ? xcd_blocks(a.gx, a.gy * nf, a.gz) : 0;  // none: the n = 0 row alone
+  if (tiles) step_fwd_kernel<<<tiles, 256, 0, st>>>(a);
+  step_bwd_kernel<<<a.nrow0 + tiles, 256, 0, st>>>(a);
   p->timing.end(st);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return fail(MLG_E_DEVICE, std::string("step kernels: ") + hipGetErrorString(e));
