@@ -217,6 +217,23 @@ static mlg_status scalar_radial(const mlg_plan_s* p, int dir, const double* B, d
                  : launch_gemm(p, pr, p->d_desc_fwd, p->max_rows_fwd, 2 * p->nz, s);
 }
 
+// Spectrum -> harmonics at the nodes in w.X[0] (physical in z), and back.  'mask': under the two-thirds
+// mask, the slots outside it read and written as zero.  On 2D plans (N_z = 1) the axial transform is
+// the identity and the radial product reads and writes the spectrum itself.
+static mlg_status to_harmonics(const mlg_plan_s* p, const double* spec, const Ws& w, bool mask, hipStream_t s) {
+  const int32_t* row_m = mask ? p->d_row_m : nullptr;
+  if (gemv_ok(p)) return launch_gemv(p, +1, spec, w.X[0], mask ? p->dealias_m + 1 : p->M, s);
+  if (mlg_status st = launch_zfft(p, spec, w.T[0], p->tau, +1, row_m, p->dealias_m, mask ? p->dealias_k : -1, s)) return st;
+  return scalar_radial(p, +1, w.T[0], w.X[0], s);
+}
+
+static mlg_status from_harmonics(const mlg_plan_s* p, const Ws& w, double* spec, bool mask, hipStream_t s) {
+  const int32_t* row_m = mask ? p->d_row_m : nullptr;
+  if (gemv_ok(p)) return launch_gemv(p, -1, w.X[0], spec, mask ? p->dealias_m + 1 : p->M, s);
+  if (mlg_status st = scalar_radial(p, -1, w.X[0], spec, s)) return st;
+  return launch_zfft(p, spec, spec, p->tau, -1, row_m, p->dealias_m, mask ? p->dealias_k : -1, s);
+}
+
 mlg_status mlg_forward(mlg_plan p, const void* phys, void* spec, void* ws, void* stream) {
   if (mlg_status st = check_plan(p)) return st;
   if (!phys || !spec || !ws) return fail(MLG_E_ARG, "null buffer");
@@ -225,8 +242,7 @@ mlg_status mlg_forward(mlg_plan p, const void* phys, void* spec, void* ws, void*
   Ws w = partition(p, ws);
   mlg_status st;
   if ((st = launch_phi_forward(p, static_cast<const double*>(phys), w.X[0], s))) return st;
-  if ((st = scalar_radial(p, -1, w.X[0], static_cast<double*>(spec), s))) return st;
-  return launch_zfft(p, static_cast<double*>(spec), static_cast<double*>(spec), p->tau, -1, nullptr, 0, -1, s);
+  return from_harmonics(p, w, static_cast<double*>(spec), false, s);
 }
 
 mlg_status mlg_backward(mlg_plan p, const void* spec, void* phys, void* ws, void* stream) {
@@ -236,8 +252,7 @@ mlg_status mlg_backward(mlg_plan p, const void* spec, void* phys, void* ws, void
   hipStream_t s = static_cast<hipStream_t>(stream);
   Ws w = partition(p, ws);
   mlg_status st;
-  if ((st = launch_zfft(p, static_cast<const double*>(spec), w.T[0], p->tau, +1, nullptr, 0, -1, s))) return st;
-  if ((st = scalar_radial(p, +1, w.T[0], w.X[0], s))) return st;
+  if ((st = to_harmonics(p, static_cast<const double*>(spec), w, false, s))) return st;
   return launch_phi_backward(p, w.X[0], static_cast<double*>(phys), s);
 }
 
@@ -255,15 +270,9 @@ mlg_status mlg_rhs_scalar(mlg_plan p, int kind, double gamma, const void* spec_u
   // the two-thirds mask applies to the field entering the product (read as zero outside it by the
   // inverse z transform) and to the product
   const bool mask = p->g.dealias != 0;
-  const int32_t* row_m = mask ? p->d_row_m : nullptr;
-  const int mask_k = mask ? p->dealias_k : -1;
-  if ((st = launch_zfft(p, static_cast<const double*>(spec_u), w.T[0], p->tau, +1, row_m, p->dealias_m, mask_k, s)))
-    return st;
-  if ((st = scalar_radial(p, +1, w.T[0], w.X[0], s))) return st;
+  if ((st = to_harmonics(p, static_cast<const double*>(spec_u), w, mask, s))) return st;
   if ((st = launch_phi_scalar_rhs(p, kind, gamma, w.X[0], s))) return st;
-  if ((st = scalar_radial(p, -1, w.X[0], static_cast<double*>(spec_out), s))) return st;
-  return launch_zfft(p, static_cast<double*>(spec_out), static_cast<double*>(spec_out), p->tau, -1, row_m,
-                     p->dealias_m, mask_k, s);
+  return from_harmonics(p, w, static_cast<double*>(spec_out), mask, s);
 }
 
 }  // extern "C"

@@ -46,6 +46,46 @@ __host__ __device__ inline unsigned xcd_blocks(int gx, int gy, int gz) {
   return 8u * (unsigned)gx * (unsigned)gy * (unsigned)((gz + 7) / 8);
 }
 
+// Matrix-vector products of 2D plans (gemv.hip, step.hip).  A block takes GR rows of an order and the whole
+// contraction: lane q of 8 owns two adjacent rows (one 16-byte table load a term), the GK groups of 8
+// lanes every GK-th term.  The contraction goes in chunks of GK GU terms: the loads of the chunk's vector
+// entries and then the GU table loads of every lane all go out together, with clamped indices and no branch,
+// and the block shares the vector through LDS (zero past the end).  GU covers the whole contraction
+// up to 1024 terms.  With the vector read from memory by every lane, its
+// returned bytes, not the table's, bound the kernels (the first step product 11.6 us at N_r = 768).
+constexpr int GR = 16;
+constexpr int GK = 64;
+constexpr int GT = GR / 2 * GK;  // threads
+inline int gemv_unroll(int terms) { return terms <= 2 * GK ? 2 : (terms <= 4 * GK ? 4 : (terms <= 8 * GK ? 8 : 16)); }
+typedef double dpair __attribute__((ext_vector_type(2), aligned(8)));  // two adjacent table entries
+
+// acc[0 .. NA) summed over the GK groups; the totals of the lanes' rows end in threads 0 .. GR / 2 - 1
+template <int NA>
+__device__ __forceinline__ void block_sum(double (&acc)[NA]) {
+  constexpr int GL = GR / 2;
+  __shared__ double part[GT / 64][GL][NA];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, q = threadIdx.x % GL;
+#pragma unroll
+  for (int i = 0; i < NA; ++i) {
+    acc[i] += __shfl_xor(acc[i], 8, 64);
+    acc[i] += __shfl_xor(acc[i], 16, 64);
+    acc[i] += __shfl_xor(acc[i], 32, 64);
+  }
+  if (lane < GL) {
+#pragma unroll
+    for (int i = 0; i < NA; ++i) part[wave][q][i] = acc[i];
+  }
+  __syncthreads();
+  if (threadIdx.x >= GL) return;
+#pragma unroll
+  for (int i = 0; i < NA; ++i) {
+    double s = part[0][q][i];
+#pragma unroll
+    for (int w = 1; w < GT / 64; ++w) s += part[w][q][i];
+    acc[i] = s;
+  }
+}
+
 // Storage conversions: reduced-precision plans keep fields as float / float2 in memory while the
 // kernels compute in double.
 __device__ __forceinline__ double2 ld2(const double2* p) { return *p; }

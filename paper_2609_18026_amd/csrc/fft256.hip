@@ -359,14 +359,14 @@ __global__ __launch_bounds__(VB) void phi_vec256_kernel(Phi256 g, const double2*
 // vector stage; the block barrier of the gather publishes them.
 constexpr int PL2 = 2 * PL;  // real lines per block of the scalar stages
 
-// Z[pr] = the pair spectrum of lines q0 + 2 pr and q0 + 2 pr + 1 (orders m < min(M, 128); the
-// Nyquist position cleared).  Ends with a block barrier.
+// Z[pr] = the pair spectrum of lines q0 + 2 pr and q0 + 2 pr + 1 (orders m < min(M, 128, mkeep + 1);
+// the Nyquist position cleared).  Ends with a block barrier.
 template <typename S2>
 __device__ __forceinline__ void gather_pairs16(double2 (*Z)[WROW], const Phi256& g, const S2* __restrict__ mixed,
                                                int64_t q0) {
   const int t = threadIdx.x;
   if (t < PL) Z[t][zpos(128)] = make_double2(0.0, 0.0);
-  const int mmax = g.M < 128 ? g.M : 128;
+  const int mmax = min(min(g.M, 128), g.mkeep + 1);
 #pragma unroll
   for (int it = 0; it < PL * 128 / VB; ++it) {
     const int e = t + VB * it;

@@ -226,7 +226,7 @@ __device__ double2* fft_lds(double2* x, double2* y, const FftRadices& fr, const 
 // A "line" q = i * N_z + l is the azimuthal line at (r_i, z_l).  Physical data of line q
 // starts at (l * N_r + i) * N_phi; its harmonic m lives in a mixed array at m * N_r N_z + q.
 struct PhiGeom {
-  int nr, nz, nphi, M, mkeep;  // modes m < M stored, m <= mkeep written non-zero
+  int nr, nz, nphi, M, mkeep;  // modes m < M stored, m <= mkeep read and written non-zero
   int64_t nlines;              // N_r * N_z
 };
 
@@ -335,7 +335,7 @@ __global__ __launch_bounds__(256) void phi_scalar_kernel(PhiGeom g, FftRadices f
   __syncthreads();
   for (int e = threadIdx.x; e < npair * half; e += blockDim.x) {
     const int p = e / half, m = e - (e / half) * half;
-    if (m >= g.M) continue;
+    if (m >= g.M || m > g.mkeep) continue;
     const int64_t qa = q0 + 2 * p, qb = qa + 1;
     double2 a = (qa < g.nlines) ? mixed[(int64_t)m * g.nlines + qa] : make_double2(0.0, 0.0);
     double2 b = (qb < g.nlines && 2 * p + 1 < lb) ? mixed[(int64_t)m * g.nlines + qb] : make_double2(0.0, 0.0);

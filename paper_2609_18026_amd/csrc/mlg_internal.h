@@ -201,6 +201,10 @@ mlg_status launch_synth_fold(const mlg_plan_s* p, const double* psi, const doubl
 mlg_status launch_scalar_fold(const mlg_plan_s* p, int dir, const double* B, double* C, hipStream_t s);
 mlg_status launch_proj_fold(const mlg_plan_s* p, double* const* in3, double* const* out3, int mmax, int kmax,
                             hipStream_t s);
+// gemv.hip: radial products of one scalar field on 2D plans, spectrum <-> harmonics of the first 'orders'
+// orders (dir < 0 writes the others as zero)
+bool gemv_ok(const mlg_plan_s* p);
+mlg_status launch_gemv(const mlg_plan_s* p, int dir, const double* x, double* y, int orders, hipStream_t s);
 // gemm_split.hip: the same two products with split-bfloat16 operands and FP32 accumulation
 mlg_status launch_split_synth(const mlg_plan_s* p, const double* psi, const double* chi, double* const* out6,
                               hipStream_t s, const SynthMask& mask);

@@ -337,6 +337,158 @@ __global__ __launch_bounds__(256) void step_bwd_kernel(StepArgs a) {
   }
 }
 
+// N_z = 1: one column per field, as matrix-vector products (dev_common.h; the tiles above would hold one
+// column of 16, and their K stages run one after the other).  N_r = 768, 2 orders, one field: the first
+// product 56 -> 8.0 us, the second 36 -> 5.8 us (with the n = 0 row, 6 us before).
+template <int GU>
+__global__ __launch_bounds__(GT) void step_fwd1_kernel(StepArgs a) {
+  constexpr int GC = GK * GU, GV = (GC + GT - 1) / GT;  // terms a chunk, vector entries a thread
+  __shared__ double2 xs[GC], xa[GC];
+  const int m = blockIdx.y;
+  const StepField fd = blockIdx.z ? a.f[1] : a.f[0];
+  const int n0 = m == 0 ? 1 : 0;
+  const int K = a.nrc - m - n0;
+  const int j0 = blockIdx.x * GR;
+  if (j0 >= K) return;
+  const int q = threadIdx.x % (GR / 2), g = threadIdx.x / (GR / 2);
+  const int jl = j0 + 2 * q;
+  // the pair (K - 1, K) reads on into the next table row (the tables end in a spare entry)
+  const double* __restrict__ A = a.fwd + a.qoff[m] + min(jl, K - 1);
+  const int64_t rb = a.off[m] + n0;
+  const double2* __restrict__ s = fd.s + rb;
+  const double2* __restrict__ p1 = fd.a1 + rb;
+  const double2* __restrict__ p0 = (fd.a0 ? fd.a0 : fd.a1) + rb;
+  const double c1 = fd.a0 ? 3.0 : 1.0, c0 = fd.a0 ? 1.0 : 0.0;
+  double z[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};  // V^{-1} s and V^{-1} a of row jl, of row jl + 1
+  for (int k0 = 0; k0 < K; k0 += GC) {
+    double2 sv[GV], x1[GV], x0[GV];
+#pragma unroll
+    for (int t = 0; t < GV; ++t) {
+      const int k = k0 + t * GT + threadIdx.x;
+      sv[t] = k < K ? s[k] : make_double2(0.0, 0.0);
+      x1[t] = k < K ? p1[k] : make_double2(0.0, 0.0);
+      x0[t] = k < K ? p0[k] : make_double2(0.0, 0.0);
+    }
+    dpair v[GU];
+#pragma unroll
+    for (int u = 0; u < GU; ++u) {
+      v[u] = *reinterpret_cast<const dpair*>(A + (int64_t)min(k0 + g + GK * u, K - 1) * K);
+    }
+    if (k0 > 0) __syncthreads();
+#pragma unroll
+    for (int t = 0; t < GV; ++t) {
+      if (GC < GT && (int)threadIdx.x >= GC) break;
+      xs[t * GT + threadIdx.x] = sv[t];
+      xa[t * GT + threadIdx.x] = make_double2(c1 * x1[t].x - c0 * x0[t].x, c1 * x1[t].y - c0 * x0[t].y);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < GU; ++u) {
+      const double2 sv = xs[g + GK * u], av = xa[g + GK * u];
+      z[0] += v[u].x * sv.x;
+      z[1] += v[u].x * sv.y;
+      z[2] += v[u].x * av.x;
+      z[3] += v[u].x * av.y;
+      z[4] += v[u].y * sv.x;
+      z[5] += v[u].y * sv.y;
+      z[6] += v[u].y * av.x;
+      z[7] += v[u].y * av.y;
+    }
+  }
+  block_sum(z);
+  if (threadIdx.x >= GR / 2) return;
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int j = jl + h;
+    if (j >= K) continue;
+    const double zsr = z[4 * h], zsi = z[4 * h + 1], zar = z[4 * h + 2], zai = z[4 * h + 3];
+    const double lj = a.lam[a.loff[m] + j];  // the only slot is k = 0: kappa = 0
+    const double D = denom(a, lj);
+    const double psi = a.h / D;
+    const double phi = a.mode == 1 ? 2.0 / D - 1.0 : 1.0 / D;
+    fd.W[rb + j] = make_double2(phi * zsr + psi * zar, phi * zsi + psi * zai);
+    if (m == 0) {
+      // the divided differences of step_fwd_kernel at alpha = 0
+      double mp = 1.0;
+      for (int i = 1; i < a.q; ++i) mp *= lj;
+      const double inv = a.h * (-a.nu - a.nuh * mp) / D;
+      const double dphi = (a.mode == 1 ? 2.0 : 1.0) * inv, dpsi = a.h * inv;
+      fd.W0[j] = make_double2(dphi * zsr + dpsi * zar, dphi * zsi + dpsi * zai);
+    }
+  }
+}
+
+// rows n >= n0 of every order; the block past the last row block of order 0 takes its n = 0 row
+template <int GU>
+__global__ __launch_bounds__(GT) void step_bwd1_kernel(StepArgs a) {
+  constexpr int GC = GK * GU, GV = (GC + GT - 1) / GT;  // terms a chunk, vector entries a thread
+  __shared__ double2 xs[GC];
+  const int m = blockIdx.y;
+  const StepField fd = blockIdx.z ? a.f[1] : a.f[0];
+  const int n0 = m == 0 ? 1 : 0;
+  const int K = a.nrc - m - n0;
+  if (m == 0 && blockIdx.x == gridDim.x - 1) {
+    const int t = threadIdx.x;
+    double z[2] = {0.0, 0.0};
+    for (int j = t; j < K; j += GT) {
+      const double2 w = fd.W0[j];
+      z[0] += a.u[j] * w.x;
+      z[1] += a.u[j] * w.y;
+    }
+#pragma unroll
+    for (int d = 1; d < GR / 2; d *= 2) {  // the lanes of a group, then (block_sum) the groups
+      z[0] += __shfl_xor(z[0], d, 64);
+      z[1] += __shfl_xor(z[1], d, 64);
+    }
+    block_sum(z);
+    if (t != 0) return;
+    // alpha = 0: D = 1
+    const double2 s0 = fd.s[0];
+    double2 v = fd.a1[0];
+    if (fd.a0) v = make_double2(3.0 * v.x - fd.a0[0].x, 3.0 * v.y - fd.a0[0].y);
+    fd.out[0] = make_double2(s0.x + a.h * v.x + z[0], s0.y + a.h * v.y + z[1]);
+    return;
+  }
+  const int r0 = blockIdx.x * GR;
+  if (r0 >= K) return;
+  const int q = threadIdx.x % (GR / 2), g = threadIdx.x / (GR / 2);
+  const int row = r0 + 2 * q;
+  const double* __restrict__ A = a.bwd + a.qoff[m] + min(row, K - 1);
+  const int64_t rb = a.off[m] + n0;
+  const double2* __restrict__ W = fd.W + rb;
+  double z[4] = {0.0, 0.0, 0.0, 0.0};
+  for (int k0 = 0; k0 < K; k0 += GC) {
+    double2 wv[GV];
+#pragma unroll
+    for (int t = 0; t < GV; ++t) {
+      const int k = k0 + t * GT + threadIdx.x;
+      wv[t] = k < K ? W[k] : make_double2(0.0, 0.0);
+    }
+    dpair v[GU];
+#pragma unroll
+    for (int u = 0; u < GU; ++u) {
+      v[u] = *reinterpret_cast<const dpair*>(A + (int64_t)min(k0 + g + GK * u, K - 1) * K);
+    }
+    if (k0 > 0) __syncthreads();
+#pragma unroll
+    for (int t = 0; t < GV; ++t)
+      if (GC >= GT || (int)threadIdx.x < GC) xs[t * GT + threadIdx.x] = wv[t];
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < GU; ++u) {
+      const double2 w = xs[g + GK * u];
+      z[0] += v[u].x * w.x;
+      z[1] += v[u].x * w.y;
+      z[2] += v[u].y * w.x;
+      z[3] += v[u].y * w.y;
+    }
+  }
+  block_sum(z);
+  if (threadIdx.x >= GR / 2) return;
+  if (row < K) fd.out[rb + row] = make_double2(z[0], z[1]);
+  if (row + 1 < K) fd.out[rb + row + 1] = make_double2(z[2], z[3]);
+}
+
 // ---------------------------------------------------------------- adaptive modal filter
 // Sec. 3.3: every coefficient whose normalised index zeta = max(n / N_r^c, m / N_phi^c,
 // |k| / N_z^c) exceeds zeta_c is multiplied by exp(-eps ((zeta - zeta_c) / (1 - zeta_c))^8); eps
@@ -444,7 +596,7 @@ mlg_status step_setup(mlg_plan_s* p, const mlg_dissip* d) {
     qoff[m + 1] = qoff[m] + (int64_t)Kp * Kp;
     loff[m + 1] = loff[m] + Kp;
   }
-  std::vector<double> fwd(std::max<int64_t>(qoff[M], 1)), bwd(std::max<int64_t>(qoff[M], 1));
+  std::vector<double> fwd(qoff[M] + 1), bwd(qoff[M] + 1);  // with a spare entry: see step_fwd1_kernel
   std::vector<double> lam(std::max<int64_t>(loff[M], 1)), u(std::max(nrc - 1, 1), 0.0);
   std::atomic<int> next{0};
   std::atomic<bool> failed{false};
@@ -586,6 +738,25 @@ mlg_status launch_steps(const mlg_plan_s* p, int nf, int mode, int which, const 
   a.nuh = p->step_nuh;
   a.kap0 = 2.0 * M_PI / p->g.lz;
   p->timing.begin("step", st);
+  if (p->nz == 1) {
+    const unsigned tiles = (unsigned)((p->step_maxk + GR - 1) / GR), orders = (unsigned)std::min(p->M, p->nrc);
+    const dim3 gf(tiles, orders, (unsigned)nf), gb(tiles + 1, orders, (unsigned)nf);
+    switch (gemv_unroll(p->step_maxk)) {
+#define STEP1(U)                                                   \
+  if (tiles) step_fwd1_kernel<U><<<gf, GT, 0, st>>>(a);            \
+  step_bwd1_kernel<U><<<gb, GT, 0, st>>>(a);                       \
+  break;
+      case 2: STEP1(2)
+      case 4: STEP1(4)
+      case 8: STEP1(8)
+      default: STEP1(16)
+#undef STEP1
+    }
+    p->timing.end(st);
+    const hipError_t e1 = hipGetLastError();
+    if (e1 != hipSuccess) return fail(MLG_E_DEVICE, std::string("step kernels: ") + hipGetErrorString(e1));
+    return MLG_OK;
+  }
   a.gx = (p->nz + TC - 1) / TC;
   a.gy = std::max(1, (p->step_maxk + TM - 1) / TM);
   a.gz = std::min(p->M, p->nrc);
