@@ -1044,14 +1044,19 @@ __global__ __launch_bounds__(256) void energy_sum_kernel(const double* __restric
 // ---------------------------------------------------------------- pointwise evaluation of one harmonic
 // f(r_j) = sum_{n=m}^{N_r^c-1} s[n][kk] Pbar_n^m(x(r_j)) (Eq. expansion for one (m, k) column), with
 // x = (r^2 - ell^2) / (r^2 + ell^2) and sqrt(1 - x^2) = 2 ell r / (r^2 + ell^2) (Eq. map), Pbar by
-// the normalised recurrence of the plan tables in FP64: one thread per radius, coefficients read
-// in order by every thread.
-__global__ __launch_bounds__(256) void eval_harmonic_kernel(const double2* __restrict__ col, int64_t stride, int m,
-                                                            int nrc, double ell, const double* __restrict__ r,
-                                                            int64_t npts, double2* __restrict__ out) {
-  const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= npts) return;
-  const double rr = r[j], d = rr * rr + ell * ell;
+// the normalised recurrence of the plan tables in FP64: one thread per radius.  The recurrence and the series
+// coefficients do not depend on the radius: a block (one wavefront) forms them EV_N degrees at a time, a
+// root and a division each, and the chain of a radius is left with one fused multiply-add per degree.
+// 768 degrees at 560 radii: 212 -> 21 us against every thread forming them at every degree.
+constexpr int EV_T = 64, EV_N = 256;
+
+__global__ __launch_bounds__(EV_T) void eval_harmonic_kernel(const double2* __restrict__ col, int64_t stride, int m,
+                                                             int nrc, double ell, const double* __restrict__ r,
+                                                             int64_t npts, double2* __restrict__ out) {
+  __shared__ double ca[EV_N], cb[EV_N];
+  __shared__ double2 cc[EV_N];
+  const int64_t j = (int64_t)blockIdx.x * EV_T + threadIdx.x;
+  const double rr = r[j < npts ? j : npts - 1], d = rr * rr + ell * ell;
   const double x = (rr * rr - ell * ell) / d, sn = 2.0 * ell * rr / d;
   double p0 = sqrt(0.5);
   for (int i = 1; i <= m; ++i) p0 *= sqrt((double)(2 * i + 1) / (double)(2 * i)) * sn;
@@ -1066,17 +1071,29 @@ __global__ __launch_bounds__(256) void eval_harmonic_kernel(const double2* __res
     acc.x += c.x * p1;
     acc.y += c.y * p1;
   }
-  for (int n = m + 2; n < nrc; ++n) {
-    const double a = sqrt((double)(4 * n * n - 1) / (double)(n * n - m * m));
-    const double b = sqrt((double)((2 * n + 1) * (n - 1 - m) * (n - 1 + m)) / (double)((2 * n - 3) * (n * n - m * m)));
-    const double p2 = a * x * p1 - b * p0;
-    const double2 c = col[(int64_t)(n - m) * stride];
-    acc.x += c.x * p2;
-    acc.y += c.y * p2;
-    p0 = p1;
-    p1 = p2;
+  for (int n0 = m + 2; n0 < nrc; n0 += EV_N) {
+    const int cnt = min(EV_N, nrc - n0);
+    __syncthreads();
+    for (int t = threadIdx.x; t < cnt; t += EV_T) {
+      const int n = n0 + t;
+      // whole numbers in double: exact below 2^53 (as int they would overflow from n = 1025)
+      const double nn = n, mm = m, den = nn * nn - mm * mm;
+      ca[t] = sqrt((4.0 * nn * nn - 1.0) / den);
+      cb[t] = sqrt((2.0 * nn + 1.0) * (nn - 1.0 - mm) * (nn - 1.0 + mm) / ((2.0 * nn - 3.0) * den));
+      cc[t] = col[(int64_t)(n - m) * stride];
+    }
+    __syncthreads();
+#pragma unroll 8
+    for (int t = 0; t < cnt; ++t) {
+      const double p2 = ca[t] * x * p1 - cb[t] * p0;
+      const double2 c = cc[t];
+      acc.x += c.x * p2;
+      acc.y += c.y * p2;
+      p0 = p1;
+      p1 = p2;
+    }
   }
-  out[j] = acc;
+  if (j < npts) out[j] = acc;
 }
 
 // ---------------------------------------------------------------- logarithmic proxy (Eq. logproxy)
@@ -1411,7 +1428,7 @@ mlg_status launch_eval_harmonic(const mlg_plan_s* p, const double* spec, int m, 
   if (npts <= 0) return MLG_OK;
   // the packed row offset of order m comes from the plan's host copy of the offsets
   const double2* col = reinterpret_cast<const double2*>(spec) + p->off[m] * p->nz + kk;
-  eval_harmonic_kernel<<<(unsigned)((npts + 255) / 256), 256, 0, s>>>(col, p->nz, m, p->nrc, p->g.ell, r, npts,
+  eval_harmonic_kernel<<<(unsigned)((npts + EV_T - 1) / EV_T), EV_T, 0, s>>>(col, p->nz, m, p->nrc, p->g.ell, r, npts,
                                                                      reinterpret_cast<double2*>(out));
   return check_launch("eval_harmonic_kernel");
 }
