@@ -86,65 +86,111 @@ struct MMArgs {
   float gscale;        // LOSS: 2 / (nvalid * N)
 };
 
-// Stage a 64 x 32 tile (rows r0.., contraction k0..) into Xs[row][k].  KC: element (r, k) at
-// src[r * ld + k]; otherwise at src[k * ld + r].  Rows >= R read as zero.
-template <bool KC>
-__device__ __forceinline__ void load_tile(const unsigned short* __restrict__ src, int ld, int r0, int R, int k0,
-                                          unsigned short (*Xs)[40], int tid) {
-  if (KC) {
-    const int r = tid >> 2, k8 = (tid & 3) * 8;
-    u16x8 v = (u16x8)(0);
-    if (r0 + r < R) v = *reinterpret_cast<const u16x8*>(src + (int64_t)(r0 + r) * ld + k0 + k8);
-    *reinterpret_cast<u16x8*>(&Xs[r][k8]) = v;
-  } else {
-    const int k = tid >> 3, r8 = (tid & 7) * 8;
-    u16x8 v = (u16x8)(0);
-    if (r0 + r8 < R) v = *reinterpret_cast<const u16x8*>(src + (int64_t)(k0 + k) * ld + r0 + r8);
+// A panel of NR rows (64 or 32) and KP contraction entries at most, in registers between the loads and the LDS
+// store.  KC: element (r, k) at src[r * ld + k], 256 / NR threads per row with 16-byte pieces of k in turn;
+// otherwise at src[k * ld + r], threads over 8-row pieces and pairs of k.  Rows >= R and entries past the
+// panel's kn read as zero.
+constexpr int KP = 288;       // the widest layer's contraction, and the row chunk of a weight gradient: one panel
+constexpr int KS = KP + 8;    // row stride in LDS: 148 words, so that the 16-byte reads of 16 rows spread over the banks
+
+template <int NR, bool KC>
+struct Panel {
+  static constexpr int TPR = 256 / NR;                                // KC: threads per row
+  static constexpr int TPK = NR / 8, PAIRS = 256 / TPK;               // otherwise: threads per k, pairs of k per pass
+  static constexpr int NQ = (KP / 2 + PAIRS - 1) / PAIRS;             // passes
+  static constexpr int NV = KC ? (KP / 8 + TPR - 1) / TPR : 2 * NQ;   // 16-byte loads per thread
+  u16x8 v[NV];
+
+  __device__ __forceinline__ void load(const unsigned short* __restrict__ src, int ld, int r0, int R, int k0, int kn,
+                                       int tid) {
 #pragma unroll
-    for (int i = 0; i < 8; ++i) Xs[r8 + i][k] = v[i];
+    for (int t = 0; t < NV; ++t) {
+      const int r = KC ? r0 + tid / TPR : r0 + 8 * (tid % TPK);
+      const int k = KC ? 8 * (tid % TPR + TPR * t) : 2 * (tid / TPK + PAIRS * (t >> 1)) + (t & 1);
+      v[t] = (u16x8)(0);
+      if (r < R && k < kn)
+        v[t] = *reinterpret_cast<const u16x8*>(src + (KC ? (int64_t)r * ld + k0 + k : (int64_t)(k0 + k) * ld + r));
+    }
   }
-}
+  __device__ __forceinline__ void store(unsigned short* Xs, int tid) const {
+    if (KC) {
+#pragma unroll
+      for (int t = 0; t < NV; ++t) {
+        const int k = 8 * (tid % TPR + TPR * t);
+        if (k < KP) *reinterpret_cast<u16x8*>(Xs + (tid / TPR) * KS + k) = v[t];
+      }
+    } else {
+#pragma unroll
+      for (int q = 0; q < NQ; ++q) {
+        const int k = 2 * (tid / TPK + PAIRS * q);
+        if (k >= KP) continue;
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+          *reinterpret_cast<unsigned int*>(Xs + (8 * (tid % TPK) + i) * KS + k) =
+              (unsigned int)v[2 * q][i] | ((unsigned int)v[2 * q + 1][i] << 16);
+      }
+    }
+  }
+};
 
 __device__ __forceinline__ bf16x8 frag(const unsigned short* p) {
   return __builtin_bit_cast(bf16x8, *reinterpret_cast<const u16x8*>(p));
 }
 
-// C = op(A) op(B) on 64 x 64 tiles, 4 waves of 32 x 32, with the layer epilogues.
+constexpr int BN = 32;  // columns per block (64 rows): 512 blocks for a 4096-row layer, two per CU
+
+struct MMShared {
+  __attribute__((aligned(16))) unsigned short A[64 * KS];
+  __attribute__((aligned(16))) unsigned short B[BN * KS];
+  float red[4];
+};
+
+// C = op(A) op(B) on the 64 x BN tile (bx, by) of split bz, 4 waves of 32 x BN / 2, with the layer epilogues.  The
+// products are small (4096 x 256 x 256: 0.5 us at the matrix rate), so latency bounds them: the whole
+// contraction of a tile is loaded at once, one wait and one barrier, where stages of 32 entries waited
+// for memory 8 times in turn (11 -> 8 us for a 4096-row layer).  The k order of every sum is kept.
 template <bool AK, bool BK, int EPI>
-__global__ __launch_bounds__(256) void mm_kernel(MMArgs a) {
-  __shared__ __attribute__((aligned(16))) unsigned short As[64][40];
-  __shared__ __attribute__((aligned(16))) unsigned short Bs[64][40];
-  __shared__ float red[4];
+__device__ __forceinline__ void mm_tile(const MMArgs& a, MMShared& sh, int bx, int by, int bz, int gx) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int m0 = blockIdx.y * 64, n0 = blockIdx.x * 64;
-  const int kbeg = blockIdx.z * a.kchunk;
+  const int m0 = by * 64, n0 = bx * BN;
+  const int kbeg = bz * a.kchunk;
   const int kend = min(a.K, kbeg + a.kchunk);
-  const int wm = (wave >> 1) * 32, wn = (wave & 1) * 32;
-  floatx4 acc[2][2];
+  constexpr int NJ = BN / 32;
+  const int wm = (wave >> 1) * 32, wn = (wave & 1) * (BN / 2);
+  floatx4 acc[2][NJ];
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
-    for (int j = 0; j < 2; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
-  for (int k0 = kbeg; k0 < kend; k0 += 32) {
-    load_tile<AK>(a.A, a.lda, m0, a.M, k0, As, tid);
-    load_tile<BK>(a.B, a.ldb, n0, a.N, k0, Bs, tid);
+    for (int j = 0; j < NJ; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+  for (int k0 = kbeg; k0 < kend; k0 += KP) {
+    const int kn = min(KP, kend - k0);
+    Panel<64, AK> pa;
+    Panel<BN, BK> pb;
+    pa.load(a.A, a.lda, m0, a.M, k0, kn, tid);
+    pb.load(a.B, a.ldb, n0, a.N, k0, kn, tid);
+    if (k0 > kbeg) __syncthreads();
+    pa.store(sh.A, tid);
+    pb.store(sh.B, tid);
     __syncthreads();
-    bf16x8 af[2], bfr[2];
+#pragma unroll 3
+    for (int ks = 0; ks < kn; ks += 32) {
+      bf16x8 af[2], bfr[NJ];
 #pragma unroll
-    for (int i = 0; i < 2; ++i) af[i] = frag(&As[wm + 16 * i + (lane & 15)][8 * (lane >> 4)]);
+      for (int i = 0; i < 2; ++i) af[i] = frag(sh.A + (wm + 16 * i + (lane & 15)) * KS + ks + 8 * (lane >> 4));
 #pragma unroll
-    for (int j = 0; j < 2; ++j) bfr[j] = frag(&Bs[wn + 16 * j + (lane & 15)][8 * (lane >> 4)]);
+      for (int j = 0; j < NJ; ++j) bfr[j] = frag(sh.B + (wn + 16 * j + (lane & 15)) * KS + ks + 8 * (lane >> 4));
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+      for (int i = 0; i < 2; ++i)
 #pragma unroll
-      for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[i], bfr[j], acc[i][j], 0, 0, 0);
-    __syncthreads();
+        for (int j = 0; j < NJ; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[i], bfr[j], acc[i][j], 0, 0, 0);
+    }
   }
   float ls = 0.f;
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
+    for (int j = 0; j < NJ; ++j)
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
         const int row = m0 + wm + 16 * i + 4 * (lane >> 4) + v;
@@ -153,7 +199,7 @@ __global__ __launch_bounds__(256) void mm_kernel(MMArgs a) {
         const float c = acc[i][j][v];
         const int64_t e = (int64_t)row * a.ldc + col;
         if (EPI == EPI_F32) {
-          a.Cf[blockIdx.z * a.cf_split + e] = c;
+          a.Cf[bz * a.cf_split + e] = c;
         } else if (EPI == EPI_TANH) {
           const float h = tanhf(c + a.bias[col]);
           a.Hf[e] = h;
@@ -176,22 +222,103 @@ __global__ __launch_bounds__(256) void mm_kernel(MMArgs a) {
   if (EPI == EPI_LOSS) {
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) ls += __shfl_xor(ls, o);
-    if (lane == 0) red[wave] = ls;
+    if (lane == 0) sh.red[wave] = ls;
     __syncthreads();
-    if (tid == 0) a.part[blockIdx.y * gridDim.x + blockIdx.x] = (red[0] + red[1]) + (red[2] + red[3]);
+    if (tid == 0) a.part[by * gx + bx] = (sh.red[0] + sh.red[1]) + (sh.red[2] + sh.red[3]);
   }
 }
 
-// Bias gradients: partial column sums of dy, dz2, dz1 over the rows of split z.
-__global__ __launch_bounds__(256) void colsum_kernel(const unsigned short* dy, const unsigned short* dz2,
-                                                     const unsigned short* dz1, int rows, int kchunk, float* part) {
-  const int z = blockIdx.x, layer = blockIdx.y, o = threadIdx.x;
+// Blocks go to the 8 XCDs round-robin (block b to XCD b mod 8), each with its own L2.  All column tiles of G
+// neighbouring row tiles (G = 4 from 32 row tiles on: the rows of one split of a weight gradient) are dealt
+// to one XCD, so that its L2 serves their common operand and finds what it wrote in the launch
+// before; so are all tiles of a split.  With the column tiles dealt out each XCD read every row.
+__host__ __device__ inline int row_group(int gy) { return gy >= 32 ? 4 : 1; }
+__host__ __device__ inline int row_blocks(int gx, int gy) {
+  const int g = row_group(gy);
+  return 8 * gx * g * ((gy + 8 * g - 1) / (8 * g));
+}
+__host__ __device__ inline int split_blocks(int gx, int gy, int splits) { return 8 * gx * gy * ((splits + 7) / 8); }
+__device__ __forceinline__ bool row_tile(int b, int gx, int gy, int& bx, int& by) {
+  const int g = row_group(gy), slot = b >> 3;
+  bx = slot % gx;
+  by = g * ((b & 7) + 8 * (slot / (g * gx))) + (slot / gx) % g;
+  return by < gy;
+}
+__device__ __forceinline__ bool split_tile(int b, int gx, int gy, int splits, int& bx, int& by, int& bz) {
+  const int slot = b >> 3, t = slot % (gx * gy);
+  bx = t % gx;
+  by = t / gx;
+  bz = (b & 7) + 8 * (slot / (gx * gy));
+  return bz < splits;
+}
+
+template <int EPI>
+__global__ __launch_bounds__(256) void mm_kernel(MMArgs a, int gx, int gy) {
+  __shared__ MMShared sh;
+  int bx, by;
+  if (row_tile(blockIdx.x, gx, gy, bx, by)) mm_tile<true, true, EPI>(a, sh, bx, by, 0, gx);
+}
+
+// A weight gradient and the backpropagated dz of the layer below, which do not depend on each other, in one
+// launch: blocks 0 .. nw - 1 are the gradient's tiles (gxw x gyw x splits), the others dz's.
+__global__ __launch_bounds__(256) void backward_kernel(MMArgs w, MMArgs d, int nw, int gxw, int gyw, int splits, int gxd,
+                                                       int gyd) {
+  __shared__ MMShared sh;
+  const int b = blockIdx.x;
+  int bx, by, bz;
+  if (b < nw) {
+    if (split_tile(b, gxw, gyw, splits, bx, by, bz)) mm_tile<false, false, EPI_F32>(w, sh, bx, by, bz, gxw);
+  } else {
+    if (row_tile(b - nw, gxd, gyd, bx, by)) mm_tile<true, false, EPI_DTANH>(d, sh, bx, by, 0, gxd);
+  }
+}
+
+// Bias gradients: partial column sums of dy, dz2, dz1 over the rows of split z, 32 columns per block.  The rows
+// come in panels of 256 staged in LDS (one row after the other, every add waited for its load: 60 us for
+// 4096 rows, 4 us in a launch of its own); every column is summed in row order.
+constexpr int CS_C = 32, CS_R = 256;
+
+__device__ __forceinline__ void colsum(const unsigned short* dy, const unsigned short* dz2, const unsigned short* dz1,
+                                       int rows, int kchunk, float* part, int z, int layer, int c0,
+                                       unsigned short (*xs)[CS_C]) {
   const unsigned short* src = layer == 0 ? dy : (layer == 1 ? dz2 : dz1);
   const int dst = layer == 0 ? P_B3 : (layer == 1 ? P_B2 : P_B1);
   const int r0 = z * kchunk, r1 = min(rows, r0 + kchunk);
+  const int lr = threadIdx.x >> 2, lc = 8 * (threadIdx.x & 3);
   float s = 0.f;
-  for (int r = r0; r < r1; ++r) s += bf16_f(src[(int64_t)r * HID + o]);
-  part[(int64_t)z * P_TOTAL + dst + o] = s;
+  for (int r = r0; r < r1; r += CS_R) {
+    u16x8 v[CS_R / 64];
+#pragma unroll
+    for (int t = 0; t < CS_R / 64; ++t) {
+      v[t] = (u16x8)(0);
+      if (r + lr + 64 * t < r1) v[t] = *reinterpret_cast<const u16x8*>(src + (int64_t)(r + lr + 64 * t) * HID + c0 + lc);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int t = 0; t < CS_R / 64; ++t) *reinterpret_cast<u16x8*>(&xs[lr + 64 * t][lc]) = v[t];
+    __syncthreads();
+    if (threadIdx.x < CS_C) {
+      const int n = min(CS_R, r1 - r);
+#pragma unroll 16
+      for (int k = 0; k < n; ++k) s += bf16_f(xs[k][threadIdx.x]);
+    }
+  }
+  if (threadIdx.x < CS_C) part[(int64_t)z * P_TOTAL + dst + c0 + threadIdx.x] = s;
+}
+
+// The first layer's weight gradient (tiles 0 .. nw - 1 as in backward_kernel) and the bias gradients of all three
+__global__ __launch_bounds__(256) void backward_last_kernel(MMArgs w, int nw, int gxw, int gyw, int splits,
+                                                            const unsigned short* dy, const unsigned short* dz2,
+                                                            const unsigned short* dz1, int rows, float* part) {
+  __shared__ MMShared sh;
+  static_assert(sizeof(sh.A) >= sizeof(unsigned short) * CS_R * CS_C, "the column panel fits in the A panel");
+  const int b = blockIdx.x;
+  int bx, by, bz;
+  if (b < nw) {
+    if (split_tile(b, gxw, gyw, splits, bx, by, bz)) mm_tile<false, false, EPI_F32>(w, sh, bx, by, bz, gxw);
+  } else if (split_tile(b - nw, HID / CS_C, 3, splits, bx, by, bz)) {
+    colsum(dy, dz2, dz1, rows, w.kchunk, part, bz, by, bx * CS_C, reinterpret_cast<unsigned short(*)[CS_C]>(sh.A));
+  }
 }
 
 // Gradient = sum of the split partials (fixed order), then Adam with bias correction.
@@ -200,8 +327,13 @@ __global__ __launch_bounds__(256) void adam_kernel(const float* part, int nsplit
                                                    float bc1, float bc2, float eps) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= P_TOTAL) return;
+  float q[NSPLIT_MAX];
+#pragma unroll
+  for (int z = 0; z < NSPLIT_MAX; ++z) q[z] = part[(int64_t)min(z, nsplit - 1) * P_TOTAL + i];  // all loads in flight
   float g = 0.f;
-  for (int z = 0; z < nsplit; ++z) g += part[(int64_t)z * P_TOTAL + i];
+#pragma unroll
+  for (int z = 0; z < NSPLIT_MAX; ++z)
+    if (z < nsplit) g += q[z];
   grad[i] = g;
   const float m = b1 * mom[i] + (1.f - b1) * g;
   const float v = b2 * vel[i] + (1.f - b2) * g * g;
@@ -228,32 +360,36 @@ __global__ __launch_bounds__(256) void loss_kernel(const float* part, int n, flo
 // Training / evaluation inputs from raw rows: X = bf16(x * xs) padded to KIN, T = y / ys.
 // idx (optional) selects rows of the data; an index outside [0, count) marks flags[0] and
 // yields a zero row.
-__global__ __launch_bounds__(256) void prep_kernel(const float* data_x, const float* data_y, const int32_t* idx,
-                                                   int64_t count, int nb, int rows, const float* xs,
-                                                   const float* ys, unsigned short* X, float* T, int* flags) {
-  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t nx = (int64_t)rows * KIN;
-  if (e < nx) {
-    const int r = (int)(e / KIN), j = (int)(e - (int64_t)r * KIN);
-    float v = 0.f;
-    if (r < nb && j < NIN) {
-      int64_t s = idx ? (int64_t)idx[r] : (int64_t)r;
-      if (s < 0 || s >= count) {
-        if (j == 0) flags[0] = 1;
-      } else {
-        v = data_x[s * NIN + j] * xs[j];
-      }
-    }
-    X[e] = bf16_bits(v);
+// A wavefront per row: its index is read once and the row's entries are in flight together.
+constexpr int PREP_ROWS = 4;
+
+__global__ __launch_bounds__(64 * PREP_ROWS) void prep_kernel(const float* data_x, const float* data_y, const int32_t* idx,
+                                                              int64_t count, int nb, int rows, const float* xs,
+                                                              const float* ys, unsigned short* X, float* T, int* flags) {
+  const int r = blockIdx.x * PREP_ROWS + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  if (r >= rows) return;
+  int64_t s = r < nb ? (idx ? (int64_t)idx[r] : (int64_t)r) : -1;
+  if (s < 0 || s >= count) {
+    if (r < nb && lane == 0) flags[0] = 1;
+    s = -1;
   }
-  if (data_y && e < (int64_t)rows * NOUT) {
-    const int r = (int)(e / NOUT), o = (int)(e - (int64_t)r * NOUT);
-    float v = 0.f;
-    if (r < nb) {
-      const int64_t s = idx ? (int64_t)idx[r] : (int64_t)r;
-      if (s >= 0 && s < count) v = data_y[s * NOUT + o] / ys[o];
-    }
-    T[e] = v;
+  const float* __restrict__ x = data_x + (s < 0 ? 0 : s) * NIN;
+  float v[(KIN + 63) / 64];
+#pragma unroll
+  for (int t = 0; t < (KIN + 63) / 64; ++t) {
+    const int j = lane + 64 * t;
+    v[t] = s >= 0 && j < NIN ? x[j] * xs[j] : 0.f;
+  }
+  unsigned short* __restrict__ Xr = X + (int64_t)r * KIN;
+#pragma unroll
+  for (int t = 0; t < (KIN + 63) / 64; ++t)
+    if (lane + 64 * t < KIN) Xr[lane + 64 * t] = bf16_bits(v[t]);
+  if (!data_y) return;
+  const float* __restrict__ y = data_y + (s < 0 ? 0 : s) * NOUT;
+#pragma unroll
+  for (int t = 0; t < NOUT / 64; ++t) {
+    const int o = lane + 64 * t;
+    T[(int64_t)r * NOUT + o] = s >= 0 ? y[o] / ys[o] : 0.f;
   }
 }
 
@@ -458,10 +594,20 @@ mlg_status dalloc(T** p, size_t n) {
   return MLG_OK;
 }
 
-template <bool AK, bool BK, int EPI>
-mlg_status mm(const MMArgs& a, int splits, hipStream_t s) {
-  dim3 grid((a.N + 63) / 64, (a.M + 63) / 64, splits);
-  hipLaunchKernelGGL((mm_kernel<AK, BK, EPI>), grid, dim3(256), 0, s, a);
+template <int EPI>
+mlg_status mm(const MMArgs& a, hipStream_t s) {
+  const int gx = (a.N + BN - 1) / BN, gy = (a.M + 63) / 64;
+  hipLaunchKernelGGL((mm_kernel<EPI>), dim3(row_blocks(gx, gy)), dim3(256), 0, s, a, gx, gy);
+  MLG_HIP_TRY(hipGetLastError());
+  return MLG_OK;
+}
+
+// the weight gradient w (nsplit splits) and the dz of the layer below, d, in one launch
+mlg_status mm_backward(const MMArgs& w, const MMArgs& d, int nsplit, hipStream_t s) {
+  const int gxw = (w.N + BN - 1) / BN, gyw = (w.M + 63) / 64, gxd = (d.N + BN - 1) / BN, gyd = (d.M + 63) / 64;
+  const int nw = split_blocks(gxw, gyw, nsplit);
+  hipLaunchKernelGGL(backward_kernel, dim3(nw + row_blocks(gxd, gyd)), dim3(256), 0, s, w, d, nw, gxw, gyw, nsplit, gxd,
+                     gyd);
   MLG_HIP_TRY(hipGetLastError());
   return MLG_OK;
 }
@@ -496,7 +642,7 @@ struct mlg_closure_s {
   float* d_v = nullptr;
   float* d_g = nullptr;
   float* d_part = nullptr;       // NSPLIT_MAX x P_TOTAL
-  float* d_loss_part = nullptr;  // (rows / 64) x (NOUT / 64)
+  float* d_loss_part = nullptr;  // (rows / 64) x (NOUT / BN)
   float* d_loss = nullptr;
   unsigned short* d_wb = nullptr;
   float* d_xs = nullptr;
@@ -561,7 +707,7 @@ mlg_status run_forward(mlg_closure_s* c, int rows, int nvalid, float* out, hipSt
   a.bias = c->d_p + P_B1;
   a.Hf = c->d_h1f;
   a.Cb = c->d_h1b;
-  if (mlg_status st = mm<true, true, EPI_TANH>(a, 1, s)) return st;
+  if (mlg_status st = mm<EPI_TANH>(a, s)) return st;
   a.A = c->d_h1b;
   a.lda = HID;
   a.B = c->d_wb + P_W2;
@@ -571,7 +717,7 @@ mlg_status run_forward(mlg_closure_s* c, int rows, int nvalid, float* out, hipSt
   a.bias = c->d_p + P_B2;
   a.Hf = c->d_h2f;
   a.Cb = c->d_h2b;
-  if (mlg_status st = mm<true, true, EPI_TANH>(a, 1, s)) return st;
+  if (mlg_status st = mm<EPI_TANH>(a, s)) return st;
   a.A = c->d_h2b;
   a.B = c->d_wb + P_W3;
   a.N = NOUT;
@@ -581,13 +727,13 @@ mlg_status run_forward(mlg_closure_s* c, int rows, int nvalid, float* out, hipSt
   if (out) {
     a.Cf = out;
     a.yscale = c->d_ys;
-    return mm<true, true, EPI_OUT>(a, 1, s);
+    return mm<EPI_OUT>(a, s);
   }
   a.T = c->d_t;
   a.Cb = c->d_dy;
   a.part = c->d_loss_part;
   a.gscale = 2.0f / ((float)nvalid * (float)NOUT);
-  return mm<true, true, EPI_LOSS>(a, 1, s);
+  return mm<EPI_LOSS>(a, s);
 }
 
 mlg_status run_backward(mlg_closure_s* c, int rows, float lr, hipStream_t s) {
@@ -606,7 +752,6 @@ mlg_status run_backward(mlg_closure_s* c, int rows, float lr, hipStream_t s) {
   g.N = HID;
   g.ldc = HID;
   g.Cf = c->d_part + P_W3;
-  if (mlg_status st = mm<false, false, EPI_F32>(g, nsplit, s)) return st;
   // dz2 = bf16((dy W3) * (1 - h2^2))
   MMArgs d{};
   d.M = rows;
@@ -620,12 +765,11 @@ mlg_status run_backward(mlg_closure_s* c, int rows, float lr, hipStream_t s) {
   d.ldc = HID;
   d.Hf = c->d_h2f;
   d.Cb = c->d_dz2;
-  if (mlg_status st = mm<true, false, EPI_DTANH>(d, 1, s)) return st;
+  if (mlg_status st = mm_backward(g, d, nsplit, s)) return st;
   g.A = c->d_dz2;
   g.lda = HID;
   g.B = c->d_h1b;
   g.Cf = c->d_part + P_W2;
-  if (mlg_status st = mm<false, false, EPI_F32>(g, nsplit, s)) return st;
   d.A = c->d_dz2;
   d.lda = HID;
   d.K = HID;
@@ -633,16 +777,16 @@ mlg_status run_backward(mlg_closure_s* c, int rows, float lr, hipStream_t s) {
   d.B = c->d_wb + P_W2;
   d.Hf = c->d_h1f;
   d.Cb = c->d_dz1;
-  if (mlg_status st = mm<true, false, EPI_DTANH>(d, 1, s)) return st;
+  if (mlg_status st = mm_backward(g, d, nsplit, s)) return st;
   g.A = c->d_dz1;
   g.B = c->d_x;
   g.ldb = KIN;
   g.N = KIN;
   g.ldc = KIN;
   g.Cf = c->d_part + P_W1;
-  if (mlg_status st = mm<false, false, EPI_F32>(g, nsplit, s)) return st;
-  hipLaunchKernelGGL(colsum_kernel, dim3(nsplit, 3), dim3(256), 0, s, c->d_dy, c->d_dz2, c->d_dz1, rows, kchunk,
-                     c->d_part);
+  const int gxw = (g.N + BN - 1) / BN, gyw = (g.M + 63) / 64, nw = split_blocks(gxw, gyw, nsplit);
+  hipLaunchKernelGGL(backward_last_kernel, dim3(nw + split_blocks(HID / CS_C, 3, nsplit)), dim3(256), 0, s, g, nw, gxw,
+                     gyw, nsplit, c->d_dy, c->d_dz2, c->d_dz1, rows, c->d_part);
   MLG_HIP_TRY(hipGetLastError());
   c->step += 1;
   const double b1 = 0.9, b2 = 0.999;
@@ -763,7 +907,7 @@ mlg_status mlg_closure_create(const mlg_closure_cfg* cfg, mlg_plan coarse, mlg_c
   if ((st = dalloc(&c->d_slot, slots.size())) || (st = dalloc(&c->d_col_of_slot, col_of_slot.size())) ||
       (st = dalloc(&c->d_p, P_TOTAL)) || (st = dalloc(&c->d_m, P_TOTAL)) || (st = dalloc(&c->d_v, P_TOTAL)) ||
       (st = dalloc(&c->d_g, P_TOTAL)) || (st = dalloc(&c->d_part, (size_t)NSPLIT_MAX * P_TOTAL)) ||
-      (st = dalloc(&c->d_loss_part, (R / 64) * (NOUT / 64))) || (st = dalloc(&c->d_loss, 1)) ||
+      (st = dalloc(&c->d_loss_part, (R / 64) * (NOUT / BN))) || (st = dalloc(&c->d_loss, 1)) ||
       (st = dalloc(&c->d_wb, P_TOTAL)) || (st = dalloc(&c->d_xs, KIN)) || (st = dalloc(&c->d_ys, NOUT)) ||
       (st = dalloc(&c->d_x, R * KIN)) || (st = dalloc(&c->d_h1b, R * HID)) || (st = dalloc(&c->d_h2b, R * HID)) ||
       (st = dalloc(&c->d_dy, R * NOUT)) || (st = dalloc(&c->d_dz2, R * HID)) || (st = dalloc(&c->d_dz1, R * HID)) ||
@@ -913,7 +1057,7 @@ mlg_status mlg_closure_forward(mlg_closure c, const float* x, int32_t nb, float*
   DevGuard guard(c->device);
   hipStream_t s = static_cast<hipStream_t>(stream);
   const int rows = round_up(nb, 64);
-  hipLaunchKernelGGL(prep_kernel, dim3(blocks_for((int64_t)rows * KIN)), dim3(256), 0, s, x, (const float*)nullptr,
+  hipLaunchKernelGGL(prep_kernel, dim3((rows + PREP_ROWS - 1) / PREP_ROWS), dim3(64 * PREP_ROWS), 0, s, x, (const float*)nullptr,
                      (const int32_t*)nullptr, (int64_t)nb, nb, rows, c->d_xs, c->d_ys, c->d_x, c->d_t, c->d_flags);
   MLG_HIP_TRY(hipGetLastError());
   return run_forward(c, rows, nb, y, s);
@@ -929,14 +1073,16 @@ mlg_status mlg_closure_train_step(mlg_closure c, const float* data_x, const floa
   DevGuard guard(c->device);
   hipStream_t s = static_cast<hipStream_t>(stream);
   const int rows = round_up(nb, 64);
-  hipLaunchKernelGGL(prep_kernel, dim3(blocks_for((int64_t)rows * KIN)), dim3(256), 0, s, data_x, data_y, idx, count,
+  hipLaunchKernelGGL(prep_kernel, dim3((rows + PREP_ROWS - 1) / PREP_ROWS), dim3(64 * PREP_ROWS), 0, s, data_x, data_y, idx, count,
                      nb, rows, c->d_xs, c->d_ys, c->d_x, c->d_t, c->d_flags);
   MLG_HIP_TRY(hipGetLastError());
   if (mlg_status st = run_forward(c, rows, nb, nullptr, s)) return st;
-  const int nparts = (rows / 64) * (NOUT / 64);
-  hipLaunchKernelGGL(loss_kernel, dim3(1), dim3(256), 0, s, c->d_loss_part, nparts,
-                     1.0f / ((float)nb * (float)NOUT), c->d_loss);
-  MLG_HIP_TRY(hipGetLastError());
+  if (loss_out) {
+    const int nparts = (rows / 64) * (NOUT / BN);
+    hipLaunchKernelGGL(loss_kernel, dim3(1), dim3(256), 0, s, c->d_loss_part, nparts,
+                       1.0f / ((float)nb * (float)NOUT), c->d_loss);
+    MLG_HIP_TRY(hipGetLastError());
+  }
   if (mlg_status st = run_backward(c, rows, lr, s)) return st;
   c->last_nb = nb;
   if (loss_out) {
