@@ -204,33 +204,35 @@ mlg_status mlg_plan_nodes(mlg_plan p, double* x, double* w, double* r) {
 
 // Radial products of one scalar field: folded over the node symmetry for even N_r (unless the plan
 // was created with MLG_RADIAL_FOLD=0), the generic batched GEMM otherwise.
-static mlg_status scalar_radial(const mlg_plan_s* p, int dir, const double* B, double* C, hipStream_t s) {
-  if (p->prec == MLG_SPLIT_BF16) return launch_split_scalar(p, dir, B, C, s);
-  if (p->prec == MLG_FP32) return launch_scalar_fold(p, dir, B, C, s);
-  if (p->use_fold && p->nr % 2 == 0) return launch_scalar_fold(p, dir, B, C, s);
+static mlg_status scalar_radial(const mlg_plan_s* p, int dir, const double* B, double* C, int orders, hipStream_t s) {
+  if (p->prec == MLG_SPLIT_BF16) return launch_split_scalar(p, dir, B, C, orders, s);
+  if (p->prec == MLG_FP32) return launch_scalar_fold(p, dir, B, C, orders, s);
+  if (p->use_fold && p->nr % 2 == 0) return launch_scalar_fold(p, dir, B, C, orders, s);
   GemmProds pr{};
   pr.nprod = 1;
   pr.A[0] = dir > 0 ? p->d_Pb : p->d_Pf;
   pr.B[0] = B;
   pr.C[0] = C;
-  return dir > 0 ? launch_gemm(p, pr, p->d_desc_bwd, p->max_rows_bwd, 2 * p->nz, s)
-                 : launch_gemm(p, pr, p->d_desc_fwd, p->max_rows_fwd, 2 * p->nz, s);
+  return dir > 0 ? launch_gemm(p, pr, p->d_desc_bwd, orders, p->max_rows_bwd, 2 * p->nz, s)
+                 : launch_gemm(p, pr, p->d_desc_fwd, orders, p->max_rows_fwd, 2 * p->nz, s);
 }
 
 // Spectrum -> harmonics at the nodes in w.X[0] (physical in z), and back.  'mask': under the two-thirds
-// mask, the slots outside it read and written as zero.  On 2D plans (N_z = 1) the axial transform is
+// mask, the slots outside it read and written as zero; the orders outside it are then neither transformed
+// nor multiplied (their harmonics stay unwritten, and the phi stages between do not read them).  On 2D plans (N_z = 1) the axial transform is
 // the identity and the radial product reads and writes the spectrum itself.
 static mlg_status to_harmonics(const mlg_plan_s* p, const double* spec, const Ws& w, bool mask, hipStream_t s) {
-  const int32_t* row_m = mask ? p->d_row_m : nullptr;
-  if (gemv_ok(p)) return launch_gemv(p, +1, spec, w.X[0], mask ? p->dealias_m + 1 : p->M, s);
-  if (mlg_status st = launch_zfft(p, spec, w.T[0], p->tau, +1, row_m, p->dealias_m, mask ? p->dealias_k : -1, s)) return st;
-  return scalar_radial(p, +1, w.T[0], w.X[0], s);
+  const int orders = mask ? std::min(p->M, p->dealias_m + 1) : p->M;
+  if (gemv_ok(p)) return launch_gemv(p, +1, spec, w.X[0], orders, s);
+  if (mlg_status st = launch_zfft(p, spec, w.T[0], p->off[orders], +1, nullptr, 0, mask ? p->dealias_k : -1, s)) return st;
+  return scalar_radial(p, +1, w.T[0], w.X[0], orders, s);
 }
 
 static mlg_status from_harmonics(const mlg_plan_s* p, const Ws& w, double* spec, bool mask, hipStream_t s) {
   const int32_t* row_m = mask ? p->d_row_m : nullptr;
-  if (gemv_ok(p)) return launch_gemv(p, -1, w.X[0], spec, mask ? p->dealias_m + 1 : p->M, s);
-  if (mlg_status st = scalar_radial(p, -1, w.X[0], spec, s)) return st;
+  const int orders = mask ? std::min(p->M, p->dealias_m + 1) : p->M;
+  if (gemv_ok(p)) return launch_gemv(p, -1, w.X[0], spec, orders, s);
+  if (mlg_status st = scalar_radial(p, -1, w.X[0], spec, orders, s)) return st;
   return launch_zfft(p, spec, spec, p->tau, -1, row_m, p->dealias_m, mask ? p->dealias_k : -1, s);
 }
 

@@ -386,7 +386,8 @@ __device__ __forceinline__ void gather_pairs16(double2 (*Z)[WROW], const Phi256&
 }
 
 // Scatters the spectrum X (v[j] = X[s + 32 j]) of each group's pair to the harmonics of its two
-// lines (orders m < M, scaled by 1/256; orders above mkeep written as zero).  Barriers at both ends.
+// lines (orders m < M, m <= mkeep, scaled by 1/256; the radial products after it read no others).  Barriers at
+// both ends.
 template <typename S2>
 __device__ __forceinline__ void scatter_pairs16(const double2 (&v)[8], double2 (*Z)[WROW], const Phi256& g,
                                                 int64_t q0, int ll, int s, S2* __restrict__ out) {
@@ -396,12 +397,13 @@ __device__ __forceinline__ void scatter_pairs16(const double2 (&v)[8], double2 (
   __syncthreads();
   const int t = threadIdx.x;
   const int mmax = g.M < 128 ? g.M : 128;
-  for (int e = t; e < PL2 * g.M; e += VB) {
+  const int mout = min(g.M, g.mkeep + 1);
+  for (int e = t; e < PL2 * mout; e += VB) {
     const int l2 = e & (PL2 - 1), m = e >> 4;
     const int64_t q = q0 + l2;
     if (q >= g.nlines) continue;
     double2 r = make_double2(0.0, 0.0);
-    if (m < mmax && m <= g.mkeep) {
+    if (m < mmax) {
       const double2* Zp = Z[l2 >> 1];
       const double2 zm = Zp[zpos(m)];
       const double2 zc = cconj(Zp[zpos((256 - m) & 255)]);
@@ -530,7 +532,7 @@ __global__ __launch_bounds__(VB) void zfft256w_kernel(const double2* __restrict_
   for (int j = 0; j < 8; ++j) {
     const int kk = s + 32 * j;
     v[j] = make_double2(0.0, 0.0);
-    if (!INV || keep(kk)) v[j] = ld2(x + kk);
+    if (INV ? keep(kk) : (!row_m || mrow <= mask_m)) v[j] = ld2(x + kk);  // a masked row may not have been written
   }
   fft256w<INV>(v, Z[ll], s, tw);
   S2* __restrict__ y = fs.out[f] + row * 256;

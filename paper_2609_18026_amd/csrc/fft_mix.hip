@@ -250,7 +250,7 @@ __global__ __launch_bounds__(256) void zmix_kernel(ZMix a, const double2* __rest
   for (int e = threadIdx.x; e < lb * R2; e += 256) {
     const int line = e / R2, n2 = e % R2;
     const int64_t row = r0 + line;
-    const bool ok = row < a.rows && !(INV && a.row_m && a.row_m[row < a.rows ? row : 0] > a.mask_m);
+    const bool ok = row < a.rows && !(a.row_m && a.row_m[row < a.rows ? row : 0] > a.mask_m);  // else zero
     const double2* x = in + row * n;
     double2 v[R1];
 #pragma unroll
@@ -459,6 +459,142 @@ __global__ __launch_bounds__(128) void phi_vec_mix_kernel(PhiMix g, const double
   }
 }
 
+// ---------------------------------------------------------------- scalar azimuthal stages
+// The backward transform and the nonlinear terms.  Two real lines (2p, 2p + 1) travel as one complex line
+// a + i b; a block takes 2^lbs pairs, R1 lanes per pair.  The LDS rows hold one entry more than the block has
+// pairs where the physical side reads them along j, so that neighbouring j start in different banks.
+// (The forward transform stays with phi_forward_kernel: its rounding is the floor of a transformed field's
+// smallest coefficients, which the projection's solves amplify, and another order of the same sums moved the
+// vector term of such a field by 2e-7 of its root mean square, in single coefficients, at 128^3.)
+
+// physical offsets of the lines qa and qa + 1 (N_r N_z fits 32 bits: N_r <= 4096, N_z <= 1024)
+__device__ __forceinline__ void pair_offs(const PhiMix& g, int64_t qa, int64_t& oa, int64_t& ob) {
+  const uint32_t q = (uint32_t)qa, i = q / (uint32_t)g.nz, l = q - i * (uint32_t)g.nz;
+  const bool wrap = l + 1 == (uint32_t)g.nz;
+  oa = ((int64_t)l * g.nr + i) * g.n;
+  ob = ((int64_t)(wrap ? 0 : l + 1) * g.nr + i + (wrap ? 1 : 0)) * g.n;
+}
+
+// the pair spectrum of the block's lines in Z (orders below min_, the others zero)
+template <int n, int R1>
+__device__ __forceinline__ void gather_pairs(const PhiMix& g, const double2* __restrict__ mixed, double2* Z, int row,
+                                             int64_t q0, int pr, int k1) {
+  const int64_t qa = q0 + 2 * pr;
+  for (int m = k1; m < g.min_; m += R1) {
+    const double2* f = mixed + (int64_t)m * g.nlines + qa;
+    const double2 a = qa < g.nlines ? f[0] : make_double2(0.0, 0.0);
+    const double2 b = qa + 1 < g.nlines ? f[1] : make_double2(0.0, 0.0);
+    if (m == 0) {
+      Z[pr] = make_double2(a.x, b.x);
+    } else {
+      Z[m * row + pr] = make_double2(a.x - b.y, a.y + b.x);
+      Z[(n - m) * row + pr] = make_double2(a.x + b.y, -a.y + b.x);
+    }
+  }
+  for (int k = g.min_ + k1; k <= n - g.min_; k += R1) Z[k * row + pr] = make_double2(0.0, 0.0);
+}
+
+// the harmonics of both lines of every pair from its spectrum in Z (orders below mout; from min_ on zero)
+template <int n, int R1>
+__device__ __forceinline__ void scatter_pairs(const PhiMix& g, double2* __restrict__ mixed, const double2* Z, int row,
+                                              int64_t q0, int pr, int k1) {
+  const int64_t qa = q0 + 2 * pr;
+  if (qa >= g.nlines) return;
+  const double h = 0.5 / n;
+  for (int m = k1; m < g.mout; m += R1) {
+    double2 A = make_double2(0.0, 0.0), B = A;
+    if (m < g.min_) {
+      const double2 zm = Z[m * row + pr], zc = cconj(Z[(m ? n - m : 0) * row + pr]);
+      const double2 d = csub(zm, zc);
+      A = cscale(cadd(zm, zc), h);
+      B = make_double2(h * d.y, -h * d.x);
+    }
+    double2* f = mixed + (int64_t)m * g.nlines + qa;
+    f[0] = A;
+    if (qa + 1 < g.nlines) f[1] = B;
+  }
+}
+
+template <int R1, int R2>
+__global__ __launch_bounds__(256) void phi_bwd_mix_kernel(PhiMix g, const double2* __restrict__ twg,
+                                                          const double2* __restrict__ mixed, double* __restrict__ phys) {
+  extern __shared__ double2 smem[];
+  constexpr int n = R1 * R2;
+  const int lb = 1 << g.lbs, row = lb + 1;
+  double2* Z = smem;
+  double2* T = smem + n * row;
+  double2* tw = T + n * row;
+  const int tid = threadIdx.x, pr = tid & (lb - 1), k1 = tid >> g.lbs;
+  const int64_t q0 = (int64_t)blockIdx.x << (g.lbs + 1);
+  for (int e = tid; e < n; e += blockDim.x) tw[e] = twg[e];
+  gather_pairs<n, R1>(g, mixed, Z, row, q0, pr, k1);
+  __syncthreads();
+  if (k1 < R2) mix_first<R1, true>(Z, T, R2, k1, pr, row, tw);
+  __syncthreads();
+  double2 x[R2];
+#pragma unroll
+  for (int c = 0; c < R2; ++c) x[c] = T[(k1 * R2 + c) * row + pr];
+  Dft<R2, true>::run(x);
+#pragma unroll
+  for (int c = 0; c < R2; ++c) Z[(k1 + c * R1) * row + pr] = x[c];
+  __syncthreads();
+  for (int e = tid; e < (n << g.lbs); e += blockDim.x) {
+    const int p = e / n, j = e - p * n;
+    const double2 v = Z[j * row + p];
+    const int64_t qa = q0 + 2 * p;
+    int64_t oa, ob;
+    pair_offs(g, qa, oa, ob);
+    if (qa < g.nlines) phys[oa + j] = v.x;
+    if (qa + 1 < g.nlines) phys[ob + j] = v.y;
+  }
+}
+
+// Scalar nonlinear term in place: the inverse transform ends with its radix-R2 pass, u^2 or gamma u (1 - u) on
+// both real lines in registers, and the forward transform starts from the same lanes with the radices in
+// the other order (see phi_vec_mix_kernel).
+template <int R1, int R2, int MODE>
+__global__ __launch_bounds__(256) void phi_scalar_mix_kernel(PhiMix g, const double2* __restrict__ twg, double2* mixed,
+                                                             double gamma) {
+  extern __shared__ double2 smem[];
+  constexpr int n = R1 * R2;
+  const int lb = 1 << g.lbs;
+  double2* Z = smem;
+  double2* T = smem + (n << g.lbs);
+  double2* tw = T + (n << g.lbs);
+  const int tid = threadIdx.x, pr = tid & (lb - 1), k1 = tid >> g.lbs;
+  const int64_t q0 = (int64_t)blockIdx.x << (g.lbs + 1);
+  for (int e = tid; e < n; e += blockDim.x) tw[e] = twg[e];
+  gather_pairs<n, R1>(g, mixed, Z, lb, q0, pr, k1);
+  __syncthreads();
+  if (k1 < R2) mix_first<R1, true>(Z, T, R2, k1, pr, lb, tw);
+  __syncthreads();
+  double2 x[R2];
+#pragma unroll
+  for (int c = 0; c < R2; ++c) x[c] = T[((k1 * R2 + c) << g.lbs) + pr];
+  Dft<R2, true>::run(x);
+#pragma unroll
+  for (int c = 0; c < R2; ++c) {
+    const double a = x[c].x, b = x[c].y;
+    x[c] = MODE == MLG_RHS_U2 ? make_double2(a * a, b * b)
+                              : make_double2(gamma * a * (1.0 - a), gamma * b * (1.0 - b));
+  }
+  Dft<R2, false>::run(x);
+  twiddle_tab<R2, false>(x, tw, k1);
+#pragma unroll
+  for (int c = 0; c < R2; ++c) Z[((c * R1 + k1) << g.lbs) + pr] = x[c];
+  __syncthreads();
+  if (k1 < R2) {
+    double2 v[R1];
+#pragma unroll
+    for (int c = 0; c < R1; ++c) v[c] = Z[((k1 * R1 + c) << g.lbs) + pr];
+    Dft<R1, false>::run(v);
+#pragma unroll
+    for (int c = 0; c < R1; ++c) T[((k1 + c * R2) << g.lbs) + pr] = v[c];  // every lane has read its row of T
+  }
+  __syncthreads();
+  scatter_pairs<n, R1>(g, mixed, T, lb, q0, pr, k1);
+}
+
 mlg_status check(const char* what) {
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return fail(MLG_E_DEVICE, std::string(what) + ": " + hipGetErrorString(e));
@@ -577,6 +713,65 @@ mlg_status launch_phi_vec_mix(const mlg_plan_s* p, const double* U, double* cons
   }
   p->timing.end(s);
   return check("phi_vec_mix_kernel");
+}
+
+// pairs of lines per block: at least a wavefront, and about two blocks per CU where there are lines for them
+static int pair_bits(const PhiMix& g, int R1) {
+  auto fits = [&](int lbs) { return 2 * g.n * ((1 << lbs) + 1) + g.n <= 4096; };  // 64 KB of LDS
+  int lbs = fits(3) ? 3 : 2;
+  while (lbs < 5 && fits(lbs + 1) && ((R1 << lbs) < 64 || ((R1 << lbs) < 128 && (g.nlines >> (lbs + 1)) > 1024))) ++lbs;
+  return lbs;
+}
+
+bool phi_mix_ok(const mlg_plan_s* p) {
+  int a, b;
+  return p->prec == MLG_FP64 && mix_pair(p->nphi, true, &a, &b);
+}
+
+mlg_status launch_phi_mix_backward(const mlg_plan_s* p, const double* mixed, double* phys, hipStream_t s) {
+  PhiMix g = phi_mix(p, false);
+  int R1, R2;
+  if (!mix_pair(p->nphi, true, &R1, &R2)) return fail(MLG_E_UNSUPPORTED, "phi stage: length without a radix pair");
+  g.lbs = pair_bits(g, R1);
+  const unsigned blocks = (unsigned)((g.nlines + (2 << g.lbs) - 1) >> (g.lbs + 1));
+  const unsigned threads = (unsigned)(R1 << g.lbs);
+  const size_t shm = ((size_t)2 * g.n * ((1 << g.lbs) + 1) + g.n) * sizeof(double2);
+  const double2* tw = reinterpret_cast<const double2*>(p->d_tw_phi);
+  const double2* f = reinterpret_cast<const double2*>(mixed);
+  p->timing.begin("phi_fft", s);
+  switch (g.n) {
+#define MIX_BWD(A, B) \
+  case A * B: phi_bwd_mix_kernel<A, B><<<blocks, threads, shm, s>>>(g, tw, f, phys); break;
+    MIX_PAIRS(MIX_BWD) MIX_WIDE(MIX_BWD)
+#undef MIX_BWD
+  }
+  p->timing.end(s);
+  return check("phi_bwd_mix_kernel");
+}
+
+mlg_status launch_phi_mix_scalar(const mlg_plan_s* p, int kind, double gamma, double* mixed, hipStream_t s) {
+  PhiMix g = phi_mix(p, p->g.dealias != 0);
+  int R1, R2;
+  if (!mix_pair(p->nphi, true, &R1, &R2)) return fail(MLG_E_UNSUPPORTED, "phi stage: length without a radix pair");
+  if (!p->g.dealias) g.mout = p->M;  // every stored order is written, the Nyquist order as zero
+  g.lbs = pair_bits(g, R1);
+  const unsigned blocks = (unsigned)((g.nlines + (2 << g.lbs) - 1) >> (g.lbs + 1));
+  const unsigned threads = (unsigned)(R1 << g.lbs);
+  const size_t shm = ((size_t)2 * (g.n << g.lbs) + g.n) * sizeof(double2);
+  const double2* tw = reinterpret_cast<const double2*>(p->d_tw_phi);
+  double2* f = reinterpret_cast<double2*>(mixed);
+  p->timing.begin("phi_fft", s);
+  switch (g.n) {
+#define MIX_SCALAR(A, B)                                                                                    \
+  case A * B:                                                                                               \
+    if (kind == MLG_RHS_U2) phi_scalar_mix_kernel<A, B, MLG_RHS_U2><<<blocks, threads, shm, s>>>(g, tw, f, gamma); \
+    else phi_scalar_mix_kernel<A, B, MLG_RHS_KPP><<<blocks, threads, shm, s>>>(g, tw, f, gamma);            \
+    break;
+    MIX_PAIRS(MIX_SCALAR) MIX_WIDE(MIX_SCALAR)
+#undef MIX_SCALAR
+  }
+  p->timing.end(s);
+  return check("phi_scalar_mix_kernel");
 }
 
 }  // namespace mlg

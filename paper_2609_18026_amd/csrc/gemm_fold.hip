@@ -729,7 +729,7 @@ mlg_status launch_proj_fold(const mlg_plan_s* p, double* const* in3, double* con
 }
 
 template <typename R>
-static void scalar_fold_go(const mlg_plan_s* p, int dir, const R* A, const double* B, double* C, hipStream_t s) {
+static void scalar_fold_go(const mlg_plan_s* p, int dir, const R* A, const double* B, double* C, int orders, hipStream_t s) {
   ScalarFoldArgs<R> a{};
   a.A = A;
   a.B = reinterpret_cast<const R*>(B);
@@ -740,19 +740,19 @@ static void scalar_fold_go(const mlg_plan_s* p, int dir, const R* A, const doubl
   a.ncol = 2 * p->nz;
   a.gx = (a.ncol + SC_N - 1) / SC_N;
   a.gy = dir > 0 ? (p->nr / 2 + TM - 1) / TM : ((p->nrc + 1) / 2 + 2 * TM - 1) / (2 * TM);
-  a.gz = p->M;
+  a.gz = orders;
   if (dir > 0)
     scal_bwd_fold_kernel<R><<<dim3(xcd_blocks(a.gx, a.gy, a.gz)), 256, 0, s>>>(a);
   else
     scal_fwd_fold_kernel<R><<<dim3(xcd_blocks(a.gx, a.gy, a.gz)), 512, 0, s>>>(a);
 }
 
-mlg_status launch_scalar_fold(const mlg_plan_s* p, int dir, const double* B, double* C, hipStream_t s) {
+mlg_status launch_scalar_fold(const mlg_plan_s* p, int dir, const double* B, double* C, int orders, hipStream_t s) {
   p->timing.begin("radial_gemm", s);
   if (p->prec == MLG_FP32)
-    scalar_fold_go<float>(p, dir, dir > 0 ? p->d_Pb32 : p->d_Pf32, B, C, s);
+    scalar_fold_go<float>(p, dir, dir > 0 ? p->d_Pb32 : p->d_Pf32, B, C, orders, s);
   else
-    scalar_fold_go<double>(p, dir, dir > 0 ? p->d_Pb : p->d_Pf, B, C, s);
+    scalar_fold_go<double>(p, dir, dir > 0 ? p->d_Pb : p->d_Pf, B, C, orders, s);
   p->timing.end(s);
   return check(dir > 0 ? "scal_bwd_fold_kernel" : "scal_fwd_fold_kernel");
 }

@@ -478,7 +478,7 @@ mlg_status launch_split_synth(const mlg_plan_s* p, const double* psi, const doub
   return check("split_synth_kernel");
 }
 
-mlg_status launch_split_scalar(const mlg_plan_s* p, int dir, const double* in, double* out, hipStream_t s) {
+mlg_status launch_split_scalar(const mlg_plan_s* p, int dir, const double* in, double* out, int orders, hipStream_t s) {
   const bool fwd = dir < 0;
   SplitScalarArgs a{};
   for (int t = 0; t < 2; ++t) a.tab[t] = fwd ? p->d_split_prj[t] : p->d_split_syn[t];
@@ -493,7 +493,7 @@ mlg_status launch_split_scalar(const mlg_plan_s* p, int dir, const double* in, d
   a.nz = p->nz;
   a.gx = (p->nz + TC - 1) / TC;
   a.gy = ((fwd ? p->nrc : p->nr) + TM - 1) / TM;
-  a.gz = p->M;
+  a.gz = orders;
   p->timing.begin("radial_gemm", s);
   if (fwd)
     split_scalar_kernel<true><<<xcd_blocks(a.gx, a.gy, a.gz), 256, 0, s>>>(a);

@@ -1188,12 +1188,12 @@ mlg_status check_launch(const char* what) {
 
 }  // namespace
 
-mlg_status launch_gemm(const mlg_plan_s* p, const GemmProds& prods, const GemmDesc* d_desc, int max_rows, int ncol,
-                       hipStream_t stream) {
+mlg_status launch_gemm(const mlg_plan_s* p, const GemmProds& prods, const GemmDesc* d_desc, int orders, int max_rows,
+                       int ncol, hipStream_t stream) {
   if (max_rows <= 0 || prods.nprod <= 0) return MLG_OK;
-  dim3 grid((ncol + GT_N - 1) / GT_N, (max_rows + GT_M - 1) / GT_M, p->M * prods.nprod);
+  dim3 grid((ncol + GT_N - 1) / GT_N, (max_rows + GT_M - 1) / GT_M, orders * prods.nprod);
   p->timing.begin("radial_gemm", stream);
-  radial_gemm_f64<<<grid, 256, 0, stream>>>(prods, d_desc, p->M, ncol);
+  radial_gemm_f64<<<grid, 256, 0, stream>>>(prods, d_desc, orders, ncol);
   p->timing.end(stream);
   return check_launch("radial_gemm_f64");
 }
@@ -1216,6 +1216,7 @@ mlg_status launch_phi_forward(const mlg_plan_s* p, const double* phys, double* m
 
 mlg_status launch_phi_backward(const mlg_plan_s* p, const double* mixed, double* phys, hipStream_t s) {
   if (p->nphi == 256 && p->use_fast_fft) return launch_phi256_backward(p, mixed, phys, s);
+  if (phi_mix_ok(p)) return launch_phi_mix_backward(p, mixed, phys, s);
   if (p->prec != MLG_FP64) return fail(MLG_E_UNSUPPORTED, "reduced-precision plans need N_phi = 256");
   PhiGeom g = phi_geom(p, false);
   const int lb = phi_lines_per_block(p->nphi);
@@ -1231,6 +1232,7 @@ mlg_status launch_phi_backward(const mlg_plan_s* p, const double* mixed, double*
 
 mlg_status launch_phi_scalar_rhs(const mlg_plan_s* p, int kind, double gamma, double* mixed, hipStream_t s) {
   if (p->nphi == 256 && p->use_fast_fft) return launch_phi256_scalar(p, kind, gamma, mixed, s);
+  if (phi_mix_ok(p)) return launch_phi_mix_scalar(p, kind, gamma, mixed, s);
   if (p->prec != MLG_FP64) return fail(MLG_E_UNSUPPORTED, "reduced-precision plans need N_phi = 256");
   PhiGeom g = phi_geom(p, p->g.dealias != 0);
   const int lb = phi_lines_per_block(p->nphi);

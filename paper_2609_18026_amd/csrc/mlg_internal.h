@@ -155,7 +155,8 @@ void gl_theta(int N, std::vector<long double>& theta, std::vector<long double>& 
 // Pbar_n^m(cos t) for n = m .. nmax into out[n - m]
 void pbar_col(int m, int nmax, long double t, long double* out);
 // kernels.hip launchers (all enqueue on 'stream')
-mlg_status launch_gemm(const mlg_plan_s* p, const GemmProds& prods, const GemmDesc* d_desc,
+// (the orders 0 .. orders - 1)
+mlg_status launch_gemm(const mlg_plan_s* p, const GemmProds& prods, const GemmDesc* d_desc, int orders,
                        int max_rows, int ncol, hipStream_t stream);
 mlg_status launch_phi_forward(const mlg_plan_s* p, const double* phys, double* mixed, hipStream_t s);
 mlg_status launch_phi_backward(const mlg_plan_s* p, const double* mixed, double* phys, hipStream_t s);
@@ -197,8 +198,8 @@ mlg_status launch_proj_gemm(const mlg_plan_s* p, double* const* in3, double* con
 mlg_status launch_synth_fold(const mlg_plan_s* p, const double* psi, const double* chi, double* const* out6,
                              hipStream_t s, const SynthMask& mask);
 // parity-folded radial products of one scalar field: dir > 0 backward (spectral rows -> harmonics
-// at the nodes), dir < 0 forward; even N_r only
-mlg_status launch_scalar_fold(const mlg_plan_s* p, int dir, const double* B, double* C, hipStream_t s);
+// at the nodes), dir < 0 forward; the orders 0 .. orders - 1; even N_r only
+mlg_status launch_scalar_fold(const mlg_plan_s* p, int dir, const double* B, double* C, int orders, hipStream_t s);
 mlg_status launch_proj_fold(const mlg_plan_s* p, double* const* in3, double* const* out3, int mmax, int kmax,
                             hipStream_t s);
 // gemv.hip: radial products of one scalar field on 2D plans, spectrum <-> harmonics of the first 'orders'
@@ -209,7 +210,7 @@ mlg_status launch_gemv(const mlg_plan_s* p, int dir, const double* x, double* y,
 mlg_status launch_split_synth(const mlg_plan_s* p, const double* psi, const double* chi, double* const* out6,
                               hipStream_t s, const SynthMask& mask);
 // split-bfloat16 radial products of the scalar transform pair: dir > 0 backward, dir < 0 forward
-mlg_status launch_split_scalar(const mlg_plan_s* p, int dir, const double* in, double* out, hipStream_t s);
+mlg_status launch_split_scalar(const mlg_plan_s* p, int dir, const double* in, double* out, int orders, hipStream_t s);
 // split-bfloat16 z transforms of N_z = 256 as two radix-16 DFT products on MFMA (same arguments
 // and masks as launch_zfft256)
 mlg_status launch_split_zdft(const mlg_plan_s* p, const double* const* in, double* const* out, int nf, int64_t rows,
@@ -283,6 +284,11 @@ mlg_status launch_zfft256(const mlg_plan_s* p, const double* const* in, double* 
 bool zmix_ok(const mlg_plan_s* p);
 mlg_status launch_zmix(const mlg_plan_s* p, const double* const* in, double* const* out, int nf, int64_t rows, int dir,
                        const int32_t* row_m, int mask_m, int mask_k, hipStream_t s, bool kept_only);
+// backward transform, and the nonlinear term 'kind' in place on mixed (under the mask the kept orders only are
+// read and written)
+bool phi_mix_ok(const mlg_plan_s* p);
+mlg_status launch_phi_mix_backward(const mlg_plan_s* p, const double* mixed, double* phys, hipStream_t s);
+mlg_status launch_phi_mix_scalar(const mlg_plan_s* p, int kind, double gamma, double* mixed, hipStream_t s);
 bool phi_vec_mix_ok(const mlg_plan_s* p);
 mlg_status launch_phi_vec_mix(const mlg_plan_s* p, const double* U, double* const* f6, double* taps, hipStream_t s);
 mlg_status launch_phi256_forward(const mlg_plan_s* p, const double* phys, double* mixed, hipStream_t s);

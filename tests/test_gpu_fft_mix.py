@@ -10,7 +10,7 @@ import pytest
 import synth
 from helpers import from_lib, rel, to_lib
 from oracle.grid import Grid
-from oracle.rhs import VecTables, rhs_tp
+from oracle.rhs import VecTables, rhs_scalar, rhs_tp
 from oracle.transform import Tables, backward, forward
 
 pytestmark = pytest.mark.gpu
@@ -43,6 +43,31 @@ def test_z_transform(n):
     assert rel(from_lib(spec.cpu().numpy(), g.M, g.nrc), ref) < TOL
     plan.backward(spec, back)
     assert rel(back.cpu().numpy(), backward(ref, g, t)) < TOL
+
+
+@pytest.mark.parametrize("nr, nz", [(5, 1), (7, 3), (40, 9)])
+@pytest.mark.parametrize("n", PAIRS + WIDE)
+def test_phi_scalar_stages(n, nr, nz):
+    """Transform pair with the Nyquist order stored, then both scalar terms (in place, masked) on an odd number of lines."""
+    M = n // 2 + 1
+    print("phi scalar stages", n, nr, nz, flush=True)
+    from paper_2609_18026_amd import MLG_RHS_KPP, MLG_RHS_U2
+    g = Grid(nr, n, nz, 0.9, lz=2.0, nphic=M)
+    t = Tables(g)
+    plan = _plan(nr, n, nz, 0.9, 2.0, nphic=M)
+    s = np.random.default_rng(n).standard_normal((nz, nr, n))
+    spec, back = torch.full_like(plan.empty_spec(), float("nan")), plan.empty_phys()
+    plan.forward(torch.from_numpy(s).cuda(), spec)
+    ref = forward(s, g, t)
+    assert rel(from_lib(spec.cpu().numpy(), g.M, g.nrc), ref) < TOL
+    plan.backward(spec, back)
+    assert rel(back.cpu().numpy(), backward(ref, g, t)) < TOL
+    S = synth.geometric_spectrum(g.M, g.nrc, nz, g.nzc, seed=4, a=0.8, b=0.8, c=0.8)
+    for kind, name in ((MLG_RHS_U2, "u2"), (MLG_RHS_KPP, "kpp")):
+        out = torch.full_like(spec, float("nan"))
+        plan.rhs_scalar(kind, 0.25, torch.from_numpy(to_lib(S)).cuda(), out)
+        got = from_lib(out.cpu().numpy(), g.M, g.nrc)
+        assert rel(got, rhs_scalar(S, g, t, name, 0.25)) < TOL and np.all(got[g.dealias_m() + 1:] == 0)
 
 
 @pytest.mark.parametrize("dealias", [0, 1])
