@@ -202,12 +202,12 @@ mlg_status mlg_plan_nodes(mlg_plan p, double* x, double* w, double* r) {
   return MLG_OK;
 }
 
-// Radial products of one scalar field: folded over the node symmetry for even N_r (unless the plan
-// was created with MLG_RADIAL_FOLD=0), the generic batched GEMM otherwise.
+// Radial products of one scalar field: folded over the node symmetry (unless the plan was created with
+// MLG_RADIAL_FOLD=0; forward for even N_r), the generic batched GEMM otherwise.
 static mlg_status scalar_radial(const mlg_plan_s* p, int dir, const double* B, double* C, int orders, hipStream_t s) {
   if (p->prec == MLG_SPLIT_BF16) return launch_split_scalar(p, dir, B, C, orders, s);
   if (p->prec == MLG_FP32) return launch_scalar_fold(p, dir, B, C, orders, s);
-  if (p->use_fold && p->nr % 2 == 0) return launch_scalar_fold(p, dir, B, C, orders, s);
+  if (p->use_fold && (dir > 0 || p->nr % 2 == 0)) return launch_scalar_fold(p, dir, B, C, orders, s);
   GemmProds pr{};
   pr.nprod = 1;
   pr.A[0] = dir > 0 ? p->d_Pb : p->d_Pf;

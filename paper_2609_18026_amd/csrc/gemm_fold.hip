@@ -383,8 +383,10 @@ __global__ __launch_bounds__(256, RG == 1 ? 4 : 2) void proj_fold_kernel(FoldPro
 // and an odd accumulator per block.  Loads are issued with clamped indices and zeros applied at the
 // LDS store (see synth_fold_kernel); every lane loads two adjacent entries at once (16 bytes in
 // FP64): half the load instructions of one entry per lane, 0.36 -> 0.34 ms for the transform pair.
-constexpr int SC_N = 64;  // real columns per block
-constexpr int SC_P = 8;   // pairs (backward) or half nodes (forward) per LDS stage
+// SC_N real columns per block, SC_P pairs (backward) or half nodes (forward) per LDS stage: 64 and 8 where the
+// launch fills the chip (16-deep stages leave room for fewer blocks per CU: 0.106 -> 0.121 ms backward at 256^3);
+// 32 and 16 below scalar_small() blocks, where a CU has one block and the stages' latency, not their
+// products, takes the time.  Both add the terms of a sum in the same order.
 
 template <typename R>
 struct ScalarFoldArgs {
@@ -396,13 +398,14 @@ struct ScalarFoldArgs {
   int gx, gy, gz;
 };
 
-// backward: f(i) = E(i) + O(i), f(N-1-i) = E(i) - O(i), E / O over even / odd n - m, i < N/2
-template <typename R>
-__global__ __launch_bounds__(256, 3) void scal_bwd_fold_kernel(ScalarFoldArgs<R> a) {
+// backward: f(i) = E(i) + O(i), f(N-1-i) = E(i) - O(i), E / O over even / odd n - m, i < (N+1)/2 (the middle node
+// of an odd N once)
+template <typename R, int SC_N, int SC_P>
+__global__ __launch_bounds__(256, SC_N == 64 ? 3 : 2) void scal_bwd_fold_kernel(ScalarFoldArgs<R> a) {
   Tile3 tl;
   if (!xcd_tile(a.gx, a.gy, a.gz, tl)) return;
   const int m = tl.z;
-  const int half = a.nr / 2, nr = a.nr, ncol = a.ncol;
+  const int half = (a.nr + 1) / 2, nr = a.nr, ncol = a.ncol;
   const int row0 = tl.y * TM, col0 = tl.x * SC_N;
   if (row0 >= half || col0 >= ncol) return;
   const int K = a.nrc > m ? a.nrc - m : 0;
@@ -413,30 +416,39 @@ __global__ __launch_bounds__(256, 3) void scal_bwd_fold_kernel(ScalarFoldArgs<R>
   __shared__ R As[2][2][SC_P][TM];    // [buf][parity][pair][half node]
   __shared__ R Bs[2][2][SC_P][SC_N];  // [buf][parity][pair][column]
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, cl = lane & 15;
-  typename Mma<R>::acc acc[2][4];
+  constexpr int NC = SC_N / 16;
+  typename Mma<R>::acc acc[2][NC];
 #pragma unroll
   for (int q = 0; q < 2; ++q)
 #pragma unroll
-    for (int c = 0; c < 4; ++c) acc[q][c] = Mma<R>::zero();
+    for (int c = 0; c < NC; ++c) acc[q][c] = Mma<R>::zero();
   // two register sets taken in turn, as in synth_fold_kernel: clamped unconditional loads two
   // stages ahead, zeros applied at the LDS store
-  constexpr int NL = SC_P / 4;  // 16-byte loads (two adjacent nodes or columns) per thread and stage of each operand
+  // 16-byte loads (two adjacent nodes or columns) per thread and stage
+  constexpr int NL = SC_P / 4, NB = SC_P * SC_N / 256, CH = SC_N / 2;
   typedef typename Mma<R>::pair P2;
+  typedef typename Mma<R>::pair_u P2u;  // table rows of odd length are 8-byte aligned
   struct Stage {
-    P2 a[NL], b[NL];
+    P2u a[NL];
+    P2 b[NB];
   };
   Stage sx, sy;
   const int Kc = K > 0 ? K - 1 : 0;
   auto load = [&](int p0, Stage& d) {
 #pragma unroll
     for (int t = 0; t < NL; ++t) {
-      const int e = tid + 256 * t;  // [parity][pair][32 pairs of nodes or columns]
+      const int e = tid + 256 * t;  // [parity][pair][32 pairs of nodes]
       const int par = e / (32 * SC_P), kr = (e / 32) % SC_P, c2 = 2 * (e % 32);
       const int jc = min(2 * (p0 + kr) + par, Kc);
-      const int ic = min(row0 + c2, nr - 2);  // exact for every kept node (< N_r / 2)
-      const int cc2 = min(col0 + c2, ncol - 2);
-      d.a[t] = *reinterpret_cast<const P2*>(A + (int64_t)jc * nr + ic);
-      d.b[t] = *reinterpret_cast<const P2*>(B + (int64_t)jc * ncol + cc2);
+      const int ic = min(row0 + c2, nr - 2);  // exact for every kept node (< (N_r + 1) / 2, N_r >= 3) and N_r = 2
+      d.a[t] = *reinterpret_cast<const P2u*>(A + (int64_t)jc * nr + ic);
+    }
+#pragma unroll
+    for (int t = 0; t < NB; ++t) {
+      const int e = tid + 256 * t;  // [parity][pair][pairs of columns]
+      const int par = e / (CH * SC_P), kr = (e / CH) % SC_P, c2 = 2 * (e % CH);
+      const int jc = min(2 * (p0 + kr) + par, Kc);
+      d.b[t] = *reinterpret_cast<const P2*>(B + (int64_t)jc * ncol + min(col0 + c2, ncol - 2));
     }
   };
   auto store = [&](int buf, int p0, const Stage& d) {
@@ -447,6 +459,12 @@ __global__ __launch_bounds__(256, 3) void scal_bwd_fold_kernel(ScalarFoldArgs<R>
       const bool jin = 2 * (p0 + kr) + par < K;
       As[buf][par][kr][c2] = (jin && row0 + c2 < half) ? d.a[t].x : R(0);
       As[buf][par][kr][c2 + 1] = (jin && row0 + c2 + 1 < half) ? d.a[t].y : R(0);
+    }
+#pragma unroll
+    for (int t = 0; t < NB; ++t) {
+      const int e = tid + 256 * t;
+      const int par = e / (CH * SC_P), kr = (e / CH) % SC_P, c2 = 2 * (e % CH);
+      const bool jin = 2 * (p0 + kr) + par < K;
       Bs[buf][par][kr][c2] = (jin && col0 + c2 < ncol) ? d.b[t].x : R(0);
       Bs[buf][par][kr][c2 + 1] = (jin && col0 + c2 + 1 < ncol) ? d.b[t].y : R(0);
     }
@@ -459,7 +477,7 @@ __global__ __launch_bounds__(256, 3) void scal_bwd_fold_kernel(ScalarFoldArgs<R>
       for (int par = 0; par < 2; ++par) {
         const R av = As[buf][par][kr][wave * 16 + cl];
 #pragma unroll
-        for (int c = 0; c < 4; ++c) acc[par][c] = MFMA(av, Bs[buf][par][kr][c * 16 + cl], acc[par][c]);
+        for (int c = 0; c < NC; ++c) acc[par][c] = MFMA(av, Bs[buf][par][kr][c * 16 + cl], acc[par][c]);
       }
     }
   };
@@ -487,7 +505,7 @@ __global__ __launch_bounds__(256, 3) void scal_bwd_fold_kernel(ScalarFoldArgs<R>
     if (kt < nk) compute(0);
   }
 #pragma unroll
-  for (int c = 0; c < 4; ++c) {
+  for (int c = 0; c < NC; ++c) {
     const int col = col0 + c * 16 + cl;
     if (col >= ncol) continue;
 #pragma unroll
@@ -496,17 +514,17 @@ __global__ __launch_bounds__(256, 3) void scal_bwd_fold_kernel(ScalarFoldArgs<R>
       if (i >= half) continue;
       const R e = acc[0][c][v], o = acc[1][c][v];
       C[(int64_t)i * ncol + col] = e + o;
-      C[(int64_t)(nr - 1 - i) * ncol + col] = e - o;
+      if (2 * i + 1 != nr) C[(int64_t)(nr - 1 - i) * ncol + col] = e - o;
     }
   }
 }
 
 // forward: even n - m rows contract with X_i + X_{N-1-i}, odd rows with the difference, i < N/2.
-// One block of 8 wavefronts covers 2 TM pairs of an order for 64 columns: wavefronts 0..3 the first
-// TM of them, 4..7 the next TM, both halves on the same staged sums and differences of the
+// One block of 8 wavefronts covers 2 TM pairs of an order for SC_N columns: SC_N / 16 wavefronts side by side
+// take 16 columns each, the others the next pairs, all on the same staged sums and differences of the
 // fields (with two blocks of TM pairs, each staged them; the second was partly empty on every order
 // at N_r = 256): 0.335 -> 0.328 ms for the transform pair at 256^3.
-template <typename R>
+template <typename R, int SC_N, int SC_P>
 __global__ __launch_bounds__(512) void scal_fwd_fold_kernel(ScalarFoldArgs<R> a) {
   Tile3 tl;
   if (!xcd_tile(a.gx, a.gy, a.gz, tl)) return;
@@ -521,22 +539,23 @@ __global__ __launch_bounds__(512) void scal_fwd_fold_kernel(ScalarFoldArgs<R> a)
   R* __restrict__ C = a.C + a.off[m] * ncol;
   __shared__ R As[2][2][SC_P][2 * TM];  // [buf][parity][half node][pair]
   __shared__ R Bs[2][2][SC_P][SC_N];  // [buf][sum, difference][half node][column]
-  const int tid = threadIdx.x, lane = tid & 63, wave = (tid >> 6) & 3, cl = lane & 15;
-  const int rloc = (tid >> 8) * TM, row0 = rowb + rloc;  // waves 4..7 take the block's pairs TM .. 2 TM - 1
-  typename Mma<R>::acc acc[2][4];
+  constexpr int NCW = SC_N / 16, NG = 2 * TM * NCW / (8 * 16);  // wavefronts side by side; groups of 16 pairs each
+  const int tid = threadIdx.x, lane = tid & 63, wave = (tid >> 6) % NCW, cl = lane & 15;
+  const int rloc = (tid >> 6) / NCW * 16 * NG, row0 = rowb + rloc;
+  typename Mma<R>::acc acc[2][NG];
 #pragma unroll
   for (int q = 0; q < 2; ++q)
 #pragma unroll
-    for (int c = 0; c < 4; ++c) acc[q][c] = Mma<R>::zero();
-  // wavefront w takes the block's columns 16 w .. 16 w + 15 for all its pairs, in 4 groups of 16;
+    for (int c = 0; c < NG; ++c) acc[q][c] = Mma<R>::zero();
+  // wavefront w takes 16 columns for all its pairs, in NG groups of 16;
   // groups wholly past the column (the second row tile of a short order) are skipped by every
   // wavefront alike, so the SIMDs stay evenly loaded (with 16 pairs per wavefront, the one that
   // held the first pairs worked on every tile and the others idled on short orders)
-  const int ng = max(0, min(4, (KP - row0 + 15) / 16));
+  const int ng = max(0, min(NG, (KP - row0 + 15) / 16));
   // 16-byte loads: the even and odd degree of a pair (adjacent in the [i][n - m] table; the odd one
   // of a last unpaired degree is the first entry of node i + 1, inside the table, and is not stored),
   // and two adjacent columns of the harmonics
-  constexpr int NA = SC_P / 4, NX = SC_P / 8;  // table and field loads per thread and stage
+  constexpr int NA = SC_P / 4, CH = SC_N / 2, NX = SC_P * CH / 256;  // table and field loads per thread and stage
   typedef typename Mma<R>::pair P2;
   typedef typename Mma<R>::pair_u P2u;  // 8-byte aligned (rows of odd length)
   struct Stage {
@@ -556,10 +575,10 @@ __global__ __launch_bounds__(512) void scal_fwd_fold_kernel(ScalarFoldArgs<R> a)
     }
 #pragma unroll
     for (int t = 0; t < NX; ++t) {
-      // [half node][32 pairs of columns]; threads 256..511 repeat the loads of 0..255 (unconditional
+      // [half node][pairs of columns]; threads 256..511 repeat the loads of 0..255 (unconditional
       // loads keep the wait counts uniform) and do not store them
       const int e = (tid & 255) + 256 * t;
-      const int kr = e / 32, c2 = 2 * (e % 32);
+      const int kr = e / CH, c2 = 2 * (e % CH);
       const int ic = min(i0 + kr, half - 1);
       const int cc2 = min(col0 + c2, ncol - 2);
       d.x[t] = *reinterpret_cast<const P2*>(B + (int64_t)ic * ncol + cc2);
@@ -579,7 +598,7 @@ __global__ __launch_bounds__(512) void scal_fwd_fold_kernel(ScalarFoldArgs<R> a)
 #pragma unroll
     for (int t = 0; t < NX; ++t) {
       const int e = tid + 256 * t;
-      const int kr = e / 32, c2 = 2 * (e % 32);
+      const int kr = e / CH, c2 = 2 * (e % CH);
       const bool iok = i0 + kr < half;
       const bool ok0 = iok && col0 + c2 < ncol, ok1 = iok && col0 + c2 + 1 < ncol;
       Bs[buf][0][kr][c2] = ok0 ? d.x[t].x + d.y[t].x : R(0);
@@ -597,7 +616,7 @@ __global__ __launch_bounds__(512) void scal_fwd_fold_kernel(ScalarFoldArgs<R> a)
         // even degrees contract with sums, odd with differences
         const R bv = Bs[buf][par][kr][wave * 16 + cl];
 #pragma unroll
-        for (int g = 0; g < 4; ++g)
+        for (int g = 0; g < NG; ++g)
           if (g < ng) acc[par][g] = MFMA(As[buf][par][kr][rloc + g * 16 + cl], bv, acc[par][g]);
       }
     }
@@ -626,7 +645,7 @@ __global__ __launch_bounds__(512) void scal_fwd_fold_kernel(ScalarFoldArgs<R> a)
   const int col = col0 + wave * 16 + cl;
   if (col >= ncol) return;
 #pragma unroll
-  for (int g = 0; g < 4; ++g) {
+  for (int g = 0; g < NG; ++g) {
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
       const int pr = row0 + g * 16 + Mma<R>::row(lane, v);
@@ -728,6 +747,9 @@ mlg_status launch_proj_fold(const mlg_plan_s* p, double* const* in3, double* con
   return check("proj_fold_kernel");
 }
 
+// launches of so few 64-column blocks take the small tiles
+static bool scalar_small(int blocks) { return blocks < 512; }
+
 template <typename R>
 static void scalar_fold_go(const mlg_plan_s* p, int dir, const R* A, const double* B, double* C, int orders, hipStream_t s) {
   ScalarFoldArgs<R> a{};
@@ -738,13 +760,19 @@ static void scalar_fold_go(const mlg_plan_s* p, int dir, const R* A, const doubl
   a.nr = p->nr;
   a.nrc = p->nrc;
   a.ncol = 2 * p->nz;
-  a.gx = (a.ncol + SC_N - 1) / SC_N;
-  a.gy = dir > 0 ? (p->nr / 2 + TM - 1) / TM : ((p->nrc + 1) / 2 + 2 * TM - 1) / (2 * TM);
+  a.gy = dir > 0 ? ((p->nr + 1) / 2 + TM - 1) / TM : ((p->nrc + 1) / 2 + 2 * TM - 1) / (2 * TM);
   a.gz = orders;
-  if (dir > 0)
-    scal_bwd_fold_kernel<R><<<dim3(xcd_blocks(a.gx, a.gy, a.gz)), 256, 0, s>>>(a);
-  else
-    scal_fwd_fold_kernel<R><<<dim3(xcd_blocks(a.gx, a.gy, a.gz)), 512, 0, s>>>(a);
+  const bool small = scalar_small((a.ncol + 63) / 64 * a.gy * a.gz);
+  const int width = small ? 32 : 64;
+  a.gx = (a.ncol + width - 1) / width;
+  const dim3 grid(xcd_blocks(a.gx, a.gy, a.gz));
+  if (dir > 0) {
+    if (small) scal_bwd_fold_kernel<R, 32, 16><<<grid, 256, 0, s>>>(a);
+    else scal_bwd_fold_kernel<R, 64, 8><<<grid, 256, 0, s>>>(a);
+  } else {
+    if (small) scal_fwd_fold_kernel<R, 32, 16><<<grid, 512, 0, s>>>(a);
+    else scal_fwd_fold_kernel<R, 64, 8><<<grid, 512, 0, s>>>(a);
+  }
 }
 
 mlg_status launch_scalar_fold(const mlg_plan_s* p, int dir, const double* B, double* C, int orders, hipStream_t s) {

@@ -198,7 +198,7 @@ mlg_status launch_proj_gemm(const mlg_plan_s* p, double* const* in3, double* con
 mlg_status launch_synth_fold(const mlg_plan_s* p, const double* psi, const double* chi, double* const* out6,
                              hipStream_t s, const SynthMask& mask);
 // parity-folded radial products of one scalar field: dir > 0 backward (spectral rows -> harmonics
-// at the nodes), dir < 0 forward; the orders 0 .. orders - 1; even N_r only
+// at the nodes), dir < 0 forward (even N_r only); the orders 0 .. orders - 1
 mlg_status launch_scalar_fold(const mlg_plan_s* p, int dir, const double* B, double* C, int orders, hipStream_t s);
 mlg_status launch_proj_fold(const mlg_plan_s* p, double* const* in3, double* const* out3, int mmax, int kmax,
                             hipStream_t s);
