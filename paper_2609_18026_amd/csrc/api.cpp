@@ -289,9 +289,9 @@ static bool rhs_skips_masked(const mlg_plan_s* p) {
 }
 
 // The kernel sequence of mlg_rhs_tp on the workspace 'ws' (caller-provided, or the per-GPU array of
-// mlg_rhs_tp_noalloc).
+// mlg_rhs_tp_noalloc).  'force': with the dissipation of the proxy parts (time integration).
 static mlg_status rhs_tp_run(mlg_plan p, const double* U, const void* psi, const void* chi, void* psi_n, void* chi_n,
-                             void* taps, void* ws, void* stream) {
+                             void* taps, void* ws, void* stream, bool force = false) {
   if (mlg_status st = check_plan(p)) return st;
   if (!psi || !chi || !psi_n || !chi_n || !ws) return fail(MLG_E_ARG, "null buffer");
   if (psi_n == chi_n || psi_n == psi || psi_n == chi || chi_n == psi || chi_n == chi)
@@ -326,11 +326,11 @@ static mlg_status rhs_tp_run(mlg_plan p, const double* U, const void* psi, const
   else
     st = launch_synth_gemm(p, static_cast<const double*>(psi), static_cast<const double*>(chi), w.X, s, smask);
   if (st) return st;
-  // the logarithmic proxy parts of the potentials, when they carry amplitudes (Eq. logproxy)
-  if ((st = launch_proxy_fields(p, w.X, s))) return st;
   // 2. inverse z transforms of the six fields (under the mask: the kept orders, the kept slots read)
   const int64_t mrows = (int64_t)(dealias ? std::min(p->M, p->dealias_m + 1) : p->M) * p->nr;
-  if ((st = launch_zfft_fields(p, w.X, w.X, 6, mrows, +1, nullptr, 0, dealias ? smask.kmax : -1, s))) return st;
+  // with the logarithmic proxy parts of the potentials, when they carry amplitudes (Eq. logproxy)
+  if ((st = launch_zfft_fields(p, w.X, w.X, 6, mrows, +1, nullptr, 0, dealias ? smask.kmax : -1, s, false, false, true)))
+    return st;
   // 3. phi stage: nodal u, w -> N = (U + u) x w -> harmonics of N_r/r, N_phi/r, N_z
   double* tp = static_cast<double*>(taps);
   if ((st = launch_phi_vec_rhs(p, Uh, w.X, tp, s))) return st;
@@ -350,7 +350,7 @@ static mlg_status rhs_tp_run(mlg_plan p, const double* U, const void* psi, const
   // 6. elliptic solves per (m, k)
   const double* csrc[3] = {w.T[0], w.T[1], w.T[2]};
   double* tsrc = tp ? tp + (size_t)9 * p->nz * p->nr * p->nphi : nullptr;
-  return launch_projection(p, csrc, static_cast<double*>(psi_n), static_cast<double*>(chi_n), tsrc, s);
+  return launch_projection(p, csrc, static_cast<double*>(psi_n), static_cast<double*>(chi_n), tsrc, force, s);
 }
 
 extern "C" {
@@ -433,7 +433,7 @@ mlg_status mlg_filter_setup(mlg_plan p, const mlg_filter_cfg* cfg) {
   if (cfg->eps_max < 0.0) return fail(MLG_E_ARG, "filter: eps_max must be >= 0");
   if (cfg->relax <= 0.0 || cfg->relax > 1.0) return fail(MLG_E_ARG, "filter: 0 < relax <= 1");
   DeviceGuard guard(p->device);
-  const size_t bytes = (size_t)(4 + 2 * FILTER_BLOCKS) * sizeof(double);
+  const size_t bytes = kFilterDoubles * sizeof(double);
   if (!p->d_filter) {
     hipError_t e = hipMalloc(reinterpret_cast<void**>(&p->d_filter), bytes);
     if (e != hipSuccess) {
@@ -441,9 +441,9 @@ mlg_status mlg_filter_setup(mlg_plan p, const mlg_filter_cfg* cfg) {
       return fail(MLG_E_ALLOC, std::string("hipMalloc: ") + hipGetErrorString(e));
     }
   }
-  const double zero[4] = {0.0, 0.0, 0.0, 0.0};
+  const std::vector<double> zero(kFilterDoubles, 0.0);
   MLG_HIP_TRY(hipDeviceSynchronize());
-  MLG_HIP_TRY(hipMemcpy(p->d_filter, zero, sizeof(zero), hipMemcpyHostToDevice));
+  MLG_HIP_TRY(hipMemcpy(p->d_filter, zero.data(), bytes, hipMemcpyHostToDevice));
   p->filter_zc = cfg->zeta_c;
   p->filter_tau = cfg->tau;
   p->filter_epsmax = cfg->eps_max;
@@ -458,7 +458,8 @@ mlg_status mlg_filter_apply(mlg_plan p, int32_t slot, void* spec, void* stream) 
   if (slot != 0 && slot != 1) return fail(MLG_E_ARG, "filter slot must be 0 or 1");
   if (!spec) return fail(MLG_E_ARG, "null buffer");
   DeviceGuard guard(p->device);
-  return launch_filter(p, slot, static_cast<double*>(spec), static_cast<hipStream_t>(stream));
+  double* f = static_cast<double*>(spec);
+  return launch_filter(p, slot, 1, &f, static_cast<hipStream_t>(stream));
 }
 
 mlg_status mlg_filter_state(mlg_plan p, double* out4) {
@@ -490,8 +491,7 @@ mlg_status mlg_tp_advance(mlg_plan p, const double* U, void* psi, void* chi, voi
   double* hc = static_cast<double*>(hist_chi);
   mlg_status st;
   auto rhs = [&](const double* a, const double* b, double* ra, double* rb) -> mlg_status {
-    if (mlg_status e = mlg_rhs_tp(p, U, a, b, ra, rb, nullptr, ws, stream)) return e;
-    if (mlg_status e = launch_proxy_force(p, ra, rb, s)) return e;   // dissipation of the proxy parts
+    if (mlg_status e = rhs_tp_run(p, U, a, b, ra, rb, nullptr, ws, stream, true)) return e;
     return closure ? closure_correct(closure, a, b, ra, rb, s) : MLG_OK;
   };
   // one step of both potentials
@@ -503,9 +503,8 @@ mlg_status mlg_tp_advance(mlg_plan p, const double* U, void* psi, void* chi, voi
   };
   // the adaptive modal filter between steps (Sec. 3.3), when enabled
   auto filter = [&]() -> mlg_status {
-    if (!p->filter_on) return MLG_OK;
-    if (mlg_status e = launch_filter(p, 0, sp, s)) return e;
-    return launch_filter(p, 1, sc, s);
+    double* f[2] = {sp, sc};
+    return p->filter_on ? launch_filter(p, 0, 2, f, s) : MLG_OK;
   };
   int done = 0;
   if (start) {
@@ -554,7 +553,7 @@ mlg_status mlg_scalar_advance(mlg_plan p, int32_t kind, double gamma, void* stat
   double* hp = static_cast<double*>(hist);
   mlg_status st;
   auto rhs = [&](const double* a, double* ra) { return mlg_rhs_scalar(p, kind, gamma, a, ra, ws, stream); };
-  auto filter = [&]() -> mlg_status { return p->filter_on ? launch_filter(p, 0, sp, s) : MLG_OK; };
+  auto filter = [&]() -> mlg_status { return p->filter_on ? launch_filter(p, 0, 1, &sp, s) : MLG_OK; };
   int done = 0;
   if (start) {
     // s1 = 2 S_{dt/2}(S_{dt/2}(s0)) - S_dt(s0), S_h(s) = (I - h L)^{-1} (s + h A(s))

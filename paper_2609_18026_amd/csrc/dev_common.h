@@ -86,6 +86,21 @@ __device__ __forceinline__ void block_sum(double (&acc)[NA]) {
   }
 }
 
+// Logarithmic proxy (Eq. logproxy).  Potentials psi~ + c_psi Lambda, chi~ + c_chi Lambda with Lambda = ln(r^2 + ell^2):
+// with q = (1 - x)^2 / ell^2 = grad_h^2 Lambda and r (1 - x) / ell^2 = 2 r / (r^2 + ell^2), the proxy parts add
+// u_phi = -c_psi r sqrt(q) / ell, u_z = -c_chi q, w_phi = -2 c_chi r q^{3/2} / ell, w_z = -c_psi q to the
+// m = 0, k = 0 harmonics (fields 1, 2, 4, 5 of u_r, u_phi, u_z, w_r, w_phi, w_z).
+struct LogProxy {
+  double cpsi, cchi, ell;
+};
+__device__ __forceinline__ double proxy_part(const LogProxy& p, int field, double rinv, double q) {
+  const double r = 1.0 / rinv, sq = sqrt(q);
+  if (field == 1) return -p.cpsi * r * sq / p.ell;
+  if (field == 2) return -p.cchi * q;
+  if (field == 4) return -2.0 * p.cchi * r * q * sq / p.ell;
+  return field == 5 ? -p.cpsi * q : 0.0;
+}
+
 // Storage conversions: reduced-precision plans keep fields as float / float2 in memory while the
 // kernels compute in double.
 __device__ __forceinline__ double2 ld2(const double2* p) { return *p; }

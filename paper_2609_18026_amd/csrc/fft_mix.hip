@@ -228,6 +228,11 @@ struct ZMix {
   int lb, mask_m, mask_k, kept_only;  // kept slots: |k| <= mask_k
   int64_t rows, per_field;
   const int32_t* row_m;
+  // the proxy parts (Eq. logproxy) join the slot 0 of the order 0 rows (node: rinv, q of the nr nodes; nr = 0: none;
+  // as a launch of its own this took 4 us a step)
+  const double* node;
+  int nr;
+  LogProxy proxy;
   const double2* in[6];
   double2* out[6];
 };
@@ -259,6 +264,7 @@ __global__ __launch_bounds__(256) void zmix_kernel(ZMix a, const double2* __rest
       v[c] = make_double2(0.0, 0.0);
       if (ok && (!INV || kk <= kp || kk >= n - kp)) v[c] = x[kk];
     }
+    if (INV && n2 == 0 && row < a.nr) v[0].x += proxy_part(a.proxy, (int)f, a.node[row], a.node[a.nr + row]);
     Dft<R1, INV>::run(v);
     twiddle<R1, INV>(v, tw, n2);
     double2* d = T + line * (R1 * RS) + n2;
@@ -625,7 +631,7 @@ bool zmix_ok(const mlg_plan_s* p) {
 }
 
 mlg_status launch_zmix(const mlg_plan_s* p, const double* const* in, double* const* out, int nf, int64_t rows, int dir,
-                       const int32_t* row_m, int mask_m, int mask_k, hipStream_t s, bool kept_only) {
+                       const int32_t* row_m, int mask_m, int mask_k, hipStream_t s, bool kept_only, bool proxy) {
   if (nf < 1 || nf > 6) return fail(MLG_E_ARG, "z transform: 1 to 6 fields per launch");
   ZMix a{};
   int R1, R2;
@@ -645,6 +651,11 @@ mlg_status launch_zmix(const mlg_plan_s* p, const double* const* in, double* con
   for (int i = 0; i < nf; ++i) {
     a.in[i] = reinterpret_cast<const double2*>(in[i]);
     a.out[i] = reinterpret_cast<double2*>(out[i]);
+  }
+  if (proxy && (p->log_cpsi != 0.0 || p->log_cchi != 0.0)) {
+    a.node = p->d_node;
+    a.nr = p->nr;
+    a.proxy = LogProxy{p->log_cpsi, p->log_cchi, p->g.ell};
   }
   const size_t shm = ((size_t)a.lb * line + p->nz) * sizeof(double2);
   const dim3 grid((unsigned)(a.per_field * nf));

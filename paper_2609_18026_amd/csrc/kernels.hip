@@ -560,6 +560,10 @@ struct ProjArgs {
   int nz, nrc, kmax, mmax;
   ColBlocks cb;                  // the aligned column blocks (one per block of the grid's x)
   double ell2, kap0;
+  // the regular parts evolve with the constant forcing c L Lambda on the m = 0, k = 0 column (Eq. logproxy), added
+  // to that column's outputs (null: none; as a launch of its own it took 4 us a step)
+  const double* __restrict__ force;
+  double cpsi, cchi;
 };
 
 constexpr int PS_SEG = 32;  // lanes (runs of degrees) per column: half a wave
@@ -741,6 +745,7 @@ __global__ __launch_bounds__(PS_SEG * PS_COL, SMAX <= 8 ? 2 : 1) void projection
   const int kk = active ? kc : 0;  // inactive lanes load column 0 and store nothing
   const int k = kval(kk, nz);
   const bool k0 = k == 0;
+  const bool forced = m == 0 && k0 && a.force != nullptr;
   const int nsol = cnt - i0;
   const int S = (nsol + PS_SEG - 1) / PS_SEG;
   const int s0 = i0 + r * S;
@@ -934,7 +939,7 @@ __global__ __launch_bounds__(PS_SEG * PS_COL, SMAX <= 8 ? 2 : 1) void projection
       if (j < len) {
         const int t = s0 + j;
         const double2 v = cscale(bp[j], srL[t]);
-        if (active) st2(ps + (int64_t)t * nz, v);
+        if (active) st2(ps + (int64_t)t * nz, forced ? make_double2(v.x + a.cpsi * a.force[t], v.y) : v);
         gpr += sgw[t] * v.x;
         gpi += sgw[t] * v.y;
         yq[j] = cscale(cscale(bq[j], k0 ? -1.0 : srL[t]), -ell2);  // the chi source -ell^2 q
@@ -971,7 +976,7 @@ __global__ __launch_bounds__(PS_SEG * PS_COL, SMAX <= 8 ? 2 : 1) void projection
       if (j < len) {
         const int t = s0 + j;
         const double2 v = cscale(yq[j], srL[t]);
-        if (active) st2(chv + (int64_t)t * nz, v);
+        if (active) st2(chv + (int64_t)t * nz, forced ? make_double2(v.x + a.cchi * a.force[t], v.y) : v);
         gcr += sgw[t] * v.x;
         gci += sgw[t] * v.y;
       }
@@ -989,8 +994,9 @@ __global__ __launch_bounds__(PS_SEG * PS_COL, SMAX <= 8 ? 2 : 1) void projection
       gci += __shfl_xor(gci, d, PS_SEG);
     }
     if (r == 0 && active) {
-      st2(ps, make_double2(-gpr / sgw[0], -gpi / sgw[0]));
-      st2(chv, make_double2(-gcr / sgw[0], -gci / sgw[0]));
+      const double2 p0 = make_double2(-gpr / sgw[0], -gpi / sgw[0]), c0 = make_double2(-gcr / sgw[0], -gci / sgw[0]);
+      st2(ps, forced ? make_double2(p0.x + a.cpsi * a.force[0], p0.y) : p0);
+      st2(chv, forced ? make_double2(c0.x + a.cchi * a.force[0], c0.y) : c0);
     }
   }
 }
@@ -1096,31 +1102,13 @@ __global__ __launch_bounds__(EV_T) void eval_harmonic_kernel(const double2* __re
   if (j < npts) out[j] = acc;
 }
 
-// ---------------------------------------------------------------- logarithmic proxy (Eq. logproxy)
-// Potentials psi~ + c_psi Lambda, chi~ + c_chi Lambda with Lambda = ln(r^2 + ell^2): at node i, with
-// q = (1 - x)^2 / ell^2 = grad_h^2 Lambda and r (1 - x) / ell^2 = 2 r / (r^2 + ell^2), the proxy parts
-// add u_phi = -c_psi r sqrt(q) / ell, u_z = -c_chi q, w_phi = -2 c_chi r q^{3/2} / ell, w_z = -c_psi q
-// to the m = 0, k = 0 harmonics (mixed layout, before the inverse z transforms).
-__global__ void proxy_fields_kernel(double2* __restrict__ up, double2* __restrict__ uz, double2* __restrict__ wp,
-                                    double2* __restrict__ wz, const double* __restrict__ node, int nr, int nz,
-                                    double cpsi, double cchi, double ell) {
+// the proxy parts added to the harmonics in place (mixed layout, before the inverse z transforms)
+__global__ void proxy_fields_kernel(Six fs, const double* __restrict__ node, int nr, int nz, LogProxy p) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= nr) return;
-  const double r = 1.0 / node[i], q = node[nr + i], sq = sqrt(q);
-  const int64_t o = (int64_t)i * nz;  // order 0, node i, axial slot 0
-  up[o].x += -cpsi * r * sq / ell;
-  uz[o].x += -cchi * q;
-  wp[o].x += -2.0 * cchi * r * q * sq / ell;
-  wz[o].x += -cpsi * q;
-}
-
-// The regular parts evolve with the constant forcing c L Lambda on the m = 0, k = 0 column.
-__global__ void proxy_force_kernel(double2* __restrict__ psi_n, double2* __restrict__ chi_n,
-                                   const double* __restrict__ f, int nrc, int nz, double cpsi, double cchi) {
-  const int n = blockIdx.x * blockDim.x + threadIdx.x;
-  if (n >= nrc) return;
-  psi_n[(int64_t)n * nz].x += cpsi * f[n];
-  chi_n[(int64_t)n * nz].x += cchi * f[n];
+#pragma unroll
+  for (int f = 1; f < 6; ++f)
+    if (f != 3) fs.f[f][(int64_t)i * nz].x += proxy_part(p, f, node[i], node[nr + i]);  // order 0, slot 0
 }
 
 // Zero every entry of the packed arrays whose (m, k) column is not active.
@@ -1273,13 +1261,16 @@ mlg_status launch_phi_vec_rhs(const mlg_plan_s* p, const double* U, double* cons
 
 mlg_status launch_zfft_fields(const mlg_plan_s* p, const double* const* in, double* const* out, int nf, int64_t rows,
                               int dir, const int32_t* row_m, int mask_m, int mask_k, hipStream_t s, bool fp64_only,
-                              bool kept_only) {
+                              bool kept_only, bool proxy) {
   if (rows <= 0 || nf <= 0) return MLG_OK;
+  if (proxy && !zmix_ok(p))
+    if (mlg_status st = launch_proxy_fields(p, out, s)) return st;  // in place: in == out
+  if (p->nz == 1 && !row_m && std::equal(in, in + nf, out)) return MLG_OK;  // one slot, always kept: the identity
   if (p->nz == 256 && p->prec == MLG_SPLIT_BF16 && !fp64_only)
     return launch_split_zdft(p, in, out, nf, rows, dir, row_m, mask_m, mask_k, s);
   if (p->nz == 256 && p->use_fast_fft)
     return launch_zfft256(p, in, out, nf, rows, dir, row_m, mask_m, mask_k, s, kept_only);
-  if (zmix_ok(p)) return launch_zmix(p, in, out, nf, rows, dir, row_m, mask_m, mask_k, s, kept_only);
+  if (zmix_ok(p)) return launch_zmix(p, in, out, nf, rows, dir, row_m, mask_m, mask_k, s, kept_only, proxy);
   if (p->prec != MLG_FP64) return fail(MLG_E_UNSUPPORTED, "reduced-precision plans need N_z = 256");
   for (int i = 0; i < nf; ++i)
     if (mlg_status st = launch_zfft(p, in[i], out[i], rows, dir, row_m, mask_m, mask_k, s)) return st;
@@ -1291,7 +1282,7 @@ mlg_status launch_zfft(const mlg_plan_s* p, const double* in, double* out, int64
   if (rows <= 0) return MLG_OK;
   if (p->nz == 256 && p->prec == MLG_SPLIT_BF16) return launch_split_zdft(p, &in, &out, 1, rows, dir, row_m, mask_m, mask_k, s);
   if (p->nz == 256 && p->use_fast_fft) return launch_zfft256(p, &in, &out, 1, rows, dir, row_m, mask_m, mask_k, s);
-  if (zmix_ok(p)) return launch_zmix(p, &in, &out, 1, rows, dir, row_m, mask_m, mask_k, s, false);
+  if (zmix_ok(p)) return launch_zmix(p, &in, &out, 1, rows, dir, row_m, mask_m, mask_k, s, false, false);
   if (p->prec != MLG_FP64) return fail(MLG_E_UNSUPPORTED, "reduced-precision plans need N_z = 256");
   ZGeom g{};
   g.nz = p->nz;
@@ -1327,8 +1318,11 @@ void active_columns(const mlg_plan_s* p, int* mmax_out, int* kmax_out) {
 }
 
 mlg_status launch_projection(const mlg_plan_s* p, const double* const* src3, double* psi_n, double* chi_n,
-                             double* taps_src, hipStream_t s) {
+                             double* taps_src, bool force, hipStream_t s) {
   ProjArgs a{};
+  if (force && (p->log_cpsi != 0.0 || p->log_cchi != 0.0)) a.force = p->d_logf;
+  a.cpsi = p->log_cpsi;
+  a.cchi = p->log_cchi;
   a.Cs = reinterpret_cast<const double2*>(src3[0]);
   a.Kp = reinterpret_cast<const double2*>(src3[1]);
   a.Pc = reinterpret_cast<const double2*>(src3[2]);
@@ -1437,18 +1431,10 @@ mlg_status launch_eval_harmonic(const mlg_plan_s* p, const double* spec, int m, 
 
 mlg_status launch_proxy_fields(const mlg_plan_s* p, double* const* f6, hipStream_t s) {
   if (p->log_cpsi == 0.0 && p->log_cchi == 0.0) return MLG_OK;
-  proxy_fields_kernel<<<(p->nr + 255) / 256, 256, 0, s>>>(
-      reinterpret_cast<double2*>(f6[1]), reinterpret_cast<double2*>(f6[2]), reinterpret_cast<double2*>(f6[4]),
-      reinterpret_cast<double2*>(f6[5]), p->d_node, p->nr, p->nz, p->log_cpsi, p->log_cchi, p->g.ell);
+  Six six;
+  for (int i = 0; i < 6; ++i) six.f[i] = reinterpret_cast<double2*>(f6[i]);
+  proxy_fields_kernel<<<(p->nr + 255) / 256, 256, 0, s>>>(six, p->d_node, p->nr, p->nz,
+                                                          LogProxy{p->log_cpsi, p->log_cchi, p->g.ell});
   return check_launch("proxy_fields_kernel");
 }
-
-mlg_status launch_proxy_force(const mlg_plan_s* p, double* psi_n, double* chi_n, hipStream_t s) {
-  if ((p->log_cpsi == 0.0 && p->log_cchi == 0.0) || !p->d_logf) return MLG_OK;
-  proxy_force_kernel<<<(p->nrc + 255) / 256, 256, 0, s>>>(reinterpret_cast<double2*>(psi_n),
-                                                           reinterpret_cast<double2*>(chi_n), p->d_logf, p->nrc,
-                                                           p->nz, p->log_cpsi, p->log_cchi);
-  return check_launch("proxy_force_kernel");
-}
 }  // namespace mlg
-

@@ -126,8 +126,8 @@ struct mlg_plan_s {
   double step_dt = 0, step_nu = 0, step_nuh = 0;
   int step_q = 1;                 // p / 2 (hyperviscosity power of grad^2), 1 when nu_h = 0
   bool step_ready = false;
-  // adaptive modal filter (mlg_filter_setup): d_filter holds [eps_psi, eps_chi, f_psi, f_chi] and
-  // then 2 * FILTER_BLOCKS partial sums
+  // adaptive modal filter (mlg_filter_setup): d_filter holds [eps_psi, eps_chi, f_psi, f_chi], then
+  // 2 * FILTER_BLOCKS partial sums of each field and a block counter of each field
   double* d_filter = nullptr;
   bool filter_on = false;
   double filter_zc = 0, filter_tau = 0, filter_epsmax = 0, filter_relax = 0;
@@ -173,13 +173,15 @@ mlg_status launch_zfft(const mlg_plan_s* p, const double* in, double* out, int64
 // axial modal kinetic energy from the velocity harmonics u_r, u_phi, u_z (mixed layout)
 mlg_status launch_energy(const mlg_plan_s* p, double* const* u3, double* energy, double* scratch, hipStream_t s);
 // (fp64_only: the FP64 transforms also on a split-bfloat16 plan; kept_only: the forward transform
-// may leave the slots outside the chop and masks unwritten, where the 256-point kernel runs)
+// may leave the slots outside the chop and masks unwritten, where the 256-point or the two-pass kernel runs;
+// proxy: the six harmonic fields in place, the proxy parts of the potentials added first, Eq. logproxy)
 mlg_status launch_zfft_fields(const mlg_plan_s* p, const double* const* in, double* const* out, int nf, int64_t rows,
                               int dir, const int32_t* row_m, int mask_m, int mask_k, hipStream_t s,
-                              bool fp64_only = false, bool kept_only = false);
+                              bool fp64_only = false, bool kept_only = false, bool proxy = false);
 // Elliptic solves from the projection sources (C, K', Zhat); taps_src receives C, K, Zhat.
+// 'force': the dissipation of the proxy parts of the potentials is added (Eq. logproxy).
 mlg_status launch_projection(const mlg_plan_s* p, const double* const* src3, double* psi_n, double* chi_n,
-                             double* taps_src, hipStream_t s);
+                             double* taps_src, bool force, hipStream_t s);
 // gemm_fused.hip: synthesis of the six velocity / vorticity harmonics from (psi, chi), and the five
 // projection products with the C, K', Zhat epilogue on the active (m < mmax, |k| <= kmax) columns.
 // The two-thirds mask on the potentials that enter the RHS: orders above mkeep and axial slots with
@@ -225,16 +227,16 @@ mlg_status launch_steps(const mlg_plan_s* p, int nf, int mode, int which, const 
 // s1 = 2 half - full over all spectral elements (the Richardson start-up of Sec. 3.3)
 mlg_status launch_richardson(const mlg_plan_s* p, const double* half, const double* full, double* out,
                              hipStream_t st);
-// adaptive modal filter of Sec. 3.3 on one packed spectral field with state slot 'slot' (0, 1)
+// adaptive modal filter of Sec. 3.3 on packed spectral fields: spec[i] (i < nf) with state slot 'slot' + i
 constexpr int FILTER_BLOCKS = 256;
-mlg_status launch_filter(const mlg_plan_s* p, int slot, double* spec, hipStream_t s);
+constexpr size_t kFilterDoubles = 4 + 4 * FILTER_BLOCKS + 1;  // states, partial sums of two fields, two counters
+mlg_status launch_filter(const mlg_plan_s* p, int slot, int nf, double* const* spec, hipStream_t s);
 // plan.cpp: L Lambda = nu g + nu_h (-Dbar_0)^{q-1} g on the m = 0 degrees (g: the image of
 // grad_h^2 Lambda, Eq. logproxy), in long double
 void proxy_forcing(const mlg_plan_s* p, double nu, double nuh, int q, std::vector<double>& out);
 // kernels.hip: the proxy parts of u_phi, u_z, w_phi, w_z added to the m = 0, k = 0 harmonics of the
-// six synthesised fields (mixed layout), and the forcing added to the m = 0, k = 0 column of the RHS
+// six synthesised fields (mixed layout)
 mlg_status launch_proxy_fields(const mlg_plan_s* p, double* const* f6, hipStream_t s);
-mlg_status launch_proxy_force(const mlg_plan_s* p, double* psi_n, double* chi_n, hipStream_t s);
 // kernels.hip: one (m, kk) column of a packed spectral field evaluated at npts radii (complex out)
 mlg_status launch_eval_harmonic(const mlg_plan_s* p, const double* spec, int m, int kk, const double* r, int64_t npts,
                                 double* out, hipStream_t s);
@@ -283,7 +285,7 @@ mlg_status launch_zfft256(const mlg_plan_s* p, const double* const* in, double* 
 // fft_mix.hip: two-pass transforms of the lengths n = R1 R2 other than 256
 bool zmix_ok(const mlg_plan_s* p);
 mlg_status launch_zmix(const mlg_plan_s* p, const double* const* in, double* const* out, int nf, int64_t rows, int dir,
-                       const int32_t* row_m, int mask_m, int mask_k, hipStream_t s, bool kept_only);
+                       const int32_t* row_m, int mask_m, int mask_k, hipStream_t s, bool kept_only, bool proxy);
 // backward transform, and the nonlinear term 'kind' in place on mixed (under the mask the kept orders only are
 // read and written)
 bool phi_mix_ok(const mlg_plan_s* p);

@@ -493,19 +493,21 @@ __global__ __launch_bounds__(GT) void step_bwd1_kernel(StepArgs a) {
 // Sec. 3.3: every coefficient whose normalised index zeta = max(n / N_r^c, m / N_phi^c,
 // |k| / N_z^c) exceeds zeta_c is multiplied by exp(-eps ((zeta - zeta_c) / (1 - zeta_c))^8); eps
 // follows the fraction f of sum |s|^2 held above zeta_c: target eps_max clip((f - tau) / tau, 0, 1),
-// relaxed as eps <- eps + r (target - eps), one state per field.  Three launches: partial sums over
-// a fixed number of blocks (so the reduction order never depends on the device), the state update
-// in one block, and the scaling.  The state stays on the device: a time loop never waits for it.
+// relaxed as eps <- eps + r (target - eps), one state per field.  Two launches for one or both fields (grid y):
+// partial sums over a fixed number of blocks, added in block order by the block that arrives last, which
+// updates the state (so the order never depends on the device); and the scaling, which ends at once while eps
+// is zero (its factors are then one).  The state stays on the device: a time loop never waits for it.
 struct FilterArgs {
-  double2* spec;
+  double2* spec[2];
   const int32_t* row_m;
   const int64_t* off;
   int64_t rows;
   int nz, nzc, nrc, M;
   double zc, tau, eps_max, relax;
   double* state;  // [eps_0, eps_1, f_0, f_1]
-  double* part;   // FILTER_BLOCKS x (tail, total)
-  int slot;
+  double* part;   // per slot: FILTER_BLOCKS x (tail, total)
+  unsigned int* count;  // per slot: blocks that have stored their sums (zero between launches)
+  int slot;       // of field 0
 };
 
 __device__ __forceinline__ double filter_zeta(const FilterArgs& a, int64_t row, int kk) {
@@ -516,21 +518,8 @@ __device__ __forceinline__ double filter_zeta(const FilterArgs& a, int64_t row, 
   return fmax(fmax(zr, zp), zz);
 }
 
-__global__ __launch_bounds__(256) void filter_sums_kernel(FilterArgs a) {
-  __shared__ double st[256], sa[256];
-  const int t = threadIdx.x;
-  double tail = 0.0, total = 0.0;
-  const int64_t n = a.rows * a.nz;
-  for (int64_t e = (int64_t)blockIdx.x * 256 + t; e < n; e += (int64_t)FILTER_BLOCKS * 256) {
-    const int64_t row = e / a.nz;
-    const int kk = (int)(e - row * a.nz);
-    const double2 v = a.spec[e];
-    const double w = v.x * v.x + v.y * v.y;
-    total += w;
-    if (filter_zeta(a, row, kk) > a.zc) tail += w;
-  }
-  st[t] = tail;
-  sa[t] = total;
+// tree sum of the pairs (st[t], sa[t]) over the 256 threads of a block, in st[0], sa[0]
+__device__ __forceinline__ void filter_tree(double* st, double* sa, int t) {
   __syncthreads();
   for (int h = 128; h > 0; h >>= 1) {
     if (t < h) {
@@ -539,36 +528,53 @@ __global__ __launch_bounds__(256) void filter_sums_kernel(FilterArgs a) {
     }
     __syncthreads();
   }
-  if (t == 0) {
-    a.part[2 * blockIdx.x] = st[0];
-    a.part[2 * blockIdx.x + 1] = sa[0];
-  }
 }
 
-__global__ __launch_bounds__(FILTER_BLOCKS) void filter_update_kernel(FilterArgs a) {
-  __shared__ double st[FILTER_BLOCKS], sa[FILTER_BLOCKS];
-  const int t = threadIdx.x;
-  st[t] = a.part[2 * t];
-  sa[t] = a.part[2 * t + 1];
-  __syncthreads();
-  for (int h = FILTER_BLOCKS / 2; h > 0; h >>= 1) {
-    if (t < h) {
-      st[t] += st[t + h];
-      sa[t] += sa[t + h];
-    }
-    __syncthreads();
+__global__ __launch_bounds__(256) void filter_sums_kernel(FilterArgs a) {
+  __shared__ double st[256], sa[256];
+  __shared__ bool last;
+  static_assert(FILTER_BLOCKS == 256, "the last block takes one partial sum per thread");
+  const int t = threadIdx.x, slot = a.slot + blockIdx.y;
+  const double2* __restrict__ spec = blockIdx.y ? a.spec[1] : a.spec[0];
+  double tail = 0.0, total = 0.0;
+  const int64_t n = a.rows * a.nz;
+  for (int64_t e = (int64_t)blockIdx.x * 256 + t; e < n; e += (int64_t)FILTER_BLOCKS * 256) {
+    const int64_t row = e / a.nz;
+    const int kk = (int)(e - row * a.nz);
+    const double2 v = spec[e];
+    const double w = v.x * v.x + v.y * v.y;
+    total += w;
+    if (filter_zeta(a, row, kk) > a.zc) tail += w;
   }
+  st[t] = tail;
+  sa[t] = total;
+  filter_tree(st, sa, t);
+  double* part = a.part + (size_t)slot * 2 * FILTER_BLOCKS;
+  if (t == 0) {
+    part[2 * blockIdx.x] = st[0];
+    part[2 * blockIdx.x + 1] = sa[0];
+    // the release publishes this block's sums, the acquire of the last block sees every other's
+    last = __hip_atomic_fetch_add(a.count + slot, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == FILTER_BLOCKS - 1;
+  }
+  __syncthreads();
+  if (!last) return;
+  st[t] = __hip_atomic_load(part + 2 * t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  sa[t] = __hip_atomic_load(part + 2 * t + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  filter_tree(st, sa, t);
   if (t == 0) {
     const double f = sa[0] > 0.0 ? st[0] / sa[0] : 0.0;
     const double target = a.eps_max * fmin(fmax((f - a.tau) / a.tau, 0.0), 1.0);
-    const double e0 = a.state[a.slot];
-    a.state[a.slot] = e0 + a.relax * (target - e0);
-    a.state[2 + a.slot] = f;
+    const double e0 = a.state[slot];
+    a.state[slot] = e0 + a.relax * (target - e0);
+    a.state[2 + slot] = f;
+    a.count[slot] = 0;
   }
 }
 
 __global__ __launch_bounds__(256) void filter_apply_kernel(FilterArgs a) {
-  const double eps = a.state[a.slot];
+  const double eps = a.state[a.slot + blockIdx.y];
+  if (eps == 0.0) return;
+  double2* __restrict__ spec = blockIdx.y ? a.spec[1] : a.spec[0];
   const int64_t n = a.rows * a.nz;
   for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < n; e += (int64_t)gridDim.x * 256) {
     const int64_t row = e / a.nz;
@@ -578,8 +584,8 @@ __global__ __launch_bounds__(256) void filter_apply_kernel(FilterArgs a) {
       const double x = (zeta - a.zc) / (1.0 - a.zc);
       const double x2 = x * x, x4 = x2 * x2;
       const double sg = exp(-eps * (x4 * x4));
-      const double2 v = a.spec[e];
-      a.spec[e] = make_double2(v.x * sg, v.y * sg);
+      const double2 v = spec[e];
+      spec[e] = make_double2(v.x * sg, v.y * sg);
     }
   }
 }
@@ -787,9 +793,9 @@ mlg_status launch_richardson(const mlg_plan_s* p, const double* half, const doub
   return MLG_OK;
 }
 
-mlg_status launch_filter(const mlg_plan_s* p, int slot, double* spec, hipStream_t st) {
+mlg_status launch_filter(const mlg_plan_s* p, int slot, int nf, double* const* spec, hipStream_t st) {
   FilterArgs a{};
-  a.spec = reinterpret_cast<double2*>(spec);
+  for (int i = 0; i < nf; ++i) a.spec[i] = reinterpret_cast<double2*>(spec[i]);
   a.row_m = p->d_row_m;
   a.off = p->d_goff;
   a.rows = p->tau;
@@ -803,13 +809,13 @@ mlg_status launch_filter(const mlg_plan_s* p, int slot, double* spec, hipStream_
   a.relax = p->filter_relax;
   a.state = p->d_filter;
   a.part = p->d_filter + 4;
+  a.count = reinterpret_cast<unsigned int*>(p->d_filter + 4 + 4 * FILTER_BLOCKS);
   a.slot = slot;
   const int64_t n = a.rows * a.nz;
   const unsigned blocks = (unsigned)std::min<int64_t>((n + 255) / 256, 4096);
   p->timing.begin("filter", st);
-  filter_sums_kernel<<<FILTER_BLOCKS, 256, 0, st>>>(a);
-  filter_update_kernel<<<1, FILTER_BLOCKS, 0, st>>>(a);
-  filter_apply_kernel<<<blocks, 256, 0, st>>>(a);
+  filter_sums_kernel<<<dim3(FILTER_BLOCKS, nf), 256, 0, st>>>(a);
+  filter_apply_kernel<<<dim3(blocks, nf), 256, 0, st>>>(a);
   p->timing.end(st);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return fail(MLG_E_DEVICE, std::string("filter kernels: ") + hipGetErrorString(e));
