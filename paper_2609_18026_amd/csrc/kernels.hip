@@ -1007,44 +1007,66 @@ __global__ __launch_bounds__(PS_SEG * PS_COL, SMAX <= 8 ? 2 : 1) void projection
 // its axial coefficient at slot kk is f_0,kk + sum_{m>=1} (f_m,kk e^{i m phi} + conj(f_m,-kk) e^{-i m phi})
 // and, by Parseval in phi,
 //   energy[kk] = (L_z/2) 2 pi sum_i W_i (|f_0,kk|^2 + sum_{m>=1} (|f_m,kk|^2 + |f_m,-kk|^2)),
-// summed over u_r, u_phi, u_z, with W_i = w_i ell^2/(1-x_i)^2.  Stage 1: block b sums the rows
-// [b EN_ROWS, (b+1) EN_ROWS) of every axial slot into part[b][kk] (lanes over kk, coalesced);
-// stage 2 adds the parts in block order.
-constexpr int EN_ROWS = 64;
+// summed over u_r, u_phi, u_z, with W_i = w_i ell^2/(1-x_i)^2.  Bound by the one read of the three fields.
+// Stage 1: a block sums its rows of every slot into part[0][kk][block] (the order m = 0) and part[1][kk][block]
+// (m >= 1); its threads are EN_T / cols row groups of cols slots.  Stage 2: a block per slot adds the parts of m = 0, of
+// kk and of -kk.  Reading each slot with its partner in stage 1, 64 rows a block with one thread a slot, took 52 us and the
+// sum of the parts by one thread a slot 48 us at N_r = 200 (192 kept), N_phi = N_z = 128.
+constexpr int EN_T = 256;
+constexpr int EN_ROWS = 64;   // rows per part that the scratch has to hold
 
-__global__ __launch_bounds__(256) void energy_part_kernel(const double2* __restrict__ ur,
-                                                          const double2* __restrict__ up,
-                                                          const double2* __restrict__ uz,
-                                                          const double* __restrict__ area, int nr, int nz,
-                                                          int nphi, int64_t rows, double* __restrict__ part) {
-  const int64_t r0 = (int64_t)blockIdx.x * EN_ROWS;
-  const int64_t r1 = r0 + EN_ROWS < rows ? r0 + EN_ROWS : rows;
-  for (int kk = threadIdx.x; kk < nz; kk += blockDim.x) {
-    const int kn = kk == 0 ? 0 : nz - kk;  // slot of -k
-    double acc = 0.0;
-    for (int64_t row = r0; row < r1; ++row) {
-      const int m = (int)(row / nr), i = (int)(row - (int64_t)m * nr);
-      if (2 * m == nphi) continue;  // the Nyquist order carries no physical field
-      const int64_t o = row * nz;
-      const double2 a = ur[o + kk], b = up[o + kk], d = uz[o + kk];
-      double e = a.x * a.x + a.y * a.y + b.x * b.x + b.y * b.y + d.x * d.x + d.y * d.y;
-      if (m > 0) {
-        const double2 a2 = ur[o + kn], b2 = up[o + kn], d2 = uz[o + kn];
-        e += a2.x * a2.x + a2.y * a2.y + b2.x * b2.x + b2.y * b2.y + d2.x * d2.x + d2.y * d2.y;
-      }
-      acc += area[i] * e;
+__global__ __launch_bounds__(EN_T) void energy_part_kernel(const double2* __restrict__ ur,
+                                                           const double2* __restrict__ up,
+                                                           const double2* __restrict__ uz,
+                                                           const double* __restrict__ area, int nr, int nz,
+                                                           int nphi, int rows, int per, int cols,
+                                                           double* __restrict__ part) {
+  __shared__ double red[2][EN_T];
+  const int groups = EN_T / cols, g = threadIdx.x / cols, c = threadIdx.x % cols;
+  const int r0 = blockIdx.x * per, r1 = r0 + per < rows ? r0 + per : rows;
+  for (int k0 = 0; k0 < nz; k0 += cols) {
+    const int kk = k0 + c, kc = kk < nz ? kk : nz - 1;
+    double zero = 0.0, pos = 0.0;
+#pragma unroll 4
+    for (int row = r0 + g; row < r1; row += groups) {
+      const int m = row / nr;
+      const int64_t o = (int64_t)row * nz + kc;
+      const double2 a = ur[o], b = up[o], d = uz[o];
+      double e = area[row - m * nr] * (a.x * a.x + a.y * a.y + b.x * b.x + b.y * b.y + d.x * d.x + d.y * d.y);
+      if (2 * m == nphi) e = 0.0;  // the Nyquist order carries no physical field
+      if (m == 0) zero += e;
+      else pos += e;
     }
-    part[(int64_t)blockIdx.x * nz + kk] = acc;
+    red[0][threadIdx.x] = zero;
+    red[1][threadIdx.x] = pos;
+    __syncthreads();
+    if (g == 0 && kk < nz) {
+      for (int u = 1; u < groups; ++u) {
+        zero += red[0][u * cols + c];
+        pos += red[1][u * cols + c];
+      }
+      part[(int64_t)kk * gridDim.x + blockIdx.x] = zero;
+      part[((int64_t)nz + kk) * gridDim.x + blockIdx.x] = pos;
+    }
+    __syncthreads();
   }
 }
 
-__global__ __launch_bounds__(256) void energy_sum_kernel(const double* __restrict__ part, int nparts, int nz,
-                                                         double scale, double* __restrict__ energy) {
-  const int kk = blockIdx.x * blockDim.x + threadIdx.x;
-  if (kk >= nz) return;
+__global__ __launch_bounds__(EN_T) void energy_sum_kernel(const double* __restrict__ part, int nparts, int nz,
+                                                          double scale, double* __restrict__ energy) {
+  __shared__ double red[EN_T / 64];
+  const int kk = blockIdx.x, kn = kk == 0 ? 0 : nz - kk;  // slots of k, -k
+  const double* pos = part + (int64_t)nz * nparts;
   double acc = 0.0;
-  for (int b = 0; b < nparts; ++b) acc += part[(int64_t)b * nz + kk];
-  energy[kk] = scale * acc;
+  for (int b = threadIdx.x; b < nparts; b += EN_T)
+    acc += part[(int64_t)kk * nparts + b] + (pos[(int64_t)kk * nparts + b] + pos[(int64_t)kn * nparts + b]);
+  for (int h = 1; h < 64; h <<= 1) acc += __shfl_xor(acc, h, 64);
+  if (threadIdx.x % 64 == 0) red[threadIdx.x / 64] = acc;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int w = 1; w < EN_T / 64; ++w) acc += red[w];
+    energy[kk] = scale * acc;
+  }
 }
 
 // ---------------------------------------------------------------- pointwise evaluation of one harmonic
@@ -1394,17 +1416,23 @@ mlg_status launch_projection(const mlg_plan_s* p, const double* const* src3, dou
 
 mlg_status launch_energy(const mlg_plan_s* p, double* const* u3, double* energy, double* scratch, hipStream_t s) {
   const int64_t rows = (int64_t)p->M * p->nr;
-  const int nparts = (int)((rows + EN_ROWS - 1) / EN_ROWS);
   if (rows <= 0) return fail(MLG_E_ARG, "energy: empty plan");
-  // the scratch (a triangular workspace array, 2 tri_elems doubles) holds nparts * nz partial sums
-  if ((int64_t)nparts * p->nz > 2 * (int64_t)p->tri_elems) return fail(MLG_E_UNSUPPORTED, "energy: scratch too small");
+  // the scratch is a triangular workspace array, 2 tri_elems doubles
+  if ((rows + EN_ROWS - 1) / EN_ROWS * p->nz > 2 * (int64_t)p->tri_elems)
+    return fail(MLG_E_UNSUPPORTED, "energy: scratch too small");
+  int cols = 1;
+  while (cols < p->nz && cols < EN_T) cols *= 2;
+  // up to 1024 parts (4 blocks a CU) of at least 4 rows a group, two sums of N_z slots each in the scratch
+  int64_t nparts = std::min<int64_t>(1024, std::max<int64_t>(1, rows / (4 * (EN_T / cols))));
+  nparts = std::max<int64_t>(1, std::min<int64_t>(nparts, (int64_t)p->tri_elems / p->nz));
+  const int per = (int)((rows + nparts - 1) / nparts);
+  nparts = (rows + per - 1) / per;
   const double scale = 0.5 * p->g.lz * 2.0 * M_PI;
-  energy_part_kernel<<<nparts, 256, 0, s>>>(reinterpret_cast<const double2*>(u3[0]),
-                                            reinterpret_cast<const double2*>(u3[1]),
-                                            reinterpret_cast<const double2*>(u3[2]), p->d_node + 3 * p->nr, p->nr,
-                                            p->nz, p->nphi, rows, scratch);
+  energy_part_kernel<<<(unsigned)nparts, EN_T, 0, s>>>(
+      reinterpret_cast<const double2*>(u3[0]), reinterpret_cast<const double2*>(u3[1]),
+      reinterpret_cast<const double2*>(u3[2]), p->d_node + 3 * p->nr, p->nr, p->nz, p->nphi, (int)rows, per, cols, scratch);
   if (mlg_status st = check_launch("energy_part_kernel")) return st;
-  energy_sum_kernel<<<(p->nz + 255) / 256, 256, 0, s>>>(scratch, nparts, p->nz, scale, energy);
+  energy_sum_kernel<<<p->nz, EN_T, 0, s>>>(scratch, (int)nparts, p->nz, scale, energy);
   return check_launch("energy_sum_kernel");
 }
 
