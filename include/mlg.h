@@ -323,9 +323,10 @@ mlg_status mlg_timing_read(mlg_plan plan, const char* kernel, double* total_ms, 
  * Legendre recurrence are built in FP64. */
 typedef struct mlg_batch_s* mlg_batch;
 
-/* Launch shape of the persistent kernels: regenerate Pbar by its recurrence in the backward
- * phase (1) or stream tables (0); threads per block (64, 128, 256); blocks per compute unit
- * (1..8, capped by occupancy); azimuthal lines per work item (even, 2..32). */
+/* Launch shape: regenerate Pbar by its recurrence in the radial phases (1; a block per order) or
+ * stream tables (0).  Persistent kernels (the azimuthal phase, and the radial phases with tables):
+ * threads per block (64, 128, 256); blocks per compute unit (1..8, capped by occupancy);
+ * azimuthal lines per work item (even, 2..32). */
 typedef struct {
   int32_t recurrence, threads, blocks_per_cu, lines;
 } mlg_batch_config;

@@ -5,12 +5,15 @@
 // walking its share of the phase's work list) run the phases; the kernel boundaries order them
 // (a grid-wide barrier inside one cooperative launch costs about 50 us on this part, against a few
 // microseconds for a launch boundary):
-//   1. backward radial transform per (instance, m): f_m(r_i) = sum_n Pbar_n^m(x_i) u_hat_n^m;
+//   1. backward radial transform per (instance, kept m): f_m(r_i) = sum_n Pbar_n^m(x_i) u_hat_n^m;
 //      Pbar either streamed from per-instance tables or regenerated in the kernel by the
 //      normalised three-term recurrence (FP64) from Pbar_m^m(x_i);
 //   2. per (instance, group of azimuthal lines): inverse real FFT in phi, gamma u (1 - u),
 //      forward FFT, two-thirds mask;
-//   3. forward radial projection per (instance, m): u_hat_n^m = sum_i w_i Pbar_n^m(x_i) g_m(r_i).
+//   3. forward radial projection per (instance, kept m): u_hat_n^m = sum_i w_i Pbar_n^m(x_i) g_m(r_i);
+//      one item per instance writes the zeros of its masked orders.
+// Both radial phases use Pbar_n^m(-x) = (-1)^(n-m) Pbar_n^m(x): the tables hold the nodes of one half, the even and
+// odd degrees are summed apart (backward) or act on sums and differences of mirrored nodes (forward).
 // Work lists of each phase are sorted by cost (largest first) and dealt round-robin to the
 // blocks.  Data may be FP64 or FP32 (template T); recurrences and tables are built in FP64.
 #include <hip/hip_runtime.h>
@@ -30,24 +33,32 @@
 namespace mlg {
 
 struct BatchInst {
-  int nr, nphi, M, nrc, mkeep, nrad;
+  int nr, nphi, M, nrc, nrad;
+  int mact;           // orders in the product: kept by the mask, with degrees, below the azimuthal Nyquist order
   int rad[8];
   int64_t spec_off;   // complex elements into the packed spectra
   int64_t mix_off;    // complex elements into the workspace (M x nr harmonics)
-  int64_t tb_off;     // backward table Pbar [m][n-m][i]  (reals)
-  int64_t tf_off;     // forward table w Pbar [m][i][n-m] (reals)
+  int64_t tb_off;     // backward table Pbar [m][n-m][i]  (reals), i over the (N_r + 1) / 2 nodes of one half
+  int64_t tf_off;     // forward table w Pbar [m][i][n-m] (reals), the same nodes
   int64_t rec_off;    // recurrence data: per m, (nrc - m) pairs (a_n, b_n)
-  int64_t start_off;  // Pbar_m^m(x_i): [m][i]
-  int64_t node_off;   // x_i
+  int64_t start_off;  // recurrence states [m][segment][2][i], the same nodes
+  int64_t node_off;   // x_i, then w_i
   int64_t tw_off;     // exp(-2 pi i t / N_phi), complex
-  int64_t tri_off;    // triangular row offset table start (M + 1 entries) in the int64 array
+};
+
+// One order of one instance in a radial phase, with every offset in it: a block reads it in one go where the
+// chain item -> instance -> triangular offset -> data cost three more dependent loads.  nr == 0: K zeros at spec.
+struct RadialItem {
+  int64_t spec, mix, tab, rec, start, node;
+  int nr, K, m, pad;
 };
 
 struct BatchConfig {
-  int recurrence;   // 1: regenerate Pbar in the kernel in phase 1
+  int recurrence;   // 1: regenerate Pbar in the kernels, 0: stream it from the tables
   int threads;      // 128 or 256
   int blocks_per_cu;
   int lines;        // azimuthal lines per phase-2 item (even)
+  int blocks[3];    // blocks of each phase's launch (0: the kernel does not fit)
 };
 
 }  // namespace mlg
@@ -63,11 +74,10 @@ struct mlg_batch_s {
   mlg::BatchInst* d_inst = nullptr;
   double* d_tab = nullptr;     // FP64 tables (backward, forward, recurrence, start, nodes, twiddles)
   float* d_tab32 = nullptr;    // FP32 copies of the backward / forward tables (FP32 batches)
-  int64_t* d_tri = nullptr;
-  int32_t* d_items[3] = {nullptr, nullptr, nullptr};  // packed (instance << 16 | index)
+  mlg::RadialItem* d_radial[2] = {nullptr, nullptr};  // phases 1 and 3
+  int32_t* d_phi = nullptr;                           // phase 2: packed (instance << 16 | first line)
   int nitems[3] = {0, 0, 0};
-  std::vector<int32_t> items_host[3];
-  mlg::BatchConfig cfg{0, 256, 2, 8};
+  mlg::BatchConfig cfg{0, 256, 2, 8, {0, 0, 0}};
   int tuned = 0;
   int cus = 0;
   size_t ws_bytes = 0;
@@ -194,71 +204,86 @@ struct BatchArgs {
   const BatchInst* inst;
   const double* tab;
   const T* tabT;         // tables in the data precision (backward / forward)
-  const int64_t* tri;
   const Cx<T>* spec_in;
   Cx<T>* spec_out;
   Cx<T>* mix;
-  const int32_t* items[3];
+  const RadialItem* radial[2];
+  const int32_t* phi;
   int nitems[3];
-  int recurrence;
   int lines;
   T gamma;
 };
 
+// Radial phases from the tables.  The whole block shares the contraction: the lanes of a sub (a wavefront, or half of one
+// where that covers the row) take two adjacent nodes (backward) or degrees (forward) with 16-byte loads, the subs every
+// subs-th term, U terms of loads at a time with clamped rows (the vector in LDS is zero past its end); the
+// partial sums of the subs meet in LDS.  Bound by the one read of the table: forward 42 us at 6.1 TB/s for 64 instances
+// (N_r 48 .. 256, N_phi 32 .. 256), where one thread per output walking the whole contraction over both halves of the
+// nodes took 110 us.
+constexpr int BT_DEG = 256;                     // the largest number of degrees, and of nodes
+constexpr int BT_PAD = 32;                      // zeros past the end of a vector: subs U terms at most
+constexpr int BT_VEC = (BT_DEG + 2 * BT_PAD);   // complex entries of the vector in LDS
+
+// two adjacent table entries, on the alignment of one; where the second lies past a row it is the next row's first or, at the
+// end of a table, the entry of the array that follows, and its sum is not stored
 template <typename T>
-__device__ void phase_backward(const BatchArgs<T>& A, int b, int m, char* smem) {
-  const BatchInst& I = A.inst[b];
-  const int K = (I.nrc > m && m <= I.mkeep) ? I.nrc - m : 0;  // a masked order enters as zero
-  Cx<T>* mix = A.mix + I.mix_off + (int64_t)m * I.nr;
-  if (K == 0) {
-    for (int i = threadIdx.x; i < I.nr; i += blockDim.x) mix[i] = cx<T>(0, 0);
-    return;
-  }
-  const int64_t trow = A.tri[I.tri_off + m];
-  Cx<T>* s = reinterpret_cast<Cx<T>*>(smem);
-  for (int t = threadIdx.x; t < K; t += blockDim.x) s[t] = A.spec_in[I.spec_off + trow + t];
-  double* rec = reinterpret_cast<double*>(smem + 256 * sizeof(Cx<double>));
-  if (A.recurrence)
-    for (int t = threadIdx.x; t < 2 * K; t += blockDim.x) rec[t] = A.tab[I.rec_off + 2 * trow + t];
-  __syncthreads();
-  for (int i = threadIdx.x; i < I.nr; i += blockDim.x) {
-    Cx<T> acc = cx<T>(0, 0);
-    if (A.recurrence) {
-      // Pbar_m^m, Pbar_{m+1}^m = sqrt(2m+3) x Pbar_m^m, Pbar_n^m = a_n x Pbar_{n-1} - b_n Pbar_{n-2}
-      const double x = A.tab[I.node_off + i];
-      double p0 = A.tab[I.start_off + (int64_t)m * I.nr + i];
-      double p1 = sqrt(2.0 * m + 3.0) * x * p0;
-      double ar = (double)s[0].x * p0, ai = (double)s[0].y * p0;
-      if (K > 1) {
-        ar += (double)s[1].x * p1;
-        ai += (double)s[1].y * p1;
-      }
-#pragma unroll 8
-      for (int t = 2; t < K; ++t) {
-        const double p2 = rec[2 * t] * x * p1 - rec[2 * t + 1] * p0;
-        ar += (double)s[t].x * p2;
-        ai += (double)s[t].y * p2;
-        p0 = p1;
-        p1 = p2;
-      }
-      acc = cx<T>((T)ar, (T)ai);
-    } else {
-      // eight independent partial sums keep eight table loads in flight
-      const T* P = A.tabT + I.tb_off + trow * I.nr + i;
-      Cx<T> part[8];
+struct TPair {
+  typedef T v __attribute__((ext_vector_type(2), aligned(sizeof(T))));
+};
+
+// lanes of a sub take two nodes each; SUB subs a wavefront (2 where 64 nodes fit half of it)
+template <typename T, int SUB>
+__device__ __forceinline__ void backward_table(const T* __restrict__ P, Cx<T>* s, int K, int nh, int nr, Cx<T>* mix) {
+  constexpr int LN = 64 / SUB, U = 4;
+  const int sub = threadIdx.x / LN, subs = blockDim.x / LN, q = 2 * (threadIdx.x % LN), col = min(q, nh - 1);
+  Cx<T> e[2], o[2];
+  e[0] = e[1] = o[0] = o[1] = cx<T>(0, 0);
+  for (int j0 = sub; 2 * j0 < K; j0 += subs * U) {
+    typename TPair<T>::v p[U][2];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) part[u] = cx<T>(0, 0);
-      int t = 0;
-      for (; t + 8 <= K; t += 8) {
+    for (int u = 0; u < U; ++u)
 #pragma unroll
-        for (int u = 0; u < 8; ++u) part[u] = part[u] + scl(s[t + u], P[(int64_t)(t + u) * I.nr]);
-      }
-      for (; t < K; ++t) part[0] = part[0] + scl(s[t], P[(int64_t)t * I.nr]);
+      for (int h = 0; h < 2; ++h)
+        p[u][h] = *reinterpret_cast<const typename TPair<T>::v*>(P + min(2 * (j0 + subs * u) + h, K - 1) * nh + col);
 #pragma unroll
-      for (int u = 1; u < 8; ++u) part[0] = part[0] + part[u];
-      acc = part[0];
+    for (int u = 0; u < U; ++u) {
+      const Cx<T> se = s[2 * (j0 + subs * u)], so = s[2 * (j0 + subs * u) + 1];
+      e[0] = e[0] + scl(se, p[u][0].x);
+      e[1] = e[1] + scl(se, p[u][0].y);
+      o[0] = o[0] + scl(so, p[u][1].x);
+      o[1] = o[1] + scl(so, p[u][1].y);
     }
-    mix[i] = acc;
+  }
+  __syncthreads();  // the vector has been read
+  Cx<T>* part = s;  // [sub][parity][node]
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    part[2 * sub * 2 * LN + q + h] = e[h];
+    part[(2 * sub + 1) * 2 * LN + q + h] = o[h];
+  }
+  __syncthreads();
+  for (int i = threadIdx.x; i < nh; i += blockDim.x) {
+    Cx<T> se = part[i], so = part[2 * LN + i];
+    for (int w = 1; w < subs; ++w) {
+      se = se + part[2 * w * 2 * LN + i];
+      so = so + part[(2 * w + 1) * 2 * LN + i];
+    }
+    mix[i] = se + so;
+    if (nr - 1 - i != i) mix[nr - 1 - i] = se - so;
+  }
+}
+
+template <typename T>
+__device__ void phase_backward(const BatchArgs<T>& A, const RadialItem I, char* smem) {
+  const int K = I.K, nr = I.nr, nh = (nr + 1) / 2;
+  Cx<T>* mix = A.mix + I.mix;
+  Cx<T>* s = reinterpret_cast<Cx<T>*>(smem);
+  for (int t = threadIdx.x; t < K + 2 * BT_PAD; t += blockDim.x) s[t] = t < K ? A.spec_in[I.spec + t] : cx<T>(0, 0);
+  __syncthreads();
+  if (nh <= 64) {
+    backward_table<T, 2>(A.tabT + I.tab, s, K, nh, nr, mix);
+  } else {
+    backward_table<T, 1>(A.tabT + I.tab, s, K, nh, nr, mix);
   }
   __syncthreads();
 }
@@ -279,7 +304,7 @@ __device__ void phase_phi(const BatchArgs<T>& A, int b, int q0, char* smem) {
   const int half = (n + 1) / 2;
   for (int e = threadIdx.x; e < np * half; e += blockDim.x) {
     const int p = e / half, m = e - p * half;
-    if (m >= I.M) continue;
+    if (m >= I.mact) continue;
     const int qa = q0 + 2 * p, qb = qa + 1;
     const Cx<T> a = qa < I.nr ? mix[(int64_t)m * I.nr + qa] : cx<T>(0, 0);
     const Cx<T> c = qb < I.nr ? mix[(int64_t)m * I.nr + qb] : cx<T>(0, 0);
@@ -299,7 +324,7 @@ __device__ void phase_phi(const BatchArgs<T>& A, int b, int q0, char* smem) {
   __syncthreads();
   Cx<T>* W = bfft<T>(Z, Z == X ? Y : X, I, tw, false, np);
   const T sc = (T)1 / (T)n;
-  for (int e = threadIdx.x; e < I.M * L; e += blockDim.x) {
+  for (int e = threadIdx.x; e < I.mact * L; e += blockDim.x) {
     const int m = e / L, ll = e - m * L;
     const int q = q0 + ll;
     if (q >= I.nr) continue;
@@ -313,64 +338,324 @@ __device__ void phase_phi(const BatchArgs<T>& A, int b, int q0, char* smem) {
       const Cx<T> d = zm - zc;
       v = cx<T>((T)0.5 * sc * d.y, -(T)0.5 * sc * d.x);
     }
-    if (2 * m >= n || m > I.mkeep) v = cx<T>(0, 0);
     mix[(int64_t)m * I.nr + q] = v;
   }
   __syncthreads();
 }
 
+// lanes of a sub take an even and the next odd degree, NG times
+template <typename T, int SUB, int NG, int U>
+__device__ __forceinline__ void forward_table(const T* __restrict__ P, Cx<T>* g, int K, int nh, Cx<T>* out) {
+  constexpr int LN = 64 / SUB;
+  const int sub = threadIdx.x / LN, subs = blockDim.x / LN, q = 2 * (threadIdx.x % LN);
+  Cx<T> e[NG], o[NG];
+  int col[NG];
+#pragma unroll
+  for (int c = 0; c < NG; ++c) {
+    e[c] = o[c] = cx<T>(0, 0);
+    col[c] = min(q + 128 * c, K - 1);
+  }
+  for (int i0 = sub; i0 < nh; i0 += subs * U) {
+    typename TPair<T>::v p[U][NG];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int c = 0; c < NG; ++c)
+        p[u][c] = *reinterpret_cast<const typename TPair<T>::v*>(P + min(i0 + subs * u, nh - 1) * K + col[c]);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const Cx<T> sum = g[2 * (i0 + subs * u)], dif = g[2 * (i0 + subs * u) + 1];
+#pragma unroll
+      for (int c = 0; c < NG; ++c) {
+        e[c] = e[c] + scl(sum, p[u][c].x);
+        o[c] = o[c] + scl(dif, p[u][c].y);
+      }
+    }
+  }
+  __syncthreads();  // the vector has been read
+  Cx<T>* part = g;  // [sub][degree]
+  constexpr int ROW = 2 * LN * NG;
+#pragma unroll
+  for (int c = 0; c < NG; ++c) {
+    part[sub * ROW + q + 128 * c] = e[c];
+    part[sub * ROW + q + 128 * c + 1] = o[c];
+  }
+  __syncthreads();
+  for (int t = threadIdx.x; t < K; t += blockDim.x) {
+    Cx<T> v = part[t];
+    for (int w = 1; w < subs; ++w) v = v + part[w * ROW + t];
+    out[t] = v;
+  }
+}
+
 template <typename T>
-__device__ void phase_forward(const BatchArgs<T>& A, int b, int m, char* smem) {
-  const BatchInst& I = A.inst[b];
-  const int K = I.nrc > m ? I.nrc - m : 0;
-  if (K == 0) return;
-  const int64_t trow = A.tri[I.tri_off + m];
-  Cx<T>* out = A.spec_out + I.spec_off + trow;
-  if (m > I.mkeep) {
+__device__ void phase_forward(const BatchArgs<T>& A, const RadialItem I, char* smem) {
+  const int K = I.K, nr = I.nr, nh = (nr + 1) / 2;
+  Cx<T>* out = A.spec_out + I.spec;
+  if (nr == 0) {
     for (int t = threadIdx.x; t < K; t += blockDim.x) out[t] = cx<T>(0, 0);
     return;
   }
-  Cx<T>* g = reinterpret_cast<Cx<T>*>(smem);
-  const Cx<T>* mix = A.mix + I.mix_off + (int64_t)m * I.nr;
-  for (int i = threadIdx.x; i < I.nr; i += blockDim.x) g[i] = mix[i];
-  __syncthreads();
-  const T* P = A.tabT + I.tf_off + trow * I.nr;
-  for (int t = threadIdx.x; t < K; t += blockDim.x) {
-    // eight independent partial sums keep eight table loads in flight
-    Cx<T> part[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) part[u] = cx<T>(0, 0);
-    int i = 0;
-    for (; i + 8 <= I.nr; i += 8) {
-#pragma unroll
-      for (int u = 0; u < 8; ++u) part[u] = part[u] + scl(g[i + u], P[(int64_t)(i + u) * K + t]);
-    }
-    for (; i < I.nr; ++i) part[0] = part[0] + scl(g[i], P[(int64_t)i * K + t]);
-#pragma unroll
-    for (int u = 1; u < 8; ++u) part[0] = part[0] + part[u];
-    out[t] = part[0];
+  Cx<T>* g = reinterpret_cast<Cx<T>*>(smem);  // [half node][sum, difference]
+  const Cx<T>* mix = A.mix + I.mix;
+  for (int i = threadIdx.x; i < nh + BT_PAD; i += blockDim.x) {
+    const int ic = min(i, nh - 1);
+    const Cx<T> a = mix[ic], b = mix[nr - 1 - ic];
+    const bool in = i < nh, mid = nr - 1 - i == i;  // the middle node of an odd N_r stands alone
+    g[2 * i] = !in ? cx<T>(0, 0) : (mid ? a : a + b);
+    g[2 * i + 1] = in && !mid ? a - b : cx<T>(0, 0);
   }
+  __syncthreads();
+  const T* P = A.tabT + I.tab;
+  if (K <= 64) forward_table<T, 2, 1, 4>(P, g, K, nh, out);
+  else if (K <= 128) forward_table<T, 1, 1, 8>(P, g, K, nh, out);
+  else forward_table<T, 1, 2, 4>(P, g, K, nh, out);
   __syncthreads();
 }
 
 template <typename T, int PHASE>
-__global__ void batch_kernel(BatchArgs<T> A) {
+__global__ __launch_bounds__(256, PHASE == 2 ? 5 : 6) void batch_kernel(BatchArgs<T> A) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
   for (int it = blockIdx.x; it < A.nitems[PHASE]; it += gridDim.x) {
-    const int w = A.items[PHASE][it];
-    if constexpr (PHASE == 0) phase_backward<T>(A, w >> 16, w & 0xffff, smem);
-    else if constexpr (PHASE == 1) phase_phi<T>(A, w >> 16, w & 0xffff, smem);
-    else phase_forward<T>(A, w >> 16, w & 0xffff, smem);
+    if constexpr (PHASE == 0) phase_backward<T>(A, A.radial[0][it], smem);
+    else if constexpr (PHASE == 1) phase_phi<T>(A, A.phi[it] >> 16, A.phi[it] & 0xffff, smem);
+    else phase_forward<T>(A, A.radial[1][it], smem);
   }
 }
 
-size_t smem_bytes(const mlg_batch_s* bt, int lines) {
-  size_t mx = 256 * sizeof(Cx<double>) + 512 * sizeof(double);
+// Radial phases with the recurrence Pbar_n^m = a_n x Pbar_{n-1}^m - b_n Pbar_{n-2}^m in registers: a block takes an order, its
+// wavefronts consecutive segments of RC_S degrees (the two values before each segment are kept per node), the
+// lanes of a wavefront NPL nodes each of one half (NPL = 2 above 64 half nodes).  a_n, b_n and the coefficients are the
+// same for the whole wavefront and come by scalar loads (pointers that do not alias, indices the compiler sees to be
+// uniform).  The entries n = m (0, 1) and n = m + 1 (sqrt(2 m + 3), 0) start the first segment from (-Pbar_m^m, 0).
+// A block per order whatever the launch shape asks: dealt to fewer blocks, an order waits for another's first loads.
+// 64 instances (N_r 48 .. 256, N_phi 32 .. 256): backward 33 us (a thread a node over both halves, coefficients from
+// LDS) -> 15; forward 42 us from the tables (256 MB at 6.1 TB/s) -> 23, of which the FP64 operations are about 5 and
+// 12 (8 of them the sums over the lanes), launch and first loads 6, the scalar loads 4 and 2.
+constexpr int RC_S = 32;  // degrees per segment
+constexpr int RC_B = 8;   // degrees per scalar load, backward
+constexpr int RC_F = 8;   // degrees per transposing sum, forward
+constexpr int RC_W = 2;   // wavefronts per order
+
+template <int NPL>
+struct Recurrence {
+  double x[NPL], p0[NPL], p1[NPL];
+  __device__ __forceinline__ void start(const double* __restrict__ tab, const RadialItem& I, int lane, int nh, int seg) {
+#pragma unroll
+    for (int j = 0; j < NPL; ++j) {
+      const int i = min(lane + 64 * j, nh - 1);
+      x[j] = tab[I.node + i];
+      p0[j] = tab[I.start + (2 * seg) * nh + i];
+      p1[j] = tab[I.start + (2 * seg + 1) * nh + i];
+    }
+  }
+  __device__ __forceinline__ void step(double a, double b) {
+#pragma unroll
+    for (int j = 0; j < NPL; ++j) {
+      const double p2 = (a * x[j]) * p1[j] - b * p0[j];
+      p0[j] = p1[j];
+      p1[j] = p2;
+    }
+  }
+};
+
+template <typename T, int NPL>
+__device__ __forceinline__ void recur_backward(const double* __restrict__ tab, const Cx<T>* __restrict__ spec,
+                                               Cx<T>* __restrict__ mix, const RadialItem& I, int wave) {
+  __shared__ Cx<double> part[(RC_W - 1) * 2 * 64 * NPL];  // [wave][parity][node] of the wavefronts after the first
+  constexpr int W = RC_W;
+  const int lane = threadIdx.x & 63, K = I.K, nr = I.nr, nh = (nr + 1) / 2;
+  const int segs = (K + RC_S - 1) / RC_S, seg = wave * segs / W;
+  const int end = min((wave + 1) * segs / W * RC_S, K);
+  const double* __restrict__ rec = tab + I.rec;
+  const Cx<T>* __restrict__ s = spec + I.spec;
+  int t = seg * RC_S;
+  Recurrence<NPL> r;
+  r.start(tab, I, lane, nh, min(seg, segs - 1));
+  double re[2][NPL], im[2][NPL];
+#pragma unroll
+  for (int j = 0; j < NPL; ++j) re[0][j] = re[1][j] = im[0][j] = im[1][j] = 0.0;
+  auto term = [&](int par, double a, double b, double sx, double sy) {
+    r.step(a, b);
+#pragma unroll
+    for (int j = 0; j < NPL; ++j) {
+      re[par][j] += sx * r.p1[j];
+      im[par][j] += sy * r.p1[j];
+    }
+  };
+  for (; t + RC_B <= end; t += RC_B) {
+    double ab[2 * RC_B];
+    Cx<T> v[RC_B];
+#pragma unroll
+    for (int u = 0; u < RC_B; ++u) {
+      ab[2 * u] = rec[2 * (t + u)];
+      ab[2 * u + 1] = rec[2 * (t + u) + 1];
+      v[u] = s[t + u];
+    }
+#pragma unroll
+    for (int u = 0; u < RC_B; ++u) term(u & 1, ab[2 * u], ab[2 * u + 1], (double)v[u].x, (double)v[u].y);
+  }
+  for (; t < end; t += 2) {
+    term(0, rec[2 * t], rec[2 * t + 1], (double)s[t].x, (double)s[t].y);
+    if (t + 1 < end) term(1, rec[2 * t + 2], rec[2 * t + 3], (double)s[t + 1].x, (double)s[t + 1].y);
+  }
+  if (wave > 0) {
+#pragma unroll
+    for (int par = 0; par < 2; ++par)
+#pragma unroll
+      for (int j = 0; j < NPL; ++j)
+        part[((wave - 1) * 2 + par) * 64 * NPL + lane + 64 * j] = Cx<double>{re[par][j], im[par][j]};
+  }
+  __syncthreads();
+  if (wave > 0) return;
+  Cx<T>* out = mix + I.mix;
+#pragma unroll
+  for (int j = 0; j < NPL; ++j) {
+    const int i = lane + 64 * j;
+    Cx<double> e{re[0][j], im[0][j]}, o{re[1][j], im[1][j]};
+#pragma unroll
+    for (int w = 0; w < W - 1; ++w) {
+      e = e + part[2 * w * 64 * NPL + i];
+      o = o + part[(2 * w + 1) * 64 * NPL + i];
+    }
+    if (i >= nh) continue;
+    out[i] = cx<T>((T)(e.x + o.x), (T)(e.y + o.y));
+    if (nr - 1 - i != i) out[nr - 1 - i] = cx<T>((T)(e.x - o.x), (T)(e.y - o.y));
+  }
+}
+
+// One step of the transposing sum over the lanes: of two values a lane keeps the one its bit names, summed with the
+// partner's (lane ^ 32, lane ^ 16: one swap instruction a register).
+template <int MASK>
+__device__ __forceinline__ double swap_sum(double a, double b) {
+  const int2 ua = __builtin_bit_cast(int2, a), ub = __builtin_bit_cast(int2, b);
+  if constexpr (MASK == 32) {
+    const auto lo = __builtin_amdgcn_permlane32_swap((unsigned)ua.x, (unsigned)ub.x, false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap((unsigned)ua.y, (unsigned)ub.y, false, false);
+    return __builtin_bit_cast(double, make_int2((int)lo[0], (int)hi[0])) +
+           __builtin_bit_cast(double, make_int2((int)lo[1], (int)hi[1]));
+  } else {
+    const auto lo = __builtin_amdgcn_permlane16_swap((unsigned)ua.x, (unsigned)ub.x, false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap((unsigned)ua.y, (unsigned)ub.y, false, false);
+    return __builtin_bit_cast(double, make_int2((int)lo[0], (int)hi[0])) +
+           __builtin_bit_cast(double, make_int2((int)lo[1], (int)hi[1]));
+  }
+}
+// value of the lane's partner: row mirror (lane ^ 15), half-row mirror (^ 7), quad reversal (^ 3), quad pairs (^ 1)
+template <int CTRL>
+__device__ __forceinline__ double dpp_partner(double a) {
+  const int2 u = __builtin_bit_cast(int2, a);
+  return __builtin_bit_cast(double, make_int2(__builtin_amdgcn_update_dpp(0, u.x, CTRL, 0xf, 0xf, false),
+                                              __builtin_amdgcn_update_dpp(0, u.y, CTRL, 0xf, 0xf, false)));
+}
+template <int CTRL>
+__device__ __forceinline__ double dpp_sum(double a, double b, bool bit) {
+  return (bit ? b : a) + dpp_partner<CTRL>(bit ? a : b);
+}
+
+template <typename T, int NPL>
+__device__ __forceinline__ void recur_forward(const double* __restrict__ tab, const Cx<T>* __restrict__ mix,
+                                              Cx<T>* __restrict__ spec, const RadialItem& I, int wave) {
+  constexpr int W = RC_W;
+  const int lane = threadIdx.x & 63, K = I.K, nr = I.nr, nh = (nr + 1) / 2;
+  const int segs = (K + RC_S - 1) / RC_S, seg = wave * segs / W;
+  const int end = min((wave + 1) * segs / W * RC_S, K);
+  if (seg * RC_S >= end) return;
+  const double* __restrict__ rec = tab + I.rec;
+  const Cx<T>* __restrict__ g = mix + I.mix;
+  Recurrence<NPL> r;
+  r.start(tab, I, lane, nh, seg);
+  double gx[2][NPL], gy[2][NPL];  // weighted sums and differences of mirrored nodes, 0 past the last node
+#pragma unroll
+  for (int j = 0; j < NPL; ++j) {
+    const int i = lane + 64 * j, ic = min(i, nh - 1);
+    const double w = i < nh ? tab[I.node + nh + ic] : 0.0;
+    const bool mid = nr - 1 - ic == ic;  // the middle node of an odd N_r stands alone
+    const Cx<T> a = g[ic], b = g[nr - 1 - ic];
+    const double bx = mid ? 0.0 : (double)b.x, by = mid ? 0.0 : (double)b.y;
+    gx[0][j] = w * ((double)a.x + bx);
+    gy[0][j] = w * ((double)a.y + by);
+    gx[1][j] = mid ? 0.0 : w * ((double)a.x - bx);
+    gy[1][j] = mid ? 0.0 : w * ((double)a.y - by);
+  }
+  const bool b3 = lane & 8, b2 = lane & 4;
+  T* out = reinterpret_cast<T*>(spec + I.spec);
+  for (int t0 = seg * RC_S; t0 < end; t0 += RC_F) {
+    // the terms past the column take the entries that follow in the table: their sums are not stored
+    double v[2 * RC_F];  // 2 d + (0 re, 1 im) of degree t0 + d
+#pragma unroll
+    for (int d = 0; d < RC_F; ++d) {
+      r.step(rec[2 * (t0 + d)], rec[2 * (t0 + d) + 1]);
+      v[2 * d] = r.p1[0] * gx[d & 1][0];
+      v[2 * d + 1] = r.p1[0] * gy[d & 1][0];
+#pragma unroll
+      for (int j = 1; j < NPL; ++j) {
+        v[2 * d] += r.p1[j] * gx[d & 1][j];
+        v[2 * d + 1] += r.p1[j] * gy[d & 1][j];
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < 8; ++q) v[q] = swap_sum<32>(v[q], v[q + 8]);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) v[q] = swap_sum<16>(v[q], v[q + 4]);
+#pragma unroll
+    for (int q = 0; q < 2; ++q) v[q] = dpp_sum<0x140>(v[q], v[q + 2], b3);
+    v[0] = dpp_sum<0x141>(v[0], v[1], b2);
+    v[0] += dpp_partner<0x1b>(v[0]);
+    v[0] += dpp_partner<0xb1>(v[0]);
+    if (!(lane & 3) && (lane >> 3) < end - t0) out[2 * t0 + (lane >> 2)] = (T)v[0];
+  }
+}
+
+template <typename T, bool FWD>
+__global__ __launch_bounds__(64 * RC_W) void batch_recur_kernel(const RadialItem* __restrict__ items,
+                                                                const double* __restrict__ tab,
+                                                                const Cx<T>* __restrict__ in, Cx<T>* __restrict__ out) {
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const RadialItem I = items[blockIdx.x];
+  if constexpr (FWD) {
+    if (I.nr == 0) {
+      for (int t = threadIdx.x; t < I.K; t += 64 * RC_W) out[I.spec + t] = cx<T>(0, 0);
+    } else if (I.nr <= 128) {
+      recur_forward<T, 1>(tab, in, out, I, wave);
+    } else {
+      recur_forward<T, 2>(tab, in, out, I, wave);
+    }
+  } else {
+    if (I.nr <= 128) recur_backward<T, 1>(tab, in, out, I, wave);
+    else recur_backward<T, 2>(tab, in, out, I, wave);
+  }
+}
+
+// LDS of a launch: the table phases hold the vector, then the partial sums of the subs; phase 2 two buffers of lines / 2
+// complex lines, then the twiddle table (nphi complex FP64).
+size_t radial_smem(const mlg_batch_s* bt, int threads) {
   const size_t cs = bt->prec == MLG_FP32 ? sizeof(Cx<float>) : sizeof(Cx<double>);
-  // phase 2: two buffers of lines / 2 complex lines, then the twiddle table (nphi complex FP64)
+  return std::max((size_t)BT_VEC, (size_t)threads / 64 * BT_DEG) * cs;
+}
+size_t phi_smem(const mlg_batch_s* bt, int lines) {
+  size_t mx = 0;
+  const size_t cs = bt->prec == MLG_FP32 ? sizeof(Cx<float>) : sizeof(Cx<double>);
   for (const auto& I : bt->inst)
     mx = std::max(mx, (size_t)2 * (lines / 2) * I.nphi * cs + (size_t)I.nphi * sizeof(Cx<double>));
   return mx;
+}
+
+// blocks of each phase: the configured count per CU, capped by what the kernel's registers and LDS allow
+template <typename T>
+void set_blocks(const mlg_batch_s* bt, BatchConfig& c) {
+  const void* k[3] = {reinterpret_cast<const void*>(batch_kernel<T, 0>), reinterpret_cast<const void*>(batch_kernel<T, 1>),
+                      reinterpret_cast<const void*>(batch_kernel<T, 2>)};
+  for (int p = 0; p < 3; ++p) {
+    int n = 0;
+    const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
+        &n, k[p], c.threads, p == 1 ? phi_smem(bt, c.lines) : radial_smem(bt, c.threads));
+    c.blocks[p] = e == hipSuccess && n > 0 ? std::min(n, c.blocks_per_cu) * bt->cus : 0;
+  }
+}
+void set_blocks(const mlg_batch_s* bt, BatchConfig& c) {
+  if (bt->prec == MLG_FP32) set_blocks<float>(bt, c);
+  else set_blocks<double>(bt, c);
 }
 
 template <typename T>
@@ -383,31 +668,24 @@ mlg_status run_batch(const mlg_batch_s* bt, double gamma, const void* in, void* 
     A.tabT = reinterpret_cast<const T*>(bt->d_tab);
   else
     A.tabT = reinterpret_cast<const T*>(bt->d_tab32);
-  A.tri = bt->d_tri;
   A.spec_in = reinterpret_cast<const Cx<T>*>(in);
   A.spec_out = reinterpret_cast<Cx<T>*>(out);
   A.mix = reinterpret_cast<Cx<T>*>(ws);
+  for (int p = 0; p < 2; ++p) A.radial[p] = bt->d_radial[p];
+  A.phi = bt->d_phi;
   for (int p = 0; p < 3; ++p) {
-    A.items[p] = bt->d_items[p];
     A.nitems[p] = bt->nitems[p];
+    if (c.blocks[p] <= 0) return fail(MLG_E_DEVICE, "batch kernel does not fit on a CU");
   }
-  A.recurrence = c.recurrence;
   A.lines = c.lines;
   A.gamma = (T)gamma;
-  const size_t shm = smem_bytes(bt, c.lines);
-  // blocks per CU: the configured count, capped by what the phase kernels' registers and LDS allow
-  int per_cu = 1 << 30;
-  for (const void* k : {reinterpret_cast<const void*>(batch_kernel<T, 0>), reinterpret_cast<const void*>(batch_kernel<T, 1>),
-                        reinterpret_cast<const void*>(batch_kernel<T, 2>)}) {
-    int n = 0;
-    const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k, c.threads, shm);
-    if (e != hipSuccess || n <= 0) return fail(MLG_E_DEVICE, "batch kernel does not fit on a CU");
-    per_cu = std::min(per_cu, n);
-  }
-  const int blocks = std::max(1, std::min(per_cu, c.blocks_per_cu) * bt->cus);
-  batch_kernel<T, 0><<<dim3(blocks), dim3(c.threads), shm, s>>>(A);
-  batch_kernel<T, 1><<<dim3(blocks), dim3(c.threads), shm, s>>>(A);
-  batch_kernel<T, 2><<<dim3(blocks), dim3(c.threads), shm, s>>>(A);
+  const size_t rad = radial_smem(bt, c.threads);
+  const unsigned th = (unsigned)c.threads;
+  if (c.recurrence) batch_recur_kernel<T, false><<<A.nitems[0], 64 * RC_W, 0, s>>>(A.radial[0], A.tab, A.spec_in, A.mix);
+  else batch_kernel<T, 0><<<c.blocks[0], th, rad, s>>>(A);
+  batch_kernel<T, 1><<<c.blocks[1], th, phi_smem(bt, c.lines), s>>>(A);
+  if (c.recurrence) batch_recur_kernel<T, true><<<A.nitems[2], 64 * RC_W, 0, s>>>(A.radial[1], A.tab, A.mix, A.spec_out);
+  else batch_kernel<T, 2><<<c.blocks[2], th, rad, s>>>(A);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return fail(MLG_E_DEVICE, std::string("batch kernel launch: ") + hipGetErrorString(e));
   return MLG_OK;
@@ -423,7 +701,8 @@ mlg_status batch_run(const mlg_batch_s* bt, double gamma, const void* in, void* 
   return run_batch<double>(bt, gamma, in, out, ws, s, c);
 }
 
-size_t batch_smem(const mlg_batch_s* bt, int lines) { return smem_bytes(bt, lines); }
+// the largest launch at the largest block
+size_t batch_smem(const mlg_batch_s* bt, int lines) { return std::max(phi_smem(bt, lines), radial_smem(bt, 256)); }
 
 }  // namespace mlg
 
@@ -445,36 +724,59 @@ mlg_status up(V** dst, const std::vector<typename std::remove_pointer<V*>::type>
 
 void free_batch(mlg_batch_s* b) {
   if (!b) return;
-  void* ptrs[] = {b->d_inst, b->d_tab, b->d_tab32, b->d_tri, b->d_items[0], b->d_items[1], b->d_items[2]};
+  void* ptrs[] = {b->d_inst, b->d_tab, b->d_tab32, b->d_radial[0], b->d_radial[1], b->d_phi};
   for (void* q : ptrs)
     if (q) (void)hipFree(q);
   delete b;
 }
 
+// values per node of the recurrence states of a column of K degrees
+int64_t rec_states(int K) { return 2 * ((std::max(K, 0) + RC_S - 1) / RC_S); }
+
 // Work lists sorted by estimated cost, largest first.
-mlg_status build_items(mlg_batch_s* bt, int lines) {
-  struct W { double cost; int32_t code; };
-  std::vector<W> w[3];
+mlg_status build_radial(mlg_batch_s* bt, const std::vector<int64_t>& tri) {
+  std::vector<RadialItem> w[2];
+  const int64_t* off = tri.data();
   for (int b = 0; b < bt->count; ++b) {
     const BatchInst& I = bt->inst[b];
-    for (int m = 0; m < I.M; ++m) {
-      const int K = std::max(I.nrc - m, 0);
-      w[0].push_back({(m > I.mkeep ? 1.0 : (double)std::max(K, 1) * I.nr), (b << 16) | m});
-      w[2].push_back({(m > I.mkeep ? 1.0 : (double)std::max(K, 1) * I.nr), (b << 16) | m});
+    const int nh = (I.nr + 1) / 2;
+    int64_t start = I.start_off;
+    for (int m = 0; m < I.mact; start += rec_states(I.nrc - m) * nh, ++m) {
+      RadialItem it{I.spec_off + off[m], I.mix_off + (int64_t)m * I.nr, I.tb_off + off[m] * nh, I.rec_off + 2 * off[m],
+                    start, I.node_off, I.nr, I.nrc - m, m, 0};
+      w[0].push_back(it);
+      it.tab = I.tf_off + off[m] * nh;
+      w[1].push_back(it);
     }
+    if (off[I.M] > off[I.mact])
+      w[1].push_back(RadialItem{I.spec_off + off[I.mact], 0, 0, 0, 0, 0, 0, (int)(off[I.M] - off[I.mact]), 0, 0});
+    off += I.M + 1;
+  }
+  for (int p = 0; p < 2; ++p) {
+    std::stable_sort(w[p].begin(), w[p].end(), [](const RadialItem& a, const RadialItem& c) {
+      return (int64_t)a.K * a.nr > (int64_t)c.K * c.nr;
+    });
+    if (mlg_status st = up(&bt->d_radial[p], w[p])) return st;
+    bt->nitems[2 * p] = (int)w[p].size();
+  }
+  return MLG_OK;
+}
+
+mlg_status build_phi(mlg_batch_s* bt, int lines) {
+  struct W { double cost; int32_t code; };
+  std::vector<W> w;
+  for (int b = 0; b < bt->count; ++b) {
+    const BatchInst& I = bt->inst[b];
     for (int q = 0; q < I.nr; q += lines)
-      w[1].push_back({(double)lines * I.nphi * std::log2((double)I.nphi + 1.0), (b << 16) | q});
+      w.push_back({(double)lines * I.nphi * std::log2((double)I.nphi + 1.0), (b << 16) | q});
   }
-  for (int p = 0; p < 3; ++p) {
-    std::stable_sort(w[p].begin(), w[p].end(), [](const W& a, const W& c) { return a.cost > c.cost; });
-    std::vector<int32_t> codes(w[p].size());
-    for (size_t i = 0; i < w[p].size(); ++i) codes[i] = w[p][i].code;
-    if (bt->d_items[p]) (void)hipFree(bt->d_items[p]);
-    bt->d_items[p] = nullptr;
-    if (mlg_status st = up(&bt->d_items[p], codes)) return st;
-    bt->nitems[p] = (int)codes.size();
-    bt->items_host[p] = codes;
-  }
+  std::stable_sort(w.begin(), w.end(), [](const W& a, const W& c) { return a.cost > c.cost; });
+  std::vector<int32_t> codes(w.size());
+  for (size_t i = 0; i < w.size(); ++i) codes[i] = w[i].code;
+  if (bt->d_phi) (void)hipFree(bt->d_phi);
+  bt->d_phi = nullptr;
+  if (mlg_status st = up(&bt->d_phi, codes)) return st;
+  bt->nitems[1] = (int)codes.size();
   return MLG_OK;
 }
 
@@ -527,10 +829,10 @@ mlg_status mlg_batch_create(int count, const mlg_grid* grids, mlg_precision prec
     I.nphi = g.nphi;
     I.nrc = g.nrc ? g.nrc : g.nr;
     I.M = g.nphic ? g.nphic : g.nphi / 2;
-    I.mkeep = g.dealias ? (g.nphi - 1) / 3 : (1 << 30);
     I.nrad = factor_radices(g.nphi, I.rad);
-    const int nr = I.nr, nrc = I.nrc, M = I.M;
-    I.tri_off = (int64_t)tri.size();
+    const int nr = I.nr, nrc = I.nrc, M = I.M, nh = (nr + 1) / 2;
+    I.mact = std::min({M, nrc, (g.nphi + 1) / 2, g.dealias ? (g.nphi - 1) / 3 + 1 : M});
+    const size_t tri0 = tri.size();
     int64_t t = 0;
     for (int m = 0; m < M; ++m) {
       tri.push_back(t);
@@ -545,35 +847,46 @@ mlg_status mlg_batch_create(int count, const mlg_grid* grids, mlg_precision prec
     std::vector<long double> th, wl;
     gl_theta(nr, th, wl);
     I.tb_off = (int64_t)tab.size();
-    tab.resize(tab.size() + tau * nr);
+    tab.resize(tab.size() + tau * nh);
     I.tf_off = (int64_t)tab.size();
-    tab.resize(tab.size() + tau * nr);
+    tab.resize(tab.size() + tau * nh);
     I.rec_off = (int64_t)tab.size();
     tab.resize(tab.size() + 2 * tau);
     I.start_off = (int64_t)tab.size();
-    tab.resize(tab.size() + (int64_t)M * nr);
+    int64_t states = 0;
+    for (int m = 0; m < M; ++m) states += rec_states(nrc - m);
+    tab.resize(tab.size() + states * nh);
     I.node_off = (int64_t)tab.size();
-    tab.resize(tab.size() + nr);
+    tab.resize(tab.size() + 2 * nh);
     I.tw_off = (int64_t)tab.size();
     tab.resize(tab.size() + 2 * g.nphi);
     std::vector<long double> col(nrc + 2);
-    for (int i = 0; i < nr; ++i) tab[I.node_off + i] = (double)cosl(th[i]);
+    int64_t start = I.start_off;
+    for (int i = 0; i < nh; ++i) {
+      tab[I.node_off + i] = (double)cosl(th[i]);
+      tab[I.node_off + nh + i] = (double)wl[i];
+    }
     for (int m = 0; m < M; ++m) {
       const int K = std::max(nrc - m, 0);
       if (K == 0) continue;
-      const int64_t tr = tri[I.tri_off + m];
-      for (int i = 0; i < nr; ++i) {
+      const int64_t tr = tri[tri0 + m];
+      for (int i = 0; i < nh; ++i) {
         pbar_col(m, nrc, th[i], col.data());
-        tab[I.start_off + (int64_t)m * nr + i] = (double)col[0];
+        for (int t = 0; t < K; t += RC_S) {
+          double* p = &tab[start + 2 * (t / RC_S) * nh + i];
+          p[0] = t ? (double)col[t - 2] : -(double)col[0];
+          p[nh] = t ? (double)col[t - 1] : 0.0;
+        }
         for (int n = m; n < nrc; ++n) {
-          tab[I.tb_off + (tr + n - m) * nr + i] = (double)col[n - m];
-          tab[I.tf_off + tr * nr + (int64_t)i * K + (n - m)] = (double)(wl[i] * col[n - m]);
+          tab[I.tb_off + (tr + n - m) * nh + i] = (double)col[n - m];
+          tab[I.tf_off + tr * nh + (int64_t)i * K + (n - m)] = (double)(wl[i] * col[n - m]);
         }
       }
+      start += rec_states(K) * nh;
       for (int n = m; n < nrc; ++n) {
-        ld a = 0, c = 0;
+        ld a = 0, c = n == m ? 1 : 0;
+        if (n > m) a = sqrtl((ld)(4 * n * n - 1) / (ld)(n * n - m * m));
         if (n >= m + 2) {
-          a = sqrtl((ld)(4 * n * n - 1) / (ld)(n * n - m * m));
           c = sqrtl((ld)((2 * n + 1) * (n - 1 - m) * (n - 1 + m)) / (ld)((2 * n - 3) * (n * n - m * m)));
         }
         tab[I.rec_off + 2 * (tr + n - m)] = (double)a;
@@ -587,11 +900,12 @@ mlg_status mlg_batch_create(int count, const mlg_grid* grids, mlg_precision prec
     }
     bt->inst.push_back(I);
   }
+  tab.resize(tab.size() + 2 * RC_F);  // read past the last column's recurrence
   bt->spec_total = bt->spec_offsets[count];
   bt->mix_total = mix;
   bt->ws_bytes = (size_t)mix * (prec == MLG_FP32 ? 8 : 16) + 256;
   mlg_status st;
-  if ((st = up(&bt->d_inst, bt->inst)) || (st = up(&bt->d_tab, tab)) || (st = up(&bt->d_tri, tri))) {
+  if ((st = up(&bt->d_inst, bt->inst)) || (st = up(&bt->d_tab, tab)) || (st = build_radial(bt, tri))) {
     free_batch(bt);
     if (prev >= 0) (void)hipSetDevice(prev);
     return st;
@@ -604,11 +918,12 @@ mlg_status mlg_batch_create(int count, const mlg_grid* grids, mlg_precision prec
       return st;
     }
   }
-  if ((st = build_items(bt, bt->cfg.lines))) {
+  if ((st = build_phi(bt, bt->cfg.lines))) {
     free_batch(bt);
     if (prev >= 0) (void)hipSetDevice(prev);
     return st;
   }
+  set_blocks(bt, bt->cfg);
   if (prev >= 0) (void)hipSetDevice(prev);
   *out = bt;
   return MLG_OK;
@@ -648,15 +963,14 @@ mlg_status mlg_batch_set_config(mlg_batch b, const mlg_batch_config* c) {
     return fail(MLG_E_ARG, "invalid batch configuration");
   const size_t shm = batch_smem(b, c->lines);
   if (shm > 65536) return fail(MLG_E_ARG, "configuration needs more than 64 KiB of LDS");
-  BatchConfig nc{c->recurrence, c->threads, c->blocks_per_cu, c->lines};
-  if (nc.lines != b->cfg.lines) {
-    int prev = -1;
-    (void)hipGetDevice(&prev);
-    (void)hipSetDevice(b->device);
-    mlg_status st = build_items(b, nc.lines);
-    if (prev >= 0) (void)hipSetDevice(prev);
-    if (st) return st;
-  }
+  BatchConfig nc{c->recurrence, c->threads, c->blocks_per_cu, c->lines, {0, 0, 0}};
+  int prev = -1;
+  (void)hipGetDevice(&prev);
+  (void)hipSetDevice(b->device);
+  const mlg_status st = nc.lines != b->cfg.lines ? build_phi(b, nc.lines) : MLG_OK;
+  set_blocks(b, nc);
+  if (prev >= 0) (void)hipSetDevice(prev);
+  if (st) return st;
   b->cfg = nc;
   return MLG_OK;
 }
@@ -689,11 +1003,12 @@ mlg_status mlg_batch_autotune(mlg_batch b, double gamma, const void* spec_in, vo
   mlg_status st = MLG_OK;
   for (int lines : lines_c) {
     if (batch_smem(b, lines) > 65536) continue;
-    if ((st = build_items(b, lines))) break;
+    if ((st = build_phi(b, lines))) break;
     for (int rec = 0; rec < 2; ++rec)
       for (int thr : thr_c)
         for (int bpc : bpc_c) {
-          BatchConfig c{rec, thr, bpc, lines};
+          BatchConfig c{rec, thr, bpc, lines, {0, 0, 0}};
+          set_blocks(b, c);
           if ((st = batch_run(b, gamma, spec_in, spec_out, ws, s, c))) break;  // warm-up
           (void)hipEventRecord(e0, s);
           for (int r = 0; r < 3; ++r)
@@ -713,7 +1028,7 @@ mlg_status mlg_batch_autotune(mlg_batch b, double gamma, const void* spec_in, vo
   }
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
-  if (st == MLG_OK) st = build_items(b, best.lines);
+  if (st == MLG_OK) st = build_phi(b, best.lines);
   if (st == MLG_OK) {
     b->cfg = best;
     b->tuned = 1;
