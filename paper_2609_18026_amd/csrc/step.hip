@@ -83,11 +83,17 @@ __device__ __forceinline__ double denom(const StepArgs& a, double mu) {
   return 1.0 + a.h * (a.nu * mu + a.nuh * pw);
 }
 
+// column of an LDS row of a stage: neighbouring rows, which a wavefront reads together, use the two halves of the banks
+__device__ __forceinline__ int swz(int row, int col) { return col ^ ((row & 1) << 4); }
+
 // Z = V^{-1} [s | a] per m, then W = Phi Zs + Psi Za (and the m = 0 divided differences).  Both
 // potentials go in one launch, the tiles of an order on one XCD (they share its tables), and a
 // wavefront whose rows lie past the order's last leaves the products out.  Ten steps at 128 (96) x 64 x 32, where
 // one field has 128 blocks for the 256 CUs: 1.40 -> 1.14 ms, the n = 0 row taken along by the second launch.
+// FE-BE (MODE 0) has Phi = 1 / D and Psi = h / D, so it needs one product, of s + h a.
+template <int MODE>
 __global__ __launch_bounds__(256) void step_fwd_kernel(StepArgs a) {
+  constexpr int NP = MODE == 1 ? 2 : 1;  // products
   Tile3 tl;
   if (!xcd_tile(a.gx, a.gy * a.nf, a.gz, tl)) return;
   const bool second = tl.y >= a.gy;
@@ -104,20 +110,18 @@ __global__ __launch_bounds__(256) void step_fwd_kernel(StepArgs a) {
   const int64_t rb = (a.off[m] + n0) * nz;
   const double2* __restrict__ s = fd.s + rb;
   const double2* __restrict__ p1 = fd.a1 + rb;
-  const double2* __restrict__ p0 = fd.a0 ? fd.a0 + rb : nullptr;
+  const double2* __restrict__ p0 = MODE == 1 ? fd.a0 + rb : nullptr;
   __shared__ double As[2][TK][TM];
-  __shared__ double Bs[2][2][TK][2 * TC];
+  __shared__ double Bs[2][NP][TK][2 * TC];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  double4_t acc[2][2];
+  double4_t acc[NP][2];
 #pragma unroll
-  for (int p = 0; p < 2; ++p) acc[p][0] = acc[p][1] = double4_t{0.0, 0.0, 0.0, 0.0};
+  for (int p = 0; p < NP; ++p) acc[p][0] = acc[p][1] = double4_t{0.0, 0.0, 0.0, 0.0};
   // raw loads with indices clamped into the operands (no branch around a load); the AB-CN
   // combination 3 A1 - A0 and the zeros outside the operands are formed at the LDS store, so the
   // loads of the next stage stay in flight across this stage's MFMAs
   double ra[4];
   double2 rs, r1, r0v;
-  const double2* __restrict__ q0 = p0 ? p0 : p1;
-  const double c1 = p0 ? 3.0 : 1.0, c0 = p0 ? 1.0 : 0.0;
   auto load = [&](int k0) {
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
@@ -133,22 +137,26 @@ __global__ __launch_bounds__(256) void step_fwd_kernel(StepArgs a) {
     const int64_t i = (int64_t)kc * nz + kkc;
     rs = s[i];
     r1 = p1[i];
-    r0v = q0[i];
+    if constexpr (MODE == 1) r0v = p0[i];
   };
   auto store = [&](int buf, int k0) {
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
       const int e = tid + 256 * t;
       const bool ok = k0 + (e >> 6) < K && j0 + (e & 63) < K;
-      As[buf][e >> 6][e & 63] = ok ? ra[t] : 0.0;
+      As[buf][e >> 6][swz(e >> 6, e & 63)] = ok ? ra[t] : 0.0;
     }
     const int kr = tid >> 4, cc = tid & 15;
     const bool ok = k0 + kr < K && kk0 + cc < nz;
-    const double2 v = make_double2(c1 * r1.x - c0 * r0v.x, c1 * r1.y - c0 * r0v.y);
-    Bs[buf][0][kr][cc] = ok ? rs.x : 0.0;
-    Bs[buf][0][kr][TC + cc] = ok ? rs.y : 0.0;
-    Bs[buf][1][kr][cc] = ok ? v.x : 0.0;
-    Bs[buf][1][kr][TC + cc] = ok ? v.y : 0.0;
+    if constexpr (MODE == 1) {
+      Bs[buf][0][kr][swz(kr, cc)] = ok ? rs.x : 0.0;
+      Bs[buf][0][kr][swz(kr, TC + cc)] = ok ? rs.y : 0.0;
+      Bs[buf][NP - 1][kr][swz(kr, cc)] = ok ? 3.0 * r1.x - r0v.x : 0.0;
+      Bs[buf][NP - 1][kr][swz(kr, TC + cc)] = ok ? 3.0 * r1.y - r0v.y : 0.0;
+    } else {
+      Bs[buf][0][kr][swz(kr, cc)] = ok ? rs.x + a.h * r1.x : 0.0;
+      Bs[buf][0][kr][swz(kr, TC + cc)] = ok ? rs.y + a.h * r1.y : 0.0;
+    }
   };
   const int nk = (K + TK - 1) / TK;
   const bool rows_in = j0 + wave * 16 < K;
@@ -162,11 +170,13 @@ __global__ __launch_bounds__(256) void step_fwd_kernel(StepArgs a) {
     for (int ks = 0; ks < TK; ks += 4) {
       if (!rows_in) break;
       const int kr = ks + (lane >> 4);
-      const double av = As[buf][kr][wave * 16 + (lane & 15)];
-      acc[0][0] = MFMA(av, Bs[buf][0][kr][lane & 15], acc[0][0]);
-      acc[0][1] = MFMA(av, Bs[buf][0][kr][TC + (lane & 15)], acc[0][1]);
-      acc[1][0] = MFMA(av, Bs[buf][1][kr][lane & 15], acc[1][0]);
-      acc[1][1] = MFMA(av, Bs[buf][1][kr][TC + (lane & 15)], acc[1][1]);
+      const double av = As[buf][kr][swz(kr, wave * 16 + (lane & 15))];
+      acc[0][0] = MFMA(av, Bs[buf][0][kr][swz(kr, lane & 15)], acc[0][0]);
+      acc[0][1] = MFMA(av, Bs[buf][0][kr][swz(kr, TC + (lane & 15))], acc[0][1]);
+      if constexpr (MODE == 1) {
+        acc[NP - 1][0] = MFMA(av, Bs[buf][NP - 1][kr][swz(kr, lane & 15)], acc[NP - 1][0]);
+        acc[NP - 1][1] = MFMA(av, Bs[buf][NP - 1][kr][swz(kr, TC + (lane & 15))], acc[NP - 1][1]);
+      }
     }
     if (kt + 1 < nk) store(buf ^ 1, (kt + 1) * TK);
     __syncthreads();
@@ -184,10 +194,15 @@ __global__ __launch_bounds__(256) void step_fwd_kernel(StepArgs a) {
     const double lj = lam[j];
     const double mu = lj + alpha;
     const double D = denom(a, mu);
-    const double psi = a.h / D;
-    const double phi = a.mode == 1 ? 2.0 / D - 1.0 : 1.0 / D;
-    const double zsr = acc[0][0][v], zsi = acc[0][1][v], zar = acc[1][0][v], zai = acc[1][1][v];
-    fd.W[rb + (int64_t)j * nz + kk] = make_double2(phi * zsr + psi * zar, phi * zsi + psi * zai);
+    const double zsr = acc[0][0][v], zsi = acc[0][1][v];
+    double zar = 0.0, zai = 0.0;
+    if constexpr (MODE == 1) {
+      zar = acc[NP - 1][0][v];
+      zai = acc[NP - 1][1][v];
+    }
+    const double psi = a.h / D, phi = MODE == 1 ? 2.0 / D - 1.0 : 1.0 / D;
+    fd.W[rb + (int64_t)j * nz + kk] =
+        MODE == 1 ? make_double2(phi * zsr + psi * zar, phi * zsi + psi * zai) : make_double2(phi * zsr, phi * zsi);
     if (m == 0) {
       // (f(mu) - f(alpha)) / lam in closed form: L(mu) - L(alpha) = lam * dl
       double sum = 0.0, mp = 1.0;
@@ -199,9 +214,10 @@ __global__ __launch_bounds__(256) void step_fwd_kernel(StepArgs a) {
       }
       const double dl = -a.nu - a.nuh * sum;
       const double inv = a.h * dl / (D * Da);
-      const double dphi = (a.mode == 1 ? 2.0 : 1.0) * inv;
+      const double dphi = (MODE == 1 ? 2.0 : 1.0) * inv;
       const double dpsi = a.h * inv;
-      fd.W0[(int64_t)j * nz + kk] = make_double2(dphi * zsr + dpsi * zar, dphi * zsi + dpsi * zai);
+      fd.W0[(int64_t)j * nz + kk] =
+          MODE == 1 ? make_double2(dphi * zsr + dpsi * zar, dphi * zsi + dpsi * zai) : make_double2(dphi * zsr, dphi * zsi);
     }
   }
 }
@@ -300,12 +316,12 @@ __global__ __launch_bounds__(256) void step_bwd_kernel(StepArgs a) {
     for (int t = 0; t < 4; ++t) {
       const int e = tid + 256 * t;
       const bool ok = k0 + (e >> 6) < K && r0 + (e & 63) < K;
-      As[buf][e >> 6][e & 63] = ok ? ra[t] : 0.0;
+      As[buf][e >> 6][swz(e >> 6, e & 63)] = ok ? ra[t] : 0.0;
     }
     const int kr = tid >> 4, cc = tid & 15;
     const bool ok = k0 + kr < K && kk0 + cc < nz;
-    Bs[buf][kr][cc] = ok ? rbv.x : 0.0;
-    Bs[buf][kr][TC + cc] = ok ? rbv.y : 0.0;
+    Bs[buf][kr][swz(kr, cc)] = ok ? rbv.x : 0.0;
+    Bs[buf][kr][swz(kr, TC + cc)] = ok ? rbv.y : 0.0;
   };
   const int nk = (K + TK - 1) / TK;
   const bool rows_in = r0 + wave * 16 < K;
@@ -319,9 +335,9 @@ __global__ __launch_bounds__(256) void step_bwd_kernel(StepArgs a) {
     for (int ks = 0; ks < TK; ks += 4) {
       if (!rows_in) break;
       const int kr = ks + (lane >> 4);
-      const double av = As[buf][kr][wave * 16 + (lane & 15)];
-      acc[0] = MFMA(av, Bs[buf][kr][lane & 15], acc[0]);
-      acc[1] = MFMA(av, Bs[buf][kr][TC + (lane & 15)], acc[1]);
+      const double av = As[buf][kr][swz(kr, wave * 16 + (lane & 15))];
+      acc[0] = MFMA(av, Bs[buf][kr][swz(kr, lane & 15)], acc[0]);
+      acc[1] = MFMA(av, Bs[buf][kr][swz(kr, TC + (lane & 15))], acc[1]);
     }
     if (kt + 1 < nk) store(buf ^ 1, (kt + 1) * TK);
     __syncthreads();
@@ -768,7 +784,8 @@ mlg_status launch_steps(const mlg_plan_s* p, int nf, int mode, int which, const 
   a.gz = std::min(p->M, p->nrc);
   a.nrow0 = (nf * ((p->nz + R0C - 1) / R0C) + 7) / 8 * 8;
   const unsigned tiles = p->step_maxk > 0 ? xcd_blocks(a.gx, a.gy * nf, a.gz) : 0;  // none: the n = 0 row alone
-  if (tiles) step_fwd_kernel<<<tiles, 256, 0, st>>>(a);
+  if (tiles && mode == 1) step_fwd_kernel<1><<<tiles, 256, 0, st>>>(a);
+  else if (tiles) step_fwd_kernel<0><<<tiles, 256, 0, st>>>(a);
   step_bwd_kernel<<<a.nrow0 + tiles, 256, 0, st>>>(a);
   p->timing.end(st);
   hipError_t e = hipGetLastError();
