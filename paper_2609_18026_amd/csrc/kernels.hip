@@ -6,6 +6,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstdint>
+#include <type_traits>
 
 #include "dev_common.h"
 #include "mlg_internal.h"
@@ -1407,7 +1408,23 @@ mlg_status launch_projection(const mlg_plan_s* p, const double* const* src3, dou
       else projection_kernel<true, 8, double2><<<grid, PS_SEG * PS_COL, shm, s>>>(a);
     } else {
       if (wide) projection_kernel<false, 16, double2><<<grid, PS_SEG * PS_COL, shm, s>>>(a);
-      else projection_kernel<false, 8, double2><<<grid, PS_SEG * PS_COL, shm, s>>>(a);
+      // FP64 without taps: the shortest run that holds a column (rows past a run's last are loaded all the same and
+      // cost registers).  With runs of 8 or 16 only: 37 -> 27 us at 128^3 (runs of 4, 4 waves per SIMD), 17.8 -> 14.5 at
+      // 96 rows x 64 x 32 (3), 52 -> 42 at 200 x 128 x 128 (7: 516 blocks for 768 places, not 512)
+      else {
+        auto run = [&](auto n) {
+          projection_kernel<false, decltype(n)::value, double2><<<grid, PS_SEG * PS_COL, shm, s>>>(a);
+        };
+        switch ((p->nrc - 2 + PS_SEG) / PS_SEG) {  // rows of the longest run
+          case 0: case 1: case 2: run(std::integral_constant<int, 2>()); break;
+          case 3: run(std::integral_constant<int, 3>()); break;
+          case 4: run(std::integral_constant<int, 4>()); break;
+          case 5: run(std::integral_constant<int, 5>()); break;
+          case 6: run(std::integral_constant<int, 6>()); break;
+          case 7: run(std::integral_constant<int, 7>()); break;
+          default: run(std::integral_constant<int, 8>());
+        }
+      }
     }
     p->timing.end(s);
   }
