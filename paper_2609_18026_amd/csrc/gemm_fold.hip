@@ -246,10 +246,13 @@ struct FoldProjArgs {
 // past the column and of inactive columns are computed but not stored.  Fields are float2 on
 // reduced-precision plans (converted after the load has landed).
 typedef double PairLd __attribute__((ext_vector_type(2), aligned(8)));  // two adjacent table entries
-constexpr int PROJ_RG = 2;  // row groups of 16 pairs per wavefront
+// Up to PROJ_RG1 pairs the grid, not the loads per MFMA, is what is short (946 wavefronts of 32 pairs for 1024 SIMDs at
+// 128^3): one group per wavefront, two k-steps ahead.  16.3 -> 13.2 us at 96 kept rows x 64 x 32, 35 -> 26.4 at 128^3,
+// 62.5 -> 59.4 at 200 x 128 x 128; at 256^3 it is 245 against 221 us.
+constexpr int PROJ_RG1 = 100;
 
 template <typename C2, int D, int RG>
-__global__ __launch_bounds__(256, RG == 1 ? 4 : 2) void proj_fold_kernel(FoldProjArgs<C2> a) {
+__global__ __launch_bounds__(256, 2) void proj_fold_kernel(FoldProjArgs<C2> a) {
   typedef double R;
   typedef decltype(C2().x) S;  // storage real type of the fields
   Tile3 tl;
@@ -727,10 +730,12 @@ static void proj_fold_go(const mlg_plan_s* p, double* const* in3, double* const*
   a.cb = col_blocks(kmax, p->nz);
   a.kap0 = 2.0 * M_PI / p->g.lz;
   const int kp = (p->nrc + 1) / 2;
+  const int rg = kp > PROJ_RG1 ? 2 : 1;
   a.gx = a.cb.nblk;
-  a.gy = (kp + TM * PROJ_RG - 1) / (TM * PROJ_RG);
+  a.gy = (kp + TM * rg - 1) / (TM * rg);
   a.gz = mmax;
-  proj_fold_kernel<C2, 1, PROJ_RG><<<dim3(xcd_blocks(a.gx, a.gy, a.gz)), 256, 0, s>>>(a);
+  if (rg == 2) proj_fold_kernel<C2, 1, 2><<<dim3(xcd_blocks(a.gx, a.gy, a.gz)), 256, 0, s>>>(a);
+  else proj_fold_kernel<C2, 2, 1><<<dim3(xcd_blocks(a.gx, a.gy, a.gz)), 256, 0, s>>>(a);
 }
 
 // in3: harmonics of N (float2 on reduced-precision plans); out3: FP64 sources in every case
