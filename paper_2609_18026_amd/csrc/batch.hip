@@ -1,13 +1,14 @@
 // Batched pseudospectral KPP term for many uneven 2D instances.
 //
 // For each instance b (N_z = 1): R_b = Mask(F(gamma u (1 - u))), u = B(Mask(u_hat_b)) (Sec. 3.3;
-// Sec. 5.2, Eq. kpp; the two-thirds mask holds for the field entering the product too).  Three persistent launches (a fixed number of blocks per CU, each block
-// walking its share of the phase's work list) run the phases; the kernel boundaries order them
-// (a grid-wide barrier inside one cooperative launch costs about 50 us on this part, against a few
-// microseconds for a launch boundary):
+// Sec. 5.2, Eq. kpp; the two-thirds mask holds for the field entering the product too).  Three launches run
+// the phases; the kernel boundaries order them (a grid-wide barrier inside one cooperative launch costs about 50 us on
+// this part, against a few microseconds for a launch boundary).  The azimuthal phase, and the radial phases with tables, are
+// persistent (a fixed number of blocks per CU, each walking its share of the phase's work list); with the
+// recurrence the radial phases take a block per order:
 //   1. backward radial transform per (instance, kept m): f_m(r_i) = sum_n Pbar_n^m(x_i) u_hat_n^m;
-//      Pbar either streamed from per-instance tables or regenerated in the kernel by the
-//      normalised three-term recurrence (FP64) from Pbar_m^m(x_i);
+//      Pbar streamed from per-instance tables or regenerated in the kernel (phases 1 and 3) by the
+//      normalised three-term recurrence (FP64) from states kept every 32 degrees;
 //   2. per (instance, group of azimuthal lines): inverse real FFT in phi, gamma u (1 - u),
 //      forward FFT, two-thirds mask;
 //   3. forward radial projection per (instance, kept m): u_hat_n^m = sum_i w_i Pbar_n^m(x_i) g_m(r_i);
@@ -19,7 +20,6 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
-#include <chrono>
 #include <cmath>
 #include <cstdint>
 #include <cstdio>

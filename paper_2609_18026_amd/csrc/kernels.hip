@@ -1012,7 +1012,7 @@ __global__ __launch_bounds__(PS_SEG * PS_COL, SMAX <= 8 ? 2 : 1) void projection
 // Stage 1: a block sums its rows of every slot into part[0][kk][block] (the order m = 0) and part[1][kk][block]
 // (m >= 1); its threads are EN_T / cols row groups of cols slots.  Stage 2: a block per slot adds the parts of m = 0, of
 // kk and of -kk.  Reading each slot with its partner in stage 1, 64 rows a block with one thread a slot, took 52 us and the
-// sum of the parts by one thread a slot 48 us at N_r = 200 (192 kept), N_phi = N_z = 128.
+// sum of the parts by one thread a slot 48 us at N_r = 200, N_phi = N_z = 128; now 16.8 and 4.7.
 constexpr int EN_T = 256;
 constexpr int EN_ROWS = 64;   // rows per part that the scratch has to hold
 
