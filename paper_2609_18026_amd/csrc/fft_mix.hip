@@ -23,26 +23,9 @@ namespace {
 
 using namespace ::mlg::dev;
 
-// v[c] *= w_n^(e c), c = 1 .. R - 1, w_n = exp(-2 pi i / n) (conjugated for the inverse), e R <= n: the
-// powers 1, 2, 4, 8 come from the table, every other factor is a product of at most four of them
-template <int R, bool INV>
-__device__ __forceinline__ void twiddle(double2 (&v)[R], const double2* __restrict__ tw, int e) {
-  double2 w[R];
-#pragma unroll
-  for (int c = 1; c < R; ++c) {
-    const int top = c >= 8 ? 8 : (c >= 4 ? 4 : (c >= 2 ? 2 : 1));
-    if (c == top) {
-      w[c] = tw[c * e];
-      if (INV) w[c] = cconj(w[c]);
-    } else {
-      w[c] = cmul(w[top], w[c - top]);
-    }
-    v[c] = cmul(v[c], w[c]);
-  }
-}
-
-// the same with every factor from the table (c e < n): for stages whose lanes run over the lines first, where
-// a table read is a broadcast and the products' registers cost more
+// v[c] *= w_n^(e c), c = 1 .. R - 1, w_n = exp(-2 pi i / n) (conjugated for the inverse), c e < n.  Every factor comes from
+// the table: factors formed as products of the powers 1, 2, 4, 8 left up to 15% more rounding error in a transform (root mean
+// square over white lines: 1.81e-16 at n = 48 against 1.59e-16 with the LDS passes).
 template <int R, bool INV>
 __device__ __forceinline__ void twiddle_tab(double2 (&v)[R], const double2* __restrict__ tw, int e) {
 #pragma unroll
@@ -113,7 +96,7 @@ __global__ __launch_bounds__(256) void zmix_kernel(ZMix a, const double2* __rest
     }
     if (INV && n2 == 0 && row < a.nr) v[0].x += proxy_part(a.proxy, (int)f, a.node[row], a.node[a.nr + row]);
     Dft<R1, INV>::run(v);
-    twiddle<R1, INV>(v, tw, n2);
+    twiddle_tab<R1, INV>(v, tw, n2);
     double2* d = T + line * (R1 * RS) + n2;
 #pragma unroll
     for (int c = 0; c < R1; ++c) d[c * RS] = v[c];
