@@ -499,7 +499,7 @@ mlg_status mlg_tp_advance(mlg_plan p, const double* U, void* psi, void* chi, voi
                   const double* b0, const double* b1, double* o0, double* o1) -> mlg_status {
     const double *sv[2] = {s0, s1}, *av[2] = {a0, a1}, *bv[2] = {b0, b1};
     double* ov[2] = {o0, o1};
-    return launch_steps(p, 2, mode, which, sv, av, bv, ov, s);
+    return launch_steps(p, 2, mode, which, sv, av, bv, ov, partition(p, ws).T[0], s);
   };
   // the adaptive modal filter between steps (Sec. 3.3), when enabled
   auto filter = [&]() -> mlg_status {

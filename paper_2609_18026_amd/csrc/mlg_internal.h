@@ -121,7 +121,7 @@ struct mlg_plan_s {
   double* d_step_u = nullptr;     // m = 0: u_j = sum_n X_{0 n} V[n][j]
   int64_t* d_step_qoff = nullptr; // per m offsets into fwd / bwd (M + 1)
   int64_t* d_step_loff = nullptr; // per m offsets into lam (M + 1)
-  double* d_step_w = nullptr;     // scratch of two fields: each tau * nz complex + (nrc - 1) * nz complex
+  double* d_step_w = nullptr;     // scratch of one field: tau * nz complex + (nrc - 1) * nz complex
   int step_maxk = 0;
   double step_dt = 0, step_nu = 0, step_nuh = 0;
   int step_q = 1;                 // p / 2 (hyperviscosity power of grad^2), 1 when nu_h = 0
@@ -221,9 +221,11 @@ mlg_status launch_split_zdft(const mlg_plan_s* p, const double* const* in, doubl
 mlg_status step_setup(mlg_plan_s* p, const mlg_dissip* d);
 mlg_status launch_step(const mlg_plan_s* p, int mode, int which, const double* s, const double* a1, const double* a0,
                        double* out, hipStream_t st);
-// the same step of nf = 1 or 2 fields in one pair of launches
+// the same step of nf = 1 or 2 fields in one pair of launches; scratch: that of the second field, two triangular arrays
+// (the workspace's, which is free between the right-hand sides)
 mlg_status launch_steps(const mlg_plan_s* p, int nf, int mode, int which, const double* const* s,
-                        const double* const* a1, const double* const* a0, double* const* out, hipStream_t st);
+                        const double* const* a1, const double* const* a0, double* const* out, double* scratch,
+                        hipStream_t st);
 // s1 = 2 half - full over all spectral elements (the Richardson start-up of Sec. 3.3)
 mlg_status launch_richardson(const mlg_plan_s* p, const double* half, const double* full, double* out,
                              hipStream_t st);

@@ -703,7 +703,7 @@ mlg_status step_setup(mlg_plan_s* p, const mlg_dissip* d) {
   if ((st = upl(&p->d_step_fwd, fwd)) || (st = upl(&p->d_step_bwd, bwd)) || (st = upl(&p->d_step_lam, lam)) ||
       (st = upl(&p->d_step_u, u)) || (st = upl(&p->d_step_qoff, qoff)) || (st = upl(&p->d_step_loff, loff)))
     return st;
-  const size_t wel = 2 * ((size_t)p->tau + std::max(nrc - 1, 1)) * nz * 2;  // two fields
+  const size_t wel = ((size_t)p->tau + std::max(nrc - 1, 1)) * nz * 2;  // one field
   hipError_t e = hipMalloc(reinterpret_cast<void**>(&p->d_step_w), wel * sizeof(double));
   if (e != hipSuccess) {
     p->d_step_w = nullptr;
@@ -726,13 +726,15 @@ mlg_status step_setup(mlg_plan_s* p, const mlg_dissip* d) {
 
 mlg_status launch_step(const mlg_plan_s* p, int mode, int which, const double* s, const double* a1, const double* a0,
                        double* out, hipStream_t st) {
-  return launch_steps(p, 1, mode, which, &s, &a1, &a0, &out, st);
+  return launch_steps(p, 1, mode, which, &s, &a1, &a0, &out, nullptr, st);
 }
 
 mlg_status launch_steps(const mlg_plan_s* p, int nf, int mode, int which, const double* const* s,
-                        const double* const* a1, const double* const* a0, double* const* out, hipStream_t st) {
+                        const double* const* a1, const double* const* a0, double* const* out, double* scratch,
+                        hipStream_t st) {
   StepArgs a{};
-  const size_t w_len = (size_t)p->tau * p->nz, w0_len = (size_t)std::max(p->nrc - 1, 1) * p->nz;
+  const size_t w_len = (size_t)p->tau * p->nz;
+  if (nf > 1 && !scratch) return fail(MLG_E_ARG, "step: a second field needs scratch");
   a.nf = nf;
   for (int i = 0; i < nf; ++i) {
     StepField& f = a.f[i];
@@ -740,7 +742,7 @@ mlg_status launch_steps(const mlg_plan_s* p, int nf, int mode, int which, const 
     f.a1 = reinterpret_cast<const double2*>(a1[i]);
     f.a0 = mode == 1 ? reinterpret_cast<const double2*>(a0[i]) : nullptr;
     f.out = reinterpret_cast<double2*>(out[i]);
-    f.W = reinterpret_cast<double2*>(p->d_step_w) + i * (w_len + w0_len);
+    f.W = reinterpret_cast<double2*>(i ? scratch : p->d_step_w);
     f.W0 = f.W + w_len;
   }
   a.fwd = p->d_step_fwd;
