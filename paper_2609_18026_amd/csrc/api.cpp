@@ -441,9 +441,9 @@ mlg_status mlg_filter_setup(mlg_plan p, const mlg_filter_cfg* cfg) {
       return fail(MLG_E_ALLOC, std::string("hipMalloc: ") + hipGetErrorString(e));
     }
   }
-  const std::vector<double> zero(kFilterDoubles, 0.0);
+  static const double zero[kFilterDoubles] = {};  // no host allocation, which could throw across the C entry
   MLG_HIP_TRY(hipDeviceSynchronize());
-  MLG_HIP_TRY(hipMemcpy(p->d_filter, zero.data(), bytes, hipMemcpyHostToDevice));
+  MLG_HIP_TRY(hipMemcpy(p->d_filter, zero, bytes, hipMemcpyHostToDevice));
   p->filter_zc = cfg->zeta_c;
   p->filter_tau = cfg->tau;
   p->filter_epsmax = cfg->eps_max;
