@@ -86,15 +86,17 @@ struct MMArgs {
   float gscale;        // LOSS: 2 / (nvalid * N)
 };
 
-// A panel of NR rows (64 or 32) and KP contraction entries at most, in registers between the loads and the LDS
-// store.  KC: element (r, k) at src[r * ld + k], 256 / NR threads per row with 16-byte pieces of k in turn;
+// A panel of NR rows (64 or 32) and KP contraction entries (a multiple of 32) at most, in registers between the loads and the
+// LDS store.  KC: element (r, k) at src[r * ld + k], 256 / NR threads per row with 16-byte pieces of k in turn;
 // otherwise at src[k * ld + r], threads over 8-row pieces and pairs of k.  Rows >= R and entries past the
 // panel's kn read as zero.
-constexpr int KP = 288;       // the widest layer's contraction, and the row chunk of a weight gradient: one panel
-constexpr int KS = KP + 8;    // row stride in LDS: 148 words, so that the 16-byte reads of 16 rows spread over the banks
+constexpr int KALL = 288;     // the widest layer's contraction, and the row chunk of a weight gradient: one panel
+// row stride in LDS: 148 words (20 in panels of 32 entries), so that the 16-byte reads of 16 rows spread over the banks
+constexpr int kstride(int KP) { return KP + 8; }
 
-template <int NR, bool KC>
+template <int NR, bool KC, int KP>
 struct Panel {
+  static constexpr int KS = kstride(KP);
   static constexpr int TPR = 256 / NR;                                // KC: threads per row
   static constexpr int TPK = NR / 8, PAIRS = 256 / TPK;               // otherwise: threads per k, pairs of k per pass
   static constexpr int NQ = (KP / 2 + PAIRS - 1) / PAIRS;             // passes
@@ -138,25 +140,31 @@ __device__ __forceinline__ bf16x8 frag(const unsigned short* p) {
 }
 
 constexpr int BN = 32;  // columns per block (64 rows): 512 blocks for a 4096-row layer, two per CU
+// Forward layers of more row tiles take 64 columns and panels of 64 entries: the whole contraction fills the LDS of a CU with two
+// blocks, which is one round up to LONG_TILES row tiles; after that only more blocks per CU hide the loads.  Forward pass
+// (whole contraction / these panels): 4096 rows 23.2 / 27.8 us, 6144 35.9 / 32.5, 20000 81 / 50, 131072 502 / 319.
+constexpr int BN_LONG = 64, KP_LONG = 64, LONG_TILES = 64;
 
+template <int NB, int KP>
 struct MMShared {
-  __attribute__((aligned(16))) unsigned short A[64 * KS];
-  __attribute__((aligned(16))) unsigned short B[BN * KS];
+  __attribute__((aligned(16))) unsigned short A[64 * kstride(KP)];
+  __attribute__((aligned(16))) unsigned short B[NB * kstride(KP)];
   float red[4];
 };
 
-// C = op(A) op(B) on the 64 x BN tile (bx, by) of split bz, 4 waves of 32 x BN / 2, with the layer epilogues.  The
+// C = op(A) op(B) on the 64 x NB tile (bx, by) of split bz, 4 waves of 32 x NB / 2, with the layer epilogues.  The
 // products are small (4096 x 256 x 256: 0.5 us at the matrix rate), so latency bounds them: the whole
 // contraction of a tile is loaded at once, one wait and one barrier, where stages of 32 entries waited
 // for memory 8 times in turn (11 -> 8 us for a 4096-row layer).  The k order of every sum is kept.
-template <bool AK, bool BK, int EPI>
-__device__ __forceinline__ void mm_tile(const MMArgs& a, MMShared& sh, int bx, int by, int bz, int gx) {
+template <bool AK, bool BK, int EPI, int NB = BN, int KP = KALL>
+__device__ __forceinline__ void mm_tile(const MMArgs& a, MMShared<NB, KP>& sh, int bx, int by, int bz, int gx) {
+  constexpr int KS = kstride(KP);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int m0 = by * 64, n0 = bx * BN;
+  const int m0 = by * 64, n0 = bx * NB;
   const int kbeg = bz * a.kchunk;
   const int kend = min(a.K, kbeg + a.kchunk);
-  constexpr int NJ = BN / 32;
-  const int wm = (wave >> 1) * 32, wn = (wave & 1) * (BN / 2);
+  constexpr int NJ = NB / 32;
+  const int wm = (wave >> 1) * 32, wn = (wave & 1) * (NB / 2);
   floatx4 acc[2][NJ];
 #pragma unroll
   for (int i = 0; i < 2; ++i)
@@ -164,8 +172,8 @@ __device__ __forceinline__ void mm_tile(const MMArgs& a, MMShared& sh, int bx, i
     for (int j = 0; j < NJ; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
   for (int k0 = kbeg; k0 < kend; k0 += KP) {
     const int kn = min(KP, kend - k0);
-    Panel<64, AK> pa;
-    Panel<BN, BK> pb;
+    Panel<64, AK, KP> pa;
+    Panel<NB, BK, KP> pb;
     pa.load(a.A, a.lda, m0, a.M, k0, kn, tid);
     pb.load(a.B, a.ldb, n0, a.N, k0, kn, tid);
     if (k0 > kbeg) __syncthreads();
@@ -252,18 +260,18 @@ __device__ __forceinline__ bool split_tile(int b, int gx, int gy, int splits, in
   return bz < splits;
 }
 
-template <int EPI>
+template <int EPI, int NB, int KP>
 __global__ __launch_bounds__(256) void mm_kernel(MMArgs a, int gx, int gy) {
-  __shared__ MMShared sh;
+  __shared__ MMShared<NB, KP> sh;
   int bx, by;
-  if (row_tile(blockIdx.x, gx, gy, bx, by)) mm_tile<true, true, EPI>(a, sh, bx, by, 0, gx);
+  if (row_tile(blockIdx.x, gx, gy, bx, by)) mm_tile<true, true, EPI, NB, KP>(a, sh, bx, by, 0, gx);
 }
 
 // A weight gradient and the backpropagated dz of the layer below, which do not depend on each other, in one
 // launch: blocks 0 .. nw - 1 are the gradient's tiles (gxw x gyw x splits), the others dz's.
 __global__ __launch_bounds__(256) void backward_kernel(MMArgs w, MMArgs d, int nw, int gxw, int gyw, int splits, int gxd,
                                                        int gyd) {
-  __shared__ MMShared sh;
+  __shared__ MMShared<BN, KALL> sh;
   const int b = blockIdx.x;
   int bx, by, bz;
   if (b < nw) {
@@ -310,7 +318,7 @@ __device__ __forceinline__ void colsum(const unsigned short* dy, const unsigned 
 __global__ __launch_bounds__(256) void backward_last_kernel(MMArgs w, int nw, int gxw, int gyw, int splits,
                                                             const unsigned short* dy, const unsigned short* dz2,
                                                             const unsigned short* dz1, int rows, float* part) {
-  __shared__ MMShared sh;
+  __shared__ MMShared<BN, KALL> sh;
   static_assert(sizeof(sh.A) >= sizeof(unsigned short) * CS_R * CS_C, "the column panel fits in the A panel");
   const int b = blockIdx.x;
   int bx, by, bz;
@@ -594,10 +602,15 @@ mlg_status dalloc(T** p, size_t n) {
   return MLG_OK;
 }
 
+// columns per block of a forward layer of 'rows' rows
+int mm_columns(int rows) { return (rows + 63) / 64 > LONG_TILES ? BN_LONG : BN; }
+
 template <int EPI>
 mlg_status mm(const MMArgs& a, hipStream_t s) {
-  const int gx = (a.N + BN - 1) / BN, gy = (a.M + 63) / 64;
-  hipLaunchKernelGGL((mm_kernel<EPI>), dim3(row_blocks(gx, gy)), dim3(256), 0, s, a, gx, gy);
+  const int nb = mm_columns(a.M), gx = (a.N + nb - 1) / nb, gy = (a.M + 63) / 64;
+  const dim3 grid(row_blocks(gx, gy));
+  if (gy > LONG_TILES) hipLaunchKernelGGL((mm_kernel<EPI, BN_LONG, KP_LONG>), grid, dim3(256), 0, s, a, gx, gy);
+  else hipLaunchKernelGGL((mm_kernel<EPI, BN, KALL>), grid, dim3(256), 0, s, a, gx, gy);
   MLG_HIP_TRY(hipGetLastError());
   return MLG_OK;
 }
@@ -1078,7 +1091,7 @@ mlg_status mlg_closure_train_step(mlg_closure c, const float* data_x, const floa
   MLG_HIP_TRY(hipGetLastError());
   if (mlg_status st = run_forward(c, rows, nb, nullptr, s)) return st;
   if (loss_out) {
-    const int nparts = (rows / 64) * (NOUT / BN);
+    const int nparts = (rows / 64) * (NOUT / mm_columns(rows));
     hipLaunchKernelGGL(loss_kernel, dim3(1), dim3(256), 0, s, c->d_loss_part, nparts,
                        1.0f / ((float)nb * (float)NOUT), c->d_loss);
     MLG_HIP_TRY(hipGetLastError());
