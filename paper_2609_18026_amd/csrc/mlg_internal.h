@@ -127,7 +127,7 @@ struct mlg_plan_s {
   int step_q = 1;                 // p / 2 (hyperviscosity power of grad^2), 1 when nu_h = 0
   bool step_ready = false;
   // adaptive modal filter (mlg_filter_setup): d_filter holds [eps_psi, eps_chi, f_psi, f_chi], then
-  // 2 * FILTER_BLOCKS partial sums of each field and a block counter of each field
+  // 2 * FILTER_BLOCKS partial sums of each field and the last eps of each field
   double* d_filter = nullptr;
   bool filter_on = false;
   double filter_zc = 0, filter_tau = 0, filter_epsmax = 0, filter_relax = 0;
@@ -231,7 +231,7 @@ mlg_status launch_richardson(const mlg_plan_s* p, const double* half, const doub
                              hipStream_t st);
 // adaptive modal filter of Sec. 3.3 on packed spectral fields: spec[i] (i < nf) with state slot 'slot' + i
 constexpr int FILTER_BLOCKS = 256;
-constexpr size_t kFilterDoubles = 4 + 4 * FILTER_BLOCKS + 1;  // states, partial sums of two fields, two counters
+constexpr size_t kFilterDoubles = 4 + 4 * FILTER_BLOCKS + 2;  // states, partial sums and last eps of two fields
 mlg_status launch_filter(const mlg_plan_s* p, int slot, int nf, double* const* spec, hipStream_t s);
 // plan.cpp: L Lambda = nu g + nu_h (-Dbar_0)^{q-1} g on the m = 0 degrees (g: the image of
 // grad_h^2 Lambda, Eq. logproxy), in long double
