@@ -375,6 +375,7 @@ __global__ __launch_bounds__(GT) void step_fwd1_kernel(StepArgs a) {
   const double2* __restrict__ p1 = fd.a1 + rb;
   const double2* __restrict__ p0 = (fd.a0 ? fd.a0 : fd.a1) + rb;
   const bool ab = fd.a0 != nullptr;
+  const double c1 = ab ? 3.0 : 1.0;
   double z[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};  // V^{-1} s and V^{-1} a of row jl, of row jl + 1
   for (int k0 = 0; k0 < K; k0 += GC) {
     double2 sv[GV], x1[GV], x0[GV];
@@ -383,7 +384,7 @@ __global__ __launch_bounds__(GT) void step_fwd1_kernel(StepArgs a) {
       const int k = k0 + t * GT + threadIdx.x;
       sv[t] = k < K ? s[k] : make_double2(0.0, 0.0);
       x1[t] = k < K ? p1[k] : make_double2(0.0, 0.0);
-      x0[t] = k < K ? p0[k] : make_double2(0.0, 0.0);
+      x0[t] = ab && k < K ? p0[k] : make_double2(0.0, 0.0);  // FE-BE has none (times a zero, an infinity would leave a NaN)
     }
     dpair v[GU];
 #pragma unroll
@@ -395,8 +396,7 @@ __global__ __launch_bounds__(GT) void step_fwd1_kernel(StepArgs a) {
     for (int t = 0; t < GV; ++t) {
       if (GC < GT && (int)threadIdx.x >= GC) break;
       xs[t * GT + threadIdx.x] = sv[t];
-      // FE-BE takes A as it is (1 A - 0 A would make a NaN of an infinity)
-      xa[t * GT + threadIdx.x] = ab ? make_double2(3.0 * x1[t].x - x0[t].x, 3.0 * x1[t].y - x0[t].y) : x1[t];
+      xa[t * GT + threadIdx.x] = make_double2(c1 * x1[t].x - x0[t].x, c1 * x1[t].y - x0[t].y);
     }
     __syncthreads();
 #pragma unroll
