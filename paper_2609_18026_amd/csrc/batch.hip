@@ -432,7 +432,11 @@ __global__ __launch_bounds__(256, PHASE == 0 ? 6 : (PHASE == 1 ? 4 : 5)) void ba
 constexpr int RC_S = 32;  // degrees per segment
 constexpr int RC_B = 8;   // degrees per scalar load, backward
 constexpr int RC_F = 8;   // degrees per transposing sum, forward
-constexpr int RC_W = 2;   // wavefronts per order
+// Wavefronts per order: RC_FEW up to RC_ITEMS orders in the launch (one a SIMD), where the chip has places to spare and the chain of
+// an order bounds the phase, 2 above.  One instance of 256 x 16, all three phases: 24.9 -> 17.5 us (FP32 with forward tables, before: 21.2),
+// 64 of 256 x 16 (384 orders) 43.1 -> 32.8, 12 of 256 x 256 (1032) 41.8 / 39.6; 64 of 128 x 128 (2752) 52.4 / 52.0 (FP32 47.3 / 48.4),
+// 512 of 16 x 16 (3072) 18.4 / 20.4.
+constexpr int RC_FEW = 4, RC_ITEMS = 1024;
 
 // Touches the lines of a wavefront's recurrence or coefficients, so that the scalar loads of the backward phase find them in the
 // L2: 18.8 -> 15.4 us (nothing forward, where a degree takes longer than its loads).
@@ -467,11 +471,10 @@ struct Recurrence {
   }
 };
 
-template <typename T, int NPL>
+template <typename T, int NPL, int W>
 __device__ __forceinline__ void recur_backward(const double* __restrict__ tab, const Cx<T>* __restrict__ spec,
                                                Cx<T>* __restrict__ mix, const RadialItem& I, int wave) {
-  __shared__ Cx<double> part[(RC_W - 1) * 2 * 64 * NPL];  // [wave][parity][node] of the wavefronts after the first
-  constexpr int W = RC_W;
+  __shared__ Cx<double> part[(W - 1) * 2 * 64 * NPL];  // [wave][parity][node] of the wavefronts after the first
   const int lane = threadIdx.x & 63, K = I.K, nr = I.nr, nh = (nr + 1) / 2;
   const int segs = (K + RC_S - 1) / RC_S, seg = wave * segs / W;
   const int end = min((wave + 1) * segs / W * RC_S, K);
@@ -563,10 +566,9 @@ __device__ __forceinline__ double dpp_sum(double a, double b, bool bit) {
   return (bit ? b : a) + dpp_partner<CTRL>(bit ? a : b);
 }
 
-template <typename T, int NPL>
+template <typename T, int NPL, int W>
 __device__ __forceinline__ void recur_forward(const double* __restrict__ tab, const Cx<T>* __restrict__ mix,
                                               Cx<T>* __restrict__ spec, const RadialItem& I, int wave) {
-  constexpr int W = RC_W;
   const int lane = threadIdx.x & 63, K = I.K, nr = I.nr, nh = (nr + 1) / 2;
   const int segs = (K + RC_S - 1) / RC_S, seg = wave * segs / W;
   const int end = min((wave + 1) * segs / W * RC_S, K);
@@ -617,23 +619,23 @@ __device__ __forceinline__ void recur_forward(const double* __restrict__ tab, co
   }
 }
 
-template <typename T, bool FWD>
-__global__ __launch_bounds__(64 * RC_W) void batch_recur_kernel(const RadialItem* __restrict__ items,
+template <typename T, bool FWD, int W>
+__global__ __launch_bounds__(64 * W) void batch_recur_kernel(const RadialItem* __restrict__ items,
                                                                 const double* __restrict__ tab,
                                                                 const Cx<T>* __restrict__ in, Cx<T>* __restrict__ out) {
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const RadialItem I = items[blockIdx.x];
   if constexpr (FWD) {
     if (I.nr == 0) {
-      for (int t = threadIdx.x; t < I.K; t += 64 * RC_W) out[I.spec + t] = cx<T>(0, 0);
+      for (int t = threadIdx.x; t < I.K; t += 64 * W) out[I.spec + t] = cx<T>(0, 0);
     } else if (I.nr <= 128) {
-      recur_forward<T, 1>(tab, in, out, I, wave);
+      recur_forward<T, 1, W>(tab, in, out, I, wave);
     } else {
-      recur_forward<T, 2>(tab, in, out, I, wave);
+      recur_forward<T, 2, W>(tab, in, out, I, wave);
     }
   } else {
-    if (I.nr <= 128) recur_backward<T, 1>(tab, in, out, I, wave);
-    else recur_backward<T, 2>(tab, in, out, I, wave);
+    if (I.nr <= 128) recur_backward<T, 1, W>(tab, in, out, I, wave);
+    else recur_backward<T, 2, W>(tab, in, out, I, wave);
   }
 }
 
@@ -690,11 +692,13 @@ mlg_status run_batch(const mlg_batch_s* bt, double gamma, const void* in, void* 
   A.gamma = (T)gamma;
   const size_t rad = radial_smem(bt, c.threads);
   const unsigned th = (unsigned)c.threads;
-  if (c.recurrence) batch_recur_kernel<T, false><<<A.nitems[0], 64 * RC_W, 0, s>>>(A.radial[0], A.tab, A.spec_in, A.mix);
-  else batch_kernel<T, 0><<<c.blocks[0], th, rad, s>>>(A);
+  if (!c.recurrence) batch_kernel<T, 0><<<c.blocks[0], th, rad, s>>>(A);
+  else if (A.nitems[0] > RC_ITEMS) batch_recur_kernel<T, false, 2><<<A.nitems[0], 128, 0, s>>>(A.radial[0], A.tab, A.spec_in, A.mix);
+  else batch_recur_kernel<T, false, RC_FEW><<<A.nitems[0], 64 * RC_FEW, 0, s>>>(A.radial[0], A.tab, A.spec_in, A.mix);
   batch_kernel<T, 1><<<c.blocks[1], th, phi_smem(bt, c.lines), s>>>(A);
-  if (c.recurrence) batch_recur_kernel<T, true><<<A.nitems[2], 64 * RC_W, 0, s>>>(A.radial[1], A.tab, A.mix, A.spec_out);
-  else batch_kernel<T, 2><<<c.blocks[2], th, rad, s>>>(A);
+  if (!c.recurrence) batch_kernel<T, 2><<<c.blocks[2], th, rad, s>>>(A);
+  else if (A.nitems[0] > RC_ITEMS) batch_recur_kernel<T, true, 2><<<A.nitems[2], 128, 0, s>>>(A.radial[1], A.tab, A.mix, A.spec_out);
+  else batch_recur_kernel<T, true, RC_FEW><<<A.nitems[2], 64 * RC_FEW, 0, s>>>(A.radial[1], A.tab, A.mix, A.spec_out);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return fail(MLG_E_DEVICE, std::string("batch kernel launch: ") + hipGetErrorString(e));
   return MLG_OK;
