@@ -54,7 +54,7 @@ struct BatchInst {
 // chain item -> instance -> triangular offset -> data cost three more dependent loads.  nr == 0: K zeros at spec.
 struct RadialItem {
   int64_t spec, mix, tab, rec, start, node;
-  int nr, K, m, pad;
+  int nr, K;
 };
 
 // One group of lines in the azimuthal phase.
@@ -109,10 +109,6 @@ template <typename T>
 __device__ __forceinline__ Cx<T> operator+(Cx<T> a, Cx<T> b) { return cx(a.x + b.x, a.y + b.y); }
 template <typename T>
 __device__ __forceinline__ Cx<T> operator-(Cx<T> a, Cx<T> b) { return cx(a.x - b.x, a.y - b.y); }
-template <typename T>
-__device__ __forceinline__ Cx<T> operator*(Cx<T> a, Cx<T> b) {
-  return cx(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
-}
 template <typename T>
 __device__ __forceinline__ Cx<T> scl(Cx<T> a, T s) { return cx(a.x * s, a.y * s); }
 
@@ -785,13 +781,13 @@ mlg_status build_radial(mlg_batch_s* bt, const std::vector<int64_t>& tri) {
     int64_t start = I.start_off;
     for (int m = 0; m < I.mact; start += rec_states(I.nrc - m) * nh, ++m) {
       RadialItem it{I.spec_off + off[m], I.mix_off + (int64_t)m * I.nr, I.tb_off + off[m] * nh, I.rec_off + 2 * off[m],
-                    start, I.node_off, I.nr, I.nrc - m, m, 0};
+                    start, I.node_off, I.nr, I.nrc - m};
       w[0].push_back(it);
       it.tab = I.tf_off + off[m] * nh;
       w[1].push_back(it);
     }
     if (off[I.M] > off[I.mact])
-      w[1].push_back(RadialItem{I.spec_off + off[I.mact], 0, 0, 0, 0, 0, 0, (int)(off[I.M] - off[I.mact]), 0, 0});
+      w[1].push_back(RadialItem{I.spec_off + off[I.mact], 0, 0, 0, 0, 0, 0, (int)(off[I.M] - off[I.mact])});
     off += I.M + 1;
   }
   for (int p = 0; p < 2; ++p) {

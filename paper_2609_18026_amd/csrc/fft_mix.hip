@@ -45,8 +45,6 @@ __device__ __forceinline__ void twiddle_tab(double2 (&v)[R], const double2* __re
 #define MIX_WIDE(X) \
   X(15, 12) X(16, 12) X(15, 15) X(16, 15)
 
-__device__ __forceinline__ int kval(int kk, int nz) { return (2 * kk < nz) ? kk : kk - nz; }
-
 // ---------------------------------------------------------------- z transforms
 // Contiguous lines, lb lines per block.  Lane (line, n2) of the first pass loads x[n2 + R2 n1] straight
 // into registers; lane (line, k1) of the second stores X[k1 + R1 k2].  In LDS a line is R1 rows of RS
@@ -132,7 +130,7 @@ __global__ __launch_bounds__(256) void zmix_kernel(ZMix a, const double2* __rest
 // takes 2^lbs lines (or pairs of lines); in LDS entry (k, line) sits at k * row + line, so the lanes of
 // every access run over the lines first: 16-byte entries side by side, whatever the order k.
 struct PhiMix {
-  int n, R1, R2, lbs, nr, nz;
+  int n, lbs, nr, nz;
   int min_, mout;       // orders read (the others enter as zero) and orders written
   int64_t nlines;
 };
@@ -538,9 +536,10 @@ bool phi_vec_mix_ok(const mlg_plan_s* p) {
 
 mlg_status launch_phi_vec_mix(const mlg_plan_s* p, const double* U, double* const* f6, double* taps, hipStream_t s) {
   PhiMix g = phi_mix(p, p->g.dealias != 0);
-  if (!mix_pair(p->nphi, false, &g.R1, &g.R2)) return fail(MLG_E_UNSUPPORTED, "phi stage: length without a radix pair");
+  int R1, R2;
+  if (!mix_pair(p->nphi, false, &R1, &R2)) return fail(MLG_E_UNSUPPORTED, "phi stage: length without a radix pair");
   g.lbs = 3;
-  while (g.lbs < 5 && (g.R1 << g.lbs) < 64) ++g.lbs;
+  while (g.lbs < 5 && (R1 << g.lbs) < 64) ++g.lbs;
   const size_t shm = ((size_t)2 * (g.n << g.lbs) + g.n) * sizeof(double2);
   Six six;
   for (int i = 0; i < 6; ++i) six.f[i] = reinterpret_cast<double2*>(f6[i]);

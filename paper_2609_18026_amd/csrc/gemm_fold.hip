@@ -246,9 +246,11 @@ struct FoldProjArgs {
 // past the column and of inactive columns are computed but not stored.  Fields are float2 on
 // reduced-precision plans (converted after the load has landed).
 typedef double PairLd __attribute__((ext_vector_type(2), aligned(8)));  // two adjacent table entries
-// Up to PROJ_RG1 pairs the grid, not the loads per MFMA, is what is short (946 wavefronts of 32 pairs for 1024 SIMDs at
-// 128^3): one group per wavefront, two k-steps ahead.  16.3 -> 13.2 us at 96 kept rows x 64 x 32, 35 -> 26.4 at 128^3,
-// 62.5 -> 59.4 at 200 x 128 x 128; at 256^3 it is 245 against 221 us.
+// Up to PROJ_RG1 pairs one group per wavefront, two k-steps ahead; two groups, one step ahead, above.  A short contraction gives a
+// wavefront few k-steps to hide its first loads behind, and the last of two groups is often empty; the wide reuse pays on long ones.
+// Two groups / one (us, kernel alone, N_phi x N_z): 64 pairs 35.7 / 27.4 (128 x 128), 78.5 / 61.7 (256 x 256); 80 pairs 103.5 / 94.3
+// (256 x 256); 96 pairs 138 / 133 (256 x 256), FP32 fields 139 / 127; 100 pairs 25.6 / 19.8 (32 x 32), 26.7 / 28.3 (96 x 64),
+// 62.6 / 57.3 (128 x 128), 144.7 / 144.2 (256 x 256); 128 pairs at 256 x 256 221 / 245.
 constexpr int PROJ_RG1 = 100;
 
 template <typename C2, int D, int RG>

@@ -1014,7 +1014,7 @@ __global__ __launch_bounds__(PS_SEG * PS_COL, SMAX <= 8 ? 2 : 1) void projection
 // kk and of -kk.  Reading each slot with its partner in stage 1, 64 rows a block with one thread a slot, took 52 us and the
 // sum of the parts by one thread a slot 48 us at N_r = 200, N_phi = N_z = 128; now 16.8 and 4.7.
 constexpr int EN_T = 256;
-constexpr int EN_ROWS = 64;   // rows per part that the scratch has to hold
+constexpr int EN_ROWS = 64;   // a plan is accepted where its scratch holds one sum per slot of every EN_ROWS rows
 
 __global__ __launch_bounds__(EN_T) void energy_part_kernel(const double2* __restrict__ ur,
                                                            const double2* __restrict__ up,

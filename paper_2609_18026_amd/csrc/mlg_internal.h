@@ -136,7 +136,8 @@ struct mlg_plan_s {
   double log_cpsi = 0, log_cchi = 0;
   double* d_logf = nullptr;
   bool use_fast_fft = true;   // register-resident 256-point kernels when a length is 256
-  bool use_fold = true;       // parity-folded radial products when N_r is even (MLG_RADIAL_FOLD=0 disables)
+  bool use_fold = true;       // parity-folded radial products: even N_r, and for any N_r the scalar backward
+                              // product and 2D plans (MLG_RADIAL_FOLD=0 disables)
   int phi_rad[12] = {0};
   int phi_nrad = 0;
   int z_rad[12] = {0};
