@@ -39,25 +39,25 @@ U_FRAME = (0.0, 1.0, 0.0)
 # kernel source hashes to the one that was measured (profiles/rhs_tp_256cubed_kernels.md).
 _SUMMARY = "profiles/rhs_tp_256cubed_kernels.md"
 MEASURED_TRAFFIC = {
-    "synth_gemm": {"bytes": 570752743, "launches": 1, "n": 256,
+    "synth_gemm": {"bytes": 564429541, "launches": 1, "n": 256,
                    "source": "paper_2609_18026_amd/csrc/gemm_fold.hip",
-                   "sha256": "f4a0f702484fbf98751cd20659c2689655334ac4627dbb4ccb4332c7beeb5fcc",
-                   "profile_avg_ms": 0.2729, "mfma_counter_flops": 11.77e9, "mfma_busy_pct": 59.1},
-    "proj_gemm": {"bytes": 408833265, "launches": 1, "n": 256,
+                   "sha256": "d5a708330c25438b82944ef7f4909c0adc51e8bdd76a52e4a745c59024b1d182",
+                   "profile_avg_ms": 0.2658, "mfma_counter_flops": 11.77e9, "mfma_busy_pct": 59.1},
+    "proj_gemm": {"bytes": 405482499, "launches": 1, "n": 256,
                   "source": "paper_2609_18026_amd/csrc/gemm_fold.hip",
-                  "sha256": "f4a0f702484fbf98751cd20659c2689655334ac4627dbb4ccb4332c7beeb5fcc",
-                  "profile_avg_ms": 0.2119, "mfma_counter_flops": 8.82e9, "mfma_busy_pct": 56.5},
-    "phi_fft": {"bytes": 811893208, "launches": 1, "n": 256,
+                  "sha256": "d5a708330c25438b82944ef7f4909c0adc51e8bdd76a52e4a745c59024b1d182",
+                  "profile_avg_ms": 0.2072, "mfma_counter_flops": 8.82e9, "mfma_busy_pct": 56.2},
+    "phi_fft": {"bytes": 811888566, "launches": 1, "n": 256,
                 "source": "paper_2609_18026_amd/csrc/fft256.hip",
-                "sha256": "0af234d19557e3211f2e7bfc0a1f1dad41c5692ef4e35003d44cebef8e25ce03",
-                "profile_avg_ms": 0.221},
-    "z_fft": {"bytes": 913157899 + 452430330, "launches": 2, "n": 256,
+                "sha256": "ddcf9e3aa85acfb1956892ccc9c9a054b856d793905e039b14366183b13b611f",
+                "profile_avg_ms": 0.2153},
+    "z_fft": {"bytes": 913156771 + 452427331, "launches": 2, "n": 256,
               "source": "paper_2609_18026_amd/csrc/fft256.hip",
-              "sha256": "0af234d19557e3211f2e7bfc0a1f1dad41c5692ef4e35003d44cebef8e25ce03"},
-    "projection": {"bytes": 510715433, "launches": 1, "n": 256,
+              "sha256": "ddcf9e3aa85acfb1956892ccc9c9a054b856d793905e039b14366183b13b611f"},
+    "projection": {"bytes": 512571458, "launches": 1, "n": 256,
                    "source": "paper_2609_18026_amd/csrc/kernels.hip",
-                   "sha256": "0c6f72ebed826dbc463c4d0594ca884358824ecb775e6435952dbab288e27a90",
-                   "profile_avg_ms": 0.1415},
+                   "sha256": "7c27c9ce5c25fb71837625c409dc25a2d7b956e51f5a085bac579276a351d4a4",
+                   "profile_avg_ms": 0.1402},
 }
 
 

@@ -296,7 +296,8 @@ __device__ void phase_backward(const BatchArgs<T>& A, const RadialItem I, char* 
 // Azimuthal phase: np pairs of lines, each pair one complex line.  Bound by latency: load, stages and store of an item follow
 // each other with a barrier between them, so what counts is few stages and every item resident at once.  Loads run over the
 // lines of an order first (L adjacent nodes, 128 bytes for 8).  64 instances as above: radix-2 to 5 passes between two
-// buffers 25 us, of which about 8 were a second turn of blocks and 4 the launch; now 17.5 at 12 lines in 256 threads, 19 at 8 in 128.
+// buffers 25 us, of which about 8 were a second turn of blocks and 4 the launch; now 18.4 at 8 lines in 128 threads, the shape that the
+// autotuner takes (17.5 at 12 lines in 256, which it does not try).
 template <typename T>
 __device__ void phase_phi(const BatchArgs<T>& A, const PhiItem I, char* smem) {
   const int n = I.nphi, q0 = I.q0, L = A.lines, np = L / 2, nr = I.nr, mact = I.mact, pitch = bpitch(n);
